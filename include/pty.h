@@ -162,9 +162,14 @@ int32_t pty_checkpoint_every(const pty_ctx* ctx);
  * in LDS and one workgroup per (position, mode) runs every slice with its
  * tile resident (used when every slice is checkpointed and the object
  * gradient is accumulated with atomics, else two-pass; the ePIE engine and
- * the ordered reduction always run two-pass). AUTO (default): TWO_PASS, which
- * measured faster than RESIDENT at N = 128 (8 slices, 4 modes) and equal at
- * N = 64. */
+ * the ordered reduction always run two-pass). AUTO (default): for N = 64 and
+ * 128 the chain kernels, which hold a tile in the registers of one workgroup
+ * through every slice (one launch forward, one for the adjoint) and sum the
+ * object gradient in batch order under either reduction; they need float
+ * checkpoints, a propagator that separates into a k_y and a k_x factor (any
+ * circular band limit, or a mask whose rows are centred intervals) and
+ * obj_w <= 2^20. Everything else under AUTO, and the ePIE and LSQML engines,
+ * run TWO_PASS. */
 #define PTY_STRATEGY_AUTO 0
 #define PTY_STRATEGY_TWO_PASS 1
 #define PTY_STRATEGY_RESIDENT 2
@@ -174,7 +179,8 @@ pty_status pty_set_strategy(pty_ctx* ctx, int32_t strategy);
  * position's windowed contribution, slice by slice) is accumulated.
  * ATOMIC (default): the adjoint row pass adds each contribution with float
  * atomics; the summation order, and so the last bits of the gradient, vary
- * from run to run. ORDERED: the adjoint row pass stores each position's
+ * from run to run (the chain kernels of PTY_STRATEGY_AUTO use no atomics: under
+ * either mode their sum is in batch order). ORDERED: the adjoint row pass stores each position's
  * contribution in a scratch area allocated at create (max_batch x N x N
  * complex64) and a second kernel adds them tile by tile in batch order, so
  * loss_and_grad and reconstruct_step give bit-identical results on repeated

@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "pty.h"
+#include "pty_chain.hpp"
 #include "pty_internal.h"
 #include "pty_prop.hpp"
 
@@ -80,13 +81,16 @@ void dfree(T*& p) {
   p = nullptr;
 }
 
-// Roots of unity w_N^k = exp(-2 pi i k / N), computed in double.
+// Roots of unity w_N^k = exp(-2 pi i k / N), computed in double, and, for the
+// window sizes of the chain kernels, their twiddle tables behind them.
+size_t roots_len(int N) { return chain_size(N) ? 3 * (size_t)N : (size_t)N; }
 std::vector<float2> roots(int N) {
-  std::vector<float2> t(N);
+  std::vector<float2> t(roots_len(N));
   for (int k = 0; k < N; ++k) {
     double a = 2.0 * kPiD * (double)k / (double)N;
     t[k] = make_float2((float)std::cos(a), (float)-std::sin(a));
   }
+  if (chain_size(N)) chain_table(N, t.data() + N);
   return t;
 }
 
@@ -109,7 +113,7 @@ Sizes ctx_sizes(const pty_geometry* g, int max_batch, int k, int ck_elem = 8, bo
   s.seg_tiles = k > 1 ? (size_t)max_batch * M * (k - 1) : 0;
   s.ws2_tiles = k > 1 ? s.tiles : 0;
   size_t b = 0;
-  b += align256(g->N * sizeof(float2));                             // roots
+  b += align256(roots_len(g->N) * sizeof(float2));                  // roots, twiddle tables
   b += align256((size_t)std::max(S - 1, 0) * N2 * sizeof(float2));  // propagators
   b += align256((size_t)std::max(S - 1, 0) * g->N * sizeof(float4));   // separable factors (y)
   b += align256((size_t)std::max(S - 1, 0) * g->N * sizeof(float2));   // separable factors (x)
@@ -162,12 +166,12 @@ pty_status validate_geometry(const pty_geometry* g, std::string& err) {
 enum ProfClass {
   P_ITEMS, P_COL_SHIFT, P_ROW_FWD, P_COL_PROP, P_FAR_LOSS, P_LOSS_REDUCE, P_ROW_ADJ, P_COL_PROP_ADJ,
   P_COL_FINAL, P_PROBE_GRAD, P_POS_REDUCE, P_PLAIN2D, P_FILL, P_OPTIM, P_RECOMPUTE, P_REG, P_RES_FWD, P_RES_ADJ,
-  P_OBJ_GATHER, P_NCLASS
+  P_OBJ_GATHER, P_CHAIN_FWD, P_CHAIN_ADJ, P_NCLASS
 };
 const char* kProfNames[P_NCLASS] = {"items", "col_shift", "row_fwd", "col_prop", "far_loss", "loss_reduce",
                                     "row_adj", "col_prop_adj", "col_final", "probe_grad", "pos_reduce",
                                     "plain2d", "fill", "optimizer", "recompute", "regularizers", "res_fwd",
-                                    "res_adj", "obj_gather"};
+                                    "res_adj", "obj_gather", "chain_fwd", "chain_adj"};
 
 struct ProfRec { int cls; hipEvent_t a, b; };
 
@@ -210,7 +214,7 @@ struct ProfScope {
 struct pty_ctx {
   pty_geometry g{};
   std::vector<double> dz;
-  int max_batch = 0, ck_every = 1, n_ck = 1;
+  int max_batch = 0, ck_every = 1;
   int chunk = 0;              // positions per launch in fused loss-and-gradient calls (0: all)
   // chunks run concurrently on these streams (created by pty_set_streams, default priority)
   int n_streams = 1;
@@ -299,6 +303,21 @@ bool use_resident(int strategy, int N, int ck_every) {
   return strategy == PTY_STRATEGY_RESIDENT;
 }
 
+// Chain kernels (one launch over all slices, tile in registers): N = 64 and
+// 128 under the AUTO strategy, float checkpoints, and a propagator that
+// separates (any circular limit or centred mask; other masks are read from the
+// N x N table, which the chains' lane order would read one line per lane). A
+// window's rows are addressed with 32-bit offsets, hence the limit on obj_w.
+// Measured against two-pass (group step or gradients): 64 x 64, 2 modes, 8
+// slices, 225 positions 612 -> 231 us; 128 x 128, 2 modes, 5 slices, 77
+// positions 500 -> 332 us; 4 modes, 8 slices, 1024 positions 7.14 -> 6.13 ms.
+// The rule looks at the context alone, so a reconstruction takes the same
+// path, and has the same bits, alone and in a grouped step.
+bool use_chain(const pty_ctx* c) {
+  return c->strategy == PTY_STRATEGY_AUTO && chain_size(c->g.N) && !c->ck_half && c->g.obj_w <= (1 << 20) &&
+         (c->g.n_slices == 1 || c->prop_y);
+}
+
 ReqDev base_req(pty_ctx* c) {
   ReqDev r{};
   r.prop = c->prop;
@@ -313,7 +332,6 @@ ReqDev base_req(pty_ctx* c) {
   r.eps = (float)c->g.eps;
   r.inv_sigma2 = c->g.loss == PTY_LOSS_GAUSSIAN ? (float)(1.0 / (c->g.sigma * c->g.sigma)) : 1.f;
   r.ck_every = c->ck_every;
-  r.n_ck = c->n_ck;
   r.live = c->live;
   r.live_k = c->live_k;
   r.prop_y = c->prop_y;
@@ -339,6 +357,7 @@ LaunchCtx ctx_launch(pty_ctx* c, hipStream_t s, const ReqDev& r, int B) {
   L.loss_part = c->loss_part;
   L.pos_part = c->pos_part;
   L.flags = c->flags;
+  L.chain = use_chain(c) ? 1 : 0;
   L.resident = (use_resident(c->strategy, c->g.N, c->ck_every) && c->reduce != PTY_REDUCE_ORDERED) ? 1 : 0;
   L.cscr = c->reduce == PTY_REDUCE_ORDERED ? c->cscr : nullptr;
   // float checkpoints: the column passes write the stored entry waves' row
@@ -365,15 +384,57 @@ LaunchCtx sub(const LaunchCtx& L, int off, int n) {
   return R;
 }
 
+// Probe spectra of every request (unitary), item descriptors and ramps; the
+// chain kernels' first launch does both and zeroes the dense position gradients.
 void run_prepare(const LaunchCtx& L, int N) {
+  if (L.chain) {
+    ProfScope p(P_ITEMS, L.stream);
+    launch_chain_begin(L, N);
+    return;
+  }
+  for (int q = 0; q < L.n_reqs; ++q) {
+    const ReqDev& r = L.reqs.r[q];
+    ProfScope p(P_PLAIN2D, L.stream);
+    launch_plain2d(N, L.stream, L.tw, r.probe, const_cast<float2*>(r.phat), r.M, false, 1.f / N, false);
+  }
   ProfScope p(P_ITEMS, L.stream);
   launch_items(L, N);
+}
+
+// Zeros the adjoint adds into: the object gradient (the chain kernels write
+// theirs whole) and the dense position gradient (zeroed by run_prepare of a
+// chain step; `prepared`: that has run in this call).
+void clear_grads(const LaunchCtx& L, bool prepared) {
+  for (int q = 0; q < L.n_reqs; ++q) {
+    const ReqDev& r = L.reqs.r[q];
+    if (r.accumulate) continue;
+    ProfScope p(P_FILL, L.stream);
+    if (r.gobj && !L.chain) launch_fill(L.stream, (float*)r.gobj, (size_t)r.S * r.H * r.W * 2, 0.f);
+    if (r.gpos_dense && !(L.chain && prepared)) launch_fill(L.stream, r.gpos_dense, (size_t)r.J * 2, 0.f);
+  }
+}
+
+// Probe gradient from its spectrum: unitary inverse transform.
+void probe_from_spectrum(int N, bool chain, hipStream_t s, const float2* tw, const float2* src, float2* dst, int M,
+                         bool acc) {
+  ProfScope p(P_PLAIN2D, s);
+  if (chain) launch_chain_plain_inv(N, s, tw, src, dst, M, 1.f / N, acc);
+  else launch_plain2d(N, s, tw, src, dst, M, true, 1.f / N, acc);
 }
 
 // Forward passes of the items of L (steps up to the largest S). save: store
 // entry-wave checkpoints and leave the detector-plane gradient seed (after
 // its inverse column DFT) in the workspace.
 void run_forward_chunk(const LaunchCtx& L, int N, int S_max, const std::vector<int>& far_steps, bool save) {
+  if (L.chain) {
+    ChainFwd p{};
+    p.store = save ? 1 : 0;
+    p.from = -1;
+    { ProfScope q(P_CHAIN_FWD, L.stream); launch_chain_fwd(L, N, p); }
+    ProfScope q(P_FAR_LOSS, L.stream);
+    launch_chain_far(L, N, save);
+    return;
+  }
   if (L.resident) {
     { ProfScope p(P_RES_FWD, L.stream); launch_res_fwd(L, N, save); }
     for (int i : far_steps) {
@@ -408,6 +469,49 @@ void run_finish_forward(const LaunchCtx& L, int N) {
 // recomputed per segment); grouped launches store every slice.
 void run_backward_chunk(const LaunchCtx& L, int N, int S_max, const std::vector<int>& final_steps, float scale,
                         int k, float2* ws2, void* seg) {
+  if (L.chain && k == 1) {
+    ChainAdj p{};
+    p.first = 1;
+    p.lo = -1;
+    ProfScope q(P_CHAIN_ADJ, L.stream);
+    launch_chain_adj(L, N, p);
+    return;
+  }
+  if (L.chain) {
+    // one request, the whole group: segment by segment from the last slice,
+    // the object gradient of a segment summed before the next one overwrites
+    // the segment buffer
+    float2* sg = static_cast<float2*>(seg);
+    for (int i1 = S_max - 1; i1 >= 0;) {
+      const int i0 = (i1 / k) * k;
+      if (i1 > i0) {
+        ChainFwd f{};
+        f.from = i0;
+        f.to = i1;
+        f.seg = sg;
+        f.seg_len = k - 1;
+        ProfScope q(P_RECOMPUTE, L.stream);
+        launch_chain_fwd(L, N, f);
+      }
+      ChainAdj a{};
+      a.first = i1 == S_max - 1;
+      a.hi = i1;
+      a.lo = i0 > 0 ? i0 : -1;
+      a.seg = sg;
+      a.seg_len = k - 1;
+      a.seg_base = i0 + 1;
+      { ProfScope q(P_CHAIN_ADJ, L.stream); launch_chain_adj(L, N, a); }
+      ChainFin g{};
+      g.lo = i0;
+      g.slices = i1 - i0 + 1;
+      g.seg = sg;
+      g.seg_len = k - 1;
+      g.seg_base = i0 + 1;
+      { ProfScope q(P_OBJ_GATHER, L.stream); launch_chain_finish(L, N, g, true, false, scale); }
+      i1 = i0 - 1;
+    }
+    return;
+  }
   if (L.resident) {
     { ProfScope p(P_RES_ADJ, L.stream); launch_res_adj(L, N, scale); }
     for (int t : final_steps) {
@@ -488,7 +592,14 @@ void run_backward_chunk(const LaunchCtx& L, int N, int S_max, const std::vector<
   }
 }
 
-void run_finish_backward(const LaunchCtx& L, int N, float scale) {
+void run_finish_backward(const LaunchCtx& L, int N, int S_max, int k, float scale) {
+  if (L.chain) {
+    ChainFin p{};
+    p.slices = k == 1 ? S_max : 0;
+    ProfScope q(P_OBJ_GATHER, L.stream);
+    launch_chain_finish(L, N, p, k == 1, true, scale);
+    return;
+  }
   { ProfScope p(P_PROBE_GRAD, L.stream); launch_probe_grad(L, N, scale); }
   { ProfScope p(P_POS_REDUCE, L.stream); launch_pos_reduce(L, N, scale); }
 }
@@ -509,7 +620,8 @@ pty_status check_call(pty_ctx* c, const void* probe, const void* object, const v
 void run_fused(pty_ctx* c, const LaunchCtx& L0, float scale) {
   const int N = c->g.N, S = c->g.n_slices;
   run_prepare(L0, N);
-  const auto chunks = split_chunks(L0.n_items, c->chunk);
+  // (the chains recompute segments for the whole group at once)
+  const auto chunks = split_chunks(L0.n_items, L0.chain && c->ck_every > 1 ? 0 : c->chunk);
   LaunchCtx L = L0;
   set_chain_final(L, N, chunks.size() == 1);
   // Chunks touch disjoint work tiles, checkpoints and partial sums, so they
@@ -517,7 +629,7 @@ void run_fused(pty_ctx* c, const LaunchCtx& L0, float scale) {
   // write the same words without atomics: the ordered object-gradient gather
   // and the recompute buffers (ws2, seg) shared by every chunk.
   int ns = 1;
-  if (c->n_streams > 1 && chunks.size() > 1 && !L.cscr && c->ck_every == 1 && !L.resident)
+  if (c->n_streams > 1 && chunks.size() > 1 && (!L.cscr || L.chain) && c->ck_every == 1 && !L.resident)
     ns = std::min<int>(c->n_streams, (int)chunks.size());
   if (ns > 1) {
     (void)hipEventRecord(c->ev_fork, L.stream);
@@ -535,8 +647,8 @@ void run_fused(pty_ctx* c, const LaunchCtx& L0, float scale) {
       (void)hipStreamWaitEvent(L.stream, c->ev_join[k], 0);
     }
   }
-  if (L.reqs.r[0].loss_out) run_finish_forward(L, N);
-  run_finish_backward(L, N, scale);
+  if (L.reqs.r[0].loss_out && !L.chain) run_finish_forward(L, N);
+  run_finish_backward(L, N, S, c->ck_every, scale);
 }
 
 }  // namespace
@@ -581,14 +693,13 @@ pty_status pty_create_ex(const pty_geometry* g, const pty_options* o, pty_ctx** 
   c->g.dz = c->dz.data();
   c->max_batch = max_batch;
   c->ck_every = k;
-  c->n_ck = (S + k - 1) / k;
   c->ck_half = o->checkpoint_half ? 1 : 0;
   c->sz = ctx_sizes(g, max_batch, k, ck_elem, o->lsqml != 0);
   const int N = g->N, M = g->n_modes;
   const size_t N2 = (size_t)N * N;
   std::string& e = c->err;
   auto fail = [&](pty_status s) { pty_destroy(c); return s; };
-  if ((st = dmalloc(&c->tw, N, e)) || (st = dmalloc(&c->prop, (size_t)std::max(S - 1, 0) * N2, e)) ||
+  if ((st = dmalloc(&c->tw, roots_len(N), e)) || (st = dmalloc(&c->prop, (size_t)std::max(S - 1, 0) * N2, e)) ||
       (st = dmalloc(&c->phat, (size_t)M * N2, e)) || (st = dmalloc(&c->gphat, (size_t)M * N2, e)) ||
       (st = dmalloc(&c->gprobe, (size_t)M * N2, e)) ||
       (st = dmalloc(&c->gobj, (size_t)S * g->obj_h * g->obj_w, e)) ||
@@ -613,7 +724,7 @@ pty_status pty_create_ex(const pty_geometry* g, const pty_options* o, pty_ctx** 
       return fail(st);
   }
   std::vector<float2> tw = roots(N);
-  if (hipMemcpy(c->tw, tw.data(), N * sizeof(float2), hipMemcpyHostToDevice) != hipSuccess) return fail(PTY_EHIP);
+  if (hipMemcpy(c->tw, tw.data(), tw.size() * sizeof(float2), hipMemcpyHostToDevice) != hipSuccess) return fail(PTY_EHIP);
   std::vector<uint8_t> mask;
   if (g->bandlimit_mask) mask.assign(g->bandlimit_mask, g->bandlimit_mask + N2);
   c->g.bandlimit_mask = nullptr;   // copied above; the caller's array is not kept
@@ -732,8 +843,8 @@ pty_status pty_forward(pty_ctx* c, void* stream, const pty_c64* probe, const pty
   hipStream_t s = (hipStream_t)stream;
   c->tape_valid = false;
   const int N = c->g.N, S = c->g.n_slices;
-  { ProfScope p(P_PLAIN2D, s); launch_plain2d(N, s, c->tw, (const float2*)probe, c->phat, c->g.n_modes, false, 1.f / N, false); }
   ReqDev r = base_req(c);
+  r.probe = (const float2*)probe;
   r.obj = (const float2*)object;
   r.positions = positions;
   r.batch_idx = batch_idx;
@@ -779,8 +890,8 @@ pty_status pty_forward_static(pty_ctx* c, void* stream, const pty_c64* probe, co
   float2* phat = reinterpret_cast<float2*>(base + o_phat);
   hipStream_t s = (hipStream_t)stream;
   c->tape_valid = false;
-  { ProfScope p(P_PLAIN2D, s); launch_plain2d(N, s, c->tw, (const float2*)probe, phat, M, false, 1.f / N, false); }
   ReqDev r = base_req(c);
+  r.probe = (const float2*)probe;
   r.phat = phat;
   r.gphat = nullptr;
   r.obj = (const float2*)object;
@@ -813,8 +924,8 @@ pty_status pty_forward_save(pty_ctx* c, void* stream, const pty_c64* probe, cons
   hipStream_t s = (hipStream_t)stream;
   c->tape_valid = false;
   const int N = c->g.N, S = c->g.n_slices;
-  { ProfScope p(P_PLAIN2D, s); launch_plain2d(N, s, c->tw, (const float2*)probe, c->phat, c->g.n_modes, false, 1.f / N, false); }
   ReqDev r = base_req(c);
+  r.probe = (const float2*)probe;
   r.obj = (const float2*)object;
   r.positions = positions;
   r.batch_idx = batch_idx;
@@ -865,25 +976,17 @@ pty_status backward_impl(pty_ctx* c, void* stream, double grad_scale, const doub
   r.gpos = dense ? nullptr : g_pos;
   r.gpos_dense = dense ? g_pos : nullptr;
   r.accumulate = acc ? 1 : 0;
-  if (dense && g_pos && !acc) {
-    ProfScope p(P_FILL, s);
-    launch_fill(s, g_pos, (size_t)c->g.n_positions * 2, 0.f);
-  }
   r.I_out = nullptr;
   r.loss_out = nullptr;
   r.gphat = g_probe ? c->gphat : nullptr;
   r.scale_dev = scale_dev;
-  if (g_object && !acc) {
-    ProfScope p(P_FILL, s);
-    launch_fill(s, (float*)g_object, (size_t)S * c->g.obj_h * c->g.obj_w * 2, 0.f);
-  }
-  const auto chunks = split_chunks(L.n_items, c->chunk);
+  clear_grads(L, false);
+  const auto chunks = split_chunks(L.n_items, L.chain && c->ck_every > 1 ? 0 : c->chunk);
   set_chain_final(L, N, chunks.size() == 1);
   for (auto& ch : chunks)
     run_backward_chunk(sub(L, ch.first, ch.second), N, S, {S - 1}, (float)grad_scale, c->ck_every, c->ws2, c->seg);
-  run_finish_backward(L, N, (float)grad_scale);
-  if (g_probe)
-  { ProfScope p(P_PLAIN2D, s); launch_plain2d(N, s, c->tw, c->gphat, (float2*)g_probe, c->g.n_modes, true, 1.f / N, acc); }
+  run_finish_backward(L, N, S, c->ck_every, (float)grad_scale);
+  if (g_probe) probe_from_spectrum(N, L.chain, s, c->tw, c->gphat, (float2*)g_probe, c->g.n_modes, acc);
   c->tape_valid = false;
   HIPCHECK(c, hipGetLastError());
   return PTY_OK;
@@ -902,8 +1005,8 @@ pty_status pty_loss_and_grad(pty_ctx* c, void* stream, const pty_c64* probe, con
   c->tape_valid = false;
   const int N = c->g.N, S = c->g.n_slices;
   const bool acc = (flags & PTY_ACCUMULATE) != 0;
-  { ProfScope p(P_PLAIN2D, s); launch_plain2d(N, s, c->tw, (const float2*)probe, c->phat, c->g.n_modes, false, 1.f / N, false); }
   ReqDev r = base_req(c);
+  r.probe = (const float2*)probe;
   r.obj = (const float2*)object;
   r.positions = positions;
   r.batch_idx = batch_idx;
@@ -915,17 +1018,10 @@ pty_status pty_loss_and_grad(pty_ctx* c, void* stream, const pty_c64* probe, con
   r.gpos_dense = dense ? g_pos : nullptr;
   r.accumulate = acc ? 1 : 0;
   r.gphat = g_probe ? c->gphat : nullptr;
-  if (dense && g_pos && !acc) {
-    ProfScope p(P_FILL, s);
-    launch_fill(s, g_pos, (size_t)c->g.n_positions * 2, 0.f);
-  }
-  if (g_object && !acc) {
-    ProfScope p(P_FILL, s);
-    launch_fill(s, (float*)g_object, (size_t)S * c->g.obj_h * c->g.obj_w * 2, 0.f);
-  }
   LaunchCtx L = ctx_launch(c, s, r, B);
+  clear_grads(L, true);
   run_fused(c, L, 1.f);
-  if (g_probe) { ProfScope p(P_PLAIN2D, s); launch_plain2d(N, s, c->tw, c->gphat, (float2*)g_probe, c->g.n_modes, true, 1.f / N, acc); }
+  if (g_probe) probe_from_spectrum(N, L.chain, s, c->tw, c->gphat, (float2*)g_probe, c->g.n_modes, acc);
   HIPCHECK(c, hipGetLastError());
   return PTY_OK;
 }
@@ -993,7 +1089,9 @@ namespace {
 // Cost regularizers: gradients into the dense gradients, cost added to *loss.
 // Fails (PTY_EHIP, message in c->err) when the copy or a hipFFT transform of
 // the spectral term is refused.
-pty_status apply_cost_regularizers(pty_ctx* c, hipStream_t s, const pty_state* st, double* loss) {
+// chain: the step's probe spectrum is stored as the chain kernels hold it
+// (transposed; the phase-plate terms treat both axes alike).
+pty_status apply_cost_regularizers(pty_ctx* c, hipStream_t s, const pty_state* st, double* loss, bool chain) {
   if (!c->reg_on) return PTY_OK;
   const pty_geometry& g = c->g;
   int nb = 0;
@@ -1032,7 +1130,7 @@ pty_status apply_cost_regularizers(pty_ctx* c, hipStream_t s, const pty_state* s
     // unitary DFT
     nq = launch_reg_probe_phase(s, c->phat, c->gphat, g.n_modes, g.N, c->probe_phase_tik, c->probe_phase_tv,
                                 c->rg.tv_delta, c->reg_part + 8192);
-    launch_plain2d(g.N, s, c->tw, c->gphat, c->gprobe, g.n_modes, true, 1.f / g.N, true);
+    probe_from_spectrum(g.N, chain, s, c->tw, c->gphat, c->gprobe, g.n_modes, true);
   }
   if (loss) {
     if (nb) launch_add_cost(s, c->reg_part, nb, loss);
@@ -1176,8 +1274,8 @@ extern "C" pty_status pty_reconstruct_step(pty_ctx* c, void* stream, pty_state* 
   c->tape_valid = false;
   const pty_geometry& g = c->g;
   const int N = g.N, S = g.n_slices;
-  { ProfScope p(P_PLAIN2D, s); launch_plain2d(N, s, c->tw, (const float2*)st->probe, c->phat, g.n_modes, false, 1.f / N, false); }
   ReqDev r = base_req(c);
+  r.probe = (const float2*)st->probe;
   r.obj = (const float2*)st->object;
   r.positions = st->positions;
   r.batch_idx = batch_idx;
@@ -1197,15 +1295,15 @@ extern "C" pty_status pty_reconstruct_step(pty_ctx* c, void* stream, pty_state* 
   if (epie) {
     L.emax = 1;
     L.resident = 0;
+    L.chain = 0;
   }
-  {
+  clear_grads(L, true);
+  if (epie) {
     ProfScope p(P_FILL, s);
-    launch_fill(s, (float*)c->gobj, (size_t)S * g.obj_h * g.obj_w * 2, 0.f);
-    launch_fill(s, c->gpos, (size_t)g.n_positions * 2, 0.f);
-    if (epie) launch_fill(s, c->emax, (size_t)B * S * 2, 0.f);
+    launch_fill(s, c->emax, (size_t)B * S * 2, 0.f);
   }
   run_fused(c, L, 1.f);
-  { ProfScope p(P_PLAIN2D, s); launch_plain2d(N, s, c->tw, c->gphat, c->gprobe, g.n_modes, true, 1.f / N, false); }
+  probe_from_spectrum(N, L.chain, s, c->tw, c->gphat, c->gprobe, g.n_modes, false);
   if (epie) {
     // the chain produced minus the summed updates: O += beta_O dO, P += beta_P dP / B
     ProfScope p(P_OPTIM, s);
@@ -1218,7 +1316,7 @@ extern "C" pty_status pty_reconstruct_step(pty_ctx* c, void* stream, pty_state* 
   }
   {
     ProfScope p(P_REG, s);
-    const pty_status rs = apply_cost_regularizers(c, s, st, loss);
+    const pty_status rs = apply_cost_regularizers(c, s, st, loss, L.chain != 0);
     if (rs != PTY_OK) return rs;
   }
   apply_optimizer(c, s, st, o);
@@ -1252,8 +1350,8 @@ extern "C" pty_status pty_lsqml_step(pty_ctx* c, void* stream, pty_state* st, co
   const pty_geometry& g = c->g;
   const int N = g.N, S = g.n_slices, M = g.n_modes;
   const size_t HW = (size_t)g.obj_h * g.obj_w;
-  { ProfScope p(P_PLAIN2D, s); launch_plain2d(N, s, c->tw, (const float2*)st->probe, c->phat, M, false, 1.f / N, false); }
   ReqDev r = base_req(c);
+  r.probe = (const float2*)st->probe;
   r.obj = (const float2*)st->object;
   r.positions = st->positions;
   r.batch_idx = batch_idx;
@@ -1266,17 +1364,17 @@ extern "C" pty_status pty_lsqml_step(pty_ctx* c, void* stream, pty_state* st, co
   r.wsum = c->lsq_w;
   LaunchCtx L = ctx_launch(c, s, r, B);
   L.resident = 0;
+  L.chain = 0;
   L.wsum = 1;
   L.wscr = L.cscr ? c->lsq_wscr : nullptr;   // the illumination sums follow the reduction mode
+  clear_grads(L, true);
   {
     ProfScope p(P_FILL, s);
-    launch_fill(s, (float*)c->gobj, (size_t)S * HW * 2, 0.f);
-    launch_fill(s, c->gpos, (size_t)g.n_positions * 2, 0.f);
     launch_fill(s, c->lsq_w, (size_t)S * HW, 0.f);
   }
   // the chain accumulates minus the summed directions: gobj = -D, gphat -> gprobe = -dP
   run_fused(c, L, 1.f);
-  { ProfScope p(P_PLAIN2D, s); launch_plain2d(N, s, c->tw, c->gphat, c->gprobe, M, true, 1.f / N, false); }
+  probe_from_spectrum(N, false, s, c->tw, c->gphat, c->gprobe, M, false);
   {
     ProfScope p(P_OPTIM, s);
     launch_lsq_transparency(s, c->items, B, (const float2*)st->object, S, g.obj_h, g.obj_w, N, c->lsq_tau,
@@ -1303,7 +1401,7 @@ Sizes group_sizes(int N, int max_items, int max_tiles, long long max_ck) {
   const int nblk = col_blocks(N);
   s.tiles = max_tiles;
   s.ck_tiles = max_ck;
-  size_t b = align256(N * sizeof(float2));
+  size_t b = align256(roots_len(N) * sizeof(float2));
   b += align256(((size_t)max_tiles + (size_t)max_ck) * N2 * sizeof(float2));
   b += align256((size_t)max_items * sizeof(Item));
   b += align256((size_t)max_items * 2 * N * sizeof(float2));
@@ -1342,7 +1440,7 @@ pty_status pty_group_create(int32_t N, int32_t max_items, int32_t max_tiles, int
   const int nblk = col_blocks(N);
   pty_status st;
   auto fail = [&](pty_status s) { pty_group_destroy(G); return s; };
-  if ((st = dmalloc(&G->tw, N, G->err)) || (st = dmalloc(&G->ws, (size_t)max_tiles * N2, G->err)) ||
+  if ((st = dmalloc(&G->tw, roots_len(N), G->err)) || (st = dmalloc(&G->ws, (size_t)max_tiles * N2, G->err)) ||
       (st = dmalloc(&G->ck, (size_t)max_ckpt_tiles * N2, G->err)) || (st = dmalloc(&G->items, (size_t)max_items, G->err)) ||
       (st = dmalloc(&G->ramps, (size_t)max_items * 2 * N, G->err)) ||
       (st = dmalloc(&G->loss_part, (size_t)max_items * nblk, G->err)) ||
@@ -1350,7 +1448,7 @@ pty_status pty_group_create(int32_t N, int32_t max_items, int32_t max_tiles, int
       (st = dmalloc(&G->cscr, (size_t)max_items * N2, G->err)))
     return fail(st);
   std::vector<float2> tw = roots(N);
-  if (hipMemcpy(G->tw, tw.data(), N * sizeof(float2), hipMemcpyHostToDevice) != hipSuccess) return fail(PTY_EHIP);
+  if (hipMemcpy(G->tw, tw.data(), tw.size() * sizeof(float2), hipMemcpyHostToDevice) != hipSuccess) return fail(PTY_EHIP);
   if (hipMemset(G->flags, 0, 4 * sizeof(int)) != hipSuccess) return fail(PTY_EHIP);
   *out = G;
   return PTY_OK;
@@ -1370,22 +1468,9 @@ pty_status pty_group_reconstruct_step(pty_group* G, void* stream, const pty_grou
   if (!items || n < 1 || n > kMaxReqs) { G->err = "1 to 16 items per grouped step"; return PTY_EINVAL; }
   hipStream_t s = (hipStream_t)stream;
   const int N = G->N;
-  LaunchCtx L{};
-  L.stream = s;
-  L.items = G->items;
-  L.ws = G->ws;
-  L.ck = G->ck;
-  L.ck_half = 0;
-  L.ck_spec = 1;   // every slice of every request stored in float
-  L.resident = use_resident(items[0].ctx ? items[0].ctx->strategy : PTY_STRATEGY_AUTO, N, 1) ? 1 : 0;
-  L.ramps = G->ramps;
-  L.tw = G->tw;
-  L.loss_part = G->loss_part;
-  L.pos_part = G->pos_part;
-  L.flags = G->flags;
-  int item0 = 0, tile0 = 0, S_max = 0, M_max = 0;
-  long long ck0 = 0;
-  std::vector<int> last_steps;
+  // validate everything before the first launch
+  int n_items = 0, n_tiles = 0;
+  long long n_ck = 0;
   for (int q = 0; q < n; ++q) {
     const pty_group_item& it = items[q];
     pty_ctx* c = it.ctx;
@@ -1394,71 +1479,97 @@ pty_status pty_group_reconstruct_step(pty_group* G, void* stream, const pty_grou
     if (st0 != PTY_OK) { G->err = c->err; return st0; }
     if (it.opt->kind == PTY_OPT_EPIE) { G->err = "grouped steps take SGD or Adam"; return PTY_EUNSUPPORTED; }
     if (!it.patterns || !it.batch_idx || it.batch < 1) { G->err = "item needs patterns and a batch"; return PTY_EINVAL; }
-    const int M = c->g.n_modes, S = c->g.n_slices;
-    ReqDev r = base_req(c);
-    r.obj = (const float2*)it.state->object;
-    r.positions = it.state->positions;
-    r.batch_idx = it.batch_idx;
-    r.patterns = it.patterns;
-    r.loss_out = it.loss;
-    r.gobj = c->gobj;
-    r.gpos_dense = c->gpos;
-    r.item0 = item0;
-    r.n_items = it.batch;
-    r.tile_base = tile0;
-    r.ck_base = ck0;
-    r.ck_every = 1;
-    r.n_ck = S;
-    L.reqs.r[q] = r;
-    item0 += it.batch;
-    tile0 += it.batch * M;
-    ck0 += (long long)it.batch * M * S;
-    S_max = std::max(S_max, S);
-    M_max = std::max(M_max, M);
-    last_steps.push_back(S - 1);
+    n_items += it.batch;
+    n_tiles += it.batch * c->g.n_modes;
+    n_ck += (long long)it.batch * c->g.n_modes * c->g.n_slices;
   }
-  if (item0 > G->max_items || tile0 > G->max_tiles || ck0 > G->max_ck) {
+  if (n_items > G->max_items || n_tiles > G->max_tiles || n_ck > G->max_ck) {
     G->err = "grouped step exceeds the group's workspace";
     return PTY_EINVAL;
   }
-  L.n_reqs = n;
-  L.n_items = item0;
-  L.max_modes = M_max;
   // the ordered object-gradient reduction when every request asks for it
   bool ordered = true;
   for (int q = 0; q < n; ++q) ordered &= items[q].ctx->reduce == PTY_REDUCE_ORDERED;
-  L.cscr = ordered ? G->cscr : nullptr;
-  if (ordered) L.resident = 0;
-  // a column block runs when any request has a live column in it
-  L.col_live_blocks = 0;
-  for (int q = 0; q < n; ++q) {
-    if (items[q].ctx->live_blocks == 0) { L.col_live_blocks = 0; break; }
-    L.col_live_blocks |= items[q].ctx->live_blocks;
-  }
-  for (int q = 0; q < n; ++q) {
-    pty_ctx* c = items[q].ctx;
-    launch_plain2d(N, s, G->tw, (const float2*)items[q].state->probe, c->phat, c->g.n_modes, false, 1.f / N, false);
-    launch_fill(s, (float*)c->gobj, (size_t)c->g.n_slices * c->g.obj_h * c->g.obj_w * 2, 0.f);
-    launch_fill(s, c->gpos, (size_t)c->g.n_positions * 2, 0.f);
-  }
-  std::sort(last_steps.begin(), last_steps.end());
-  last_steps.erase(std::unique(last_steps.begin(), last_steps.end()), last_steps.end());
-  // adjoint step t handles slice S_q - 1 - t of request q; slice 0 at t = S_q - 1
-  run_prepare(L, N);
-  set_chain_final(L, N, true);
-  run_forward_chunk(L, N, S_max, last_steps, true);
-  run_backward_chunk(L, N, S_max, last_steps, 1.f, 1, nullptr, nullptr);
-  run_finish_forward(L, N);
-  run_finish_backward(L, N, 1.f);
-  for (int q = 0; q < n; ++q) {
-    pty_ctx* c = items[q].ctx;
-    launch_plain2d(N, s, G->tw, c->gphat, c->gprobe, c->g.n_modes, true, 1.f / N, false);
-    if (apply_cost_regularizers(c, s, items[q].state, items[q].loss) != PTY_OK) {
-      G->err = c->err;
-      return PTY_EHIP;
+  const bool resident = !ordered && use_resident(items[0].ctx->strategy, N, 1);
+  // The requests whose contexts run the chain kernels share one set of
+  // launches, the others another, one after the other in the same workspace,
+  // so each request takes the path (and has the bits) of its steps alone.
+  for (int chain = 1; chain >= 0; --chain) {
+    LaunchCtx L{};
+    L.stream = s;
+    L.items = G->items;
+    L.ws = G->ws;
+    L.ck = G->ck;
+    L.ck_half = 0;
+    L.ck_spec = 1;   // every slice of every request stored in float
+    L.resident = resident ? 1 : 0;
+    L.chain = chain;
+    L.ramps = G->ramps;
+    L.tw = G->tw;
+    L.loss_part = G->loss_part;
+    L.pos_part = G->pos_part;
+    L.flags = G->flags;
+    L.cscr = ordered ? G->cscr : nullptr;
+    int item0 = 0, tile0 = 0, S_max = 0, M_max = 0, nq = 0;
+    long long ck0 = 0;
+    bool all_live = false;
+    std::vector<int> last_steps, mine;
+    for (int q = 0; q < n; ++q) {
+      const pty_group_item& it = items[q];
+      pty_ctx* c = it.ctx;
+      if ((use_chain(c) && !resident) != (chain == 1)) continue;
+      const int M = c->g.n_modes, S = c->g.n_slices;
+      ReqDev r = base_req(c);
+      r.probe = (const float2*)it.state->probe;
+      r.obj = (const float2*)it.state->object;
+      r.positions = it.state->positions;
+      r.batch_idx = it.batch_idx;
+      r.patterns = it.patterns;
+      r.loss_out = it.loss;
+      r.gobj = c->gobj;
+      r.gpos_dense = c->gpos;
+      r.item0 = item0;
+      r.n_items = it.batch;
+      r.tile_base = tile0;
+      r.ck_base = ck0;
+      r.ck_every = 1;
+      L.reqs.r[nq++] = r;
+      item0 += it.batch;
+      tile0 += it.batch * M;
+      ck0 += (long long)it.batch * M * S;
+      S_max = std::max(S_max, S);
+      M_max = std::max(M_max, M);
+      last_steps.push_back(S - 1);
+      mine.push_back(q);
+      // a column block runs when any request has a live column in it
+      all_live |= c->live_blocks == 0;
+      L.col_live_blocks |= c->live_blocks;
     }
-    apply_optimizer(c, s, items[q].state, items[q].opt);
-    apply_constraints(c, s, items[q].state);
+    if (nq == 0) continue;
+    if (all_live) L.col_live_blocks = 0;
+    L.n_reqs = nq;
+    L.n_items = item0;
+    L.max_modes = M_max;
+    clear_grads(L, true);
+    std::sort(last_steps.begin(), last_steps.end());
+    last_steps.erase(std::unique(last_steps.begin(), last_steps.end()), last_steps.end());
+    // adjoint step t handles slice S_q - 1 - t of request q; slice 0 at t = S_q - 1
+    run_prepare(L, N);
+    set_chain_final(L, N, true);
+    run_forward_chunk(L, N, S_max, last_steps, true);
+    run_backward_chunk(L, N, S_max, last_steps, 1.f, 1, nullptr, nullptr);
+    if (!L.chain) run_finish_forward(L, N);
+    run_finish_backward(L, N, S_max, 1, 1.f);
+    for (int q : mine) {
+      pty_ctx* c = items[q].ctx;
+      probe_from_spectrum(N, L.chain, s, G->tw, c->gphat, c->gprobe, c->g.n_modes, false);
+      if (apply_cost_regularizers(c, s, items[q].state, items[q].loss, L.chain != 0) != PTY_OK) {
+        G->err = c->err;
+        return PTY_EHIP;
+      }
+      apply_optimizer(c, s, items[q].state, items[q].opt);
+      apply_constraints(c, s, items[q].state);
+    }
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { G->err = hipGetErrorString(e); return PTY_EHIP; }

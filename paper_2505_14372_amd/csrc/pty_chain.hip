@@ -1,0 +1,760 @@
+// pty_chain.hip -- chain kernels: every slice of one (position, mode) tile in
+// one launch, the tile held in registers (pty_chain.hpp), for N = 64, 128.
+//
+// A slice step is F^-1 H F between two products with the object, all of it
+// local to a workgroup, so the tile itself never travels to memory between
+// slices: the forward chain writes the entry waves (checkpoints, real space,
+// row-major), the adjoint chain reads each one and leaves the mode's object-
+// gradient contribution conj(psi_i) g in its place, and one launch over all
+// slices sums the contributions tile by tile in batch order (no atomics).
+// Spectra between the launches (probe, far field, h_hat) are stored
+// transposed, [k_x][k_y], the order in which the lanes hold them.
+//
+// A step is: k_chain_begin (probe spectra, item descriptors, zeroed position
+// gradient), k_chain_fwd, k_chain_far (mode sum, noise model), k_chain_adj,
+// k_chain_finish (object gradient, probe-spectrum sum, loss, position
+// gradient: independent of each other, one launch) and k_chain_plain (probe
+// gradient), where the two-pass kernels take 4 S + 11.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "pty_chain.hpp"
+#include "pty_device.hpp"
+#include "pty_internal.h"
+
+namespace pty {
+
+namespace {
+
+// Constant tables read at wave-uniform addresses: loaded through the constant
+// address space, so that the values sit in scalar registers.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef const f32x2 __attribute__((address_space(4))) * ConstTab;
+__device__ __forceinline__ ConstTab const_tab(const float2* p) { return (ConstTab)(uintptr_t)p; }
+__device__ __forceinline__ float2 as_f2(f32x2 v) { return make_float2(v.x, v.y); }
+// The same table, for a use inside a loop: its loads stay where they are used
+// (hoisted out of the slice loop, the roots of both stages would fill the
+// scalar registers and spill).
+__device__ __forceinline__ ConstTab here(ConstTab p) {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
+enum Side { A1, B1, B2, C2 };
+template <int N, int SIDE>
+__device__ __forceinline__ constexpr int xoff(int e) {
+  return SIDE == A1 ? off_a1<N>(e) : SIDE == B1 ? off_b1<N>(e) : SIDE == B2 ? off_b2<N>(e) : off_c2<N>(e);
+}
+
+// Exchange: register e goes to wb + xoff<W>(e) and comes from rb + xoff<R>(e).
+// The first barrier waits for the readers of the exchange before.
+template <int N, int W, int R>
+__device__ __forceinline__ void exchange(float2 (&v)[Ch<N>::EL], typename Ch<N>::Elem* lds, int wb, int rb) {
+  constexpr int EL = Ch<N>::EL;
+  __syncthreads();
+  if constexpr (Ch<N>::SPLIT) {
+    float u[EL];
+#pragma unroll
+    for (int e = 0; e < EL; ++e) lds[wb + xoff<N, W>(e)] = v[e].x;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < EL; ++e) u[e] = lds[rb + xoff<N, R>(e)];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < EL; ++e) lds[wb + xoff<N, W>(e)] = v[e].y;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < EL; ++e) v[e] = make_float2(u[e], lds[rb + xoff<N, R>(e)]);
+  } else {
+#pragma unroll
+    for (int e = 0; e < EL; ++e) lds[wb + xoff<N, W>(e)] = v[e];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < EL; ++e) v[e] = lds[rb + xoff<N, R>(e)];
+  }
+}
+
+// The transform of one workgroup's tile.
+template <int N>
+struct Fft2 {
+  using Elem = typename Ch<N>::Elem;
+  const ChThread<N> th;
+  Elem* lds;
+  ConstTab ta, tc;
+  __device__ __forceinline__ Fft2(Elem* l, const float2* tab)
+      : th(threadIdx.x & 63, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)), lds(l),
+        ta(const_tab(tab) + th.yl * Ch<N>::EL), tc(const_tab(tab) + N + th.j1 * 16) {}
+
+  __device__ __forceinline__ void forward(float2 (&v)[Ch<N>::EL]) const {   // A -> C
+    constexpr int EL = Ch<N>::EL;
+    float2 w[EL > 16 ? EL : 16];
+    const ConstTab a = here(ta);
+#pragma unroll
+    for (int k = 1; k < EL; ++k) w[k] = as_f2(a[k]);
+    ch_stage_a<N, false>(v, w);
+    exchange<N, A1, B1>(v, lds, th.a1(), th.b1());
+    ch_stage_b<N, false>(v);
+    exchange<N, B2, C2>(v, lds, th.b2(), th.c2());
+    const ConstTab c = here(tc);
+#pragma unroll
+    for (int k = 1; k < 16; ++k) w[k] = as_f2(c[k]);
+    ch_stage_c<N, false>(v, w);
+  }
+  __device__ __forceinline__ void inverse(float2 (&v)[Ch<N>::EL]) const {   // C -> A
+    constexpr int EL = Ch<N>::EL;
+    float2 w[EL > 16 ? EL : 16];
+    const ConstTab c = here(tc);
+#pragma unroll
+    for (int k = 1; k < 16; ++k) w[k] = as_f2(c[k]);
+    ch_stage_c<N, true>(v, w);
+    exchange<N, C2, B2>(v, lds, th.c2(), th.b2());
+    ch_stage_b<N, true>(v);
+    exchange<N, B1, A1>(v, lds, th.b1(), th.a1());
+    const ConstTab a = here(ta);
+#pragma unroll
+    for (int k = 1; k < EL; ++k) w[k] = as_f2(a[k]);
+    ch_stage_a<N, true>(v, w);
+  }
+  __device__ __forceinline__ void load_spec(float2 (&v)[Ch<N>::EL], const float2* s) const {
+#pragma unroll
+    for (int e = 0; e < Ch<N>::EL; ++e) v[e] = s[th.kx(e & 15) * N + th.ky(e >> 4)];
+  }
+  __device__ __forceinline__ void store_spec(const float2 (&v)[Ch<N>::EL], float2* s, float scale) const {
+#pragma unroll
+    for (int e = 0; e < Ch<N>::EL; ++e) s[th.kx(e & 15) * N + th.ky(e >> 4)] = cscale(v[e], scale);
+  }
+  // Real-space rows through a raw buffer: one lane offset, and the row as a
+  // scalar offset (64-bit row addresses would take two scalar registers each
+  // and, kept across the slice loop, spill). W: row length in values.
+  struct Rows {
+    __amdgpu_buffer_rsrc_t r;
+    unsigned v;
+    int step;   // bytes from register to register (four rows)
+    __device__ __forceinline__ Rows(const float2* s, int W, const ChThread<N>& th)
+        : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<float2*>(s), (short)0, ((N - 1) * W + N) * 8, 0x00020000)),
+          v((unsigned)th.x * 8u + (unsigned)(th.yl * W) * 8u), step(32 * W) {}
+    __device__ __forceinline__ float2 ld(int k) const {
+      const u32x2 z = __builtin_amdgcn_raw_buffer_load_b64(r, v, k * step, 0);
+      return make_float2(__uint_as_float(z.x), __uint_as_float(z.y));
+    }
+    __device__ __forceinline__ void st(int k, float2 x) const {
+      const u32x2 z = {__float_as_uint(x.x), __float_as_uint(x.y)};
+      __builtin_amdgcn_raw_buffer_store_b64(z, r, v, k * step, 0);
+    }
+  };
+  __device__ __forceinline__ void load_real(float2 (&v)[Ch<N>::EL], const float2* s) const {
+    const Rows row(s, N, th);
+#pragma unroll
+    for (int r = 0; r < Ch<N>::EL; ++r) v[r] = row.ld(r);
+  }
+  __device__ __forceinline__ void store_real(const float2 (&v)[Ch<N>::EL], float2* s) const {
+    const Rows row(s, N, th);
+#pragma unroll
+    for (int r = 0; r < Ch<N>::EL; ++r) row.st(r, v[r]);
+  }
+  // v <- v s (or conj(s) v) with s in real space, 16 loads in flight at a time
+  template <bool CONJ>
+  __device__ __forceinline__ void times_real(float2 (&v)[Ch<N>::EL], const float2* s, int W) const {
+    asm volatile("" : "+s"(W));   // row offsets formed here, not kept across the slice loop
+    const Rows row(s, W, th);
+#pragma unroll
+    for (int r0 = 0; r0 < Ch<N>::EL; r0 += 16) {
+      float2 o[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[r] = row.ld(r0 + r);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) v[r0 + r] = CONJ ? cjmul(o[r], v[r0 + r]) : cmul(v[r0 + r], o[r]);
+      if (r0 + 16 < Ch<N>::EL) __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  // s <- conj(s) v
+  __device__ __forceinline__ void contribute(const float2 (&v)[Ch<N>::EL], float2* s) const {
+    const Rows row(s, N, th);
+#pragma unroll
+    for (int r0 = 0; r0 < Ch<N>::EL; r0 += 16) {
+      float2 o[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[r] = row.ld(r0 + r);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) row.st(r0 + r, cjmul(o[r], v[r0 + r]));
+      if (r0 + 16 < Ch<N>::EL) __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+};
+
+// times H (or conj H) of a gap, rebuilt from its separable factors:
+// H = [|k_x| <= K_y] Hy(k_y) Hx(k_x); Hx is wave-uniform
+template <int N, bool CONJ>
+__device__ __forceinline__ void propagate(float2 (&v)[Ch<N>::EL], const ReqDev& r, int gap, const ChThread<N>& th) {
+  const ConstTab px = const_tab(r.prop_x) + (size_t)gap * N;
+  const float4* py = r.prop_y + (size_t)gap * N;
+#pragma unroll
+  for (int kb = 0; kb < Ch<N>::KB; ++kb) {
+    const float4 q = py[th.ky(kb)];
+    const int K = __float_as_int(q.z);
+#pragma unroll
+    for (int j2 = 0; j2 < 16; ++j2) {
+      if (j2 % 4 == 0) sched_fence();   // (all 16 factors and row tests at once would spill)
+      const int ux = th.kx(j2);
+      const int akx = abs(ux < N / 2 ? ux : ux - N);
+      const float2 hx = as_f2(px[ux]), hy = make_float2(q.x, q.y), z = v[16 * kb + j2];
+      const float2 w = CONJ ? cjmul(hy, cjmul(hx, z)) : cmul(cmul(z, hx), hy);
+      v[16 * kb + j2] = akx > K ? make_float2(0.f, 0.f) : w;
+    }
+  }
+}
+
+// (item, mode) of a workgroup: consecutive workgroups go to the 8 XCDs in
+// turn, so the modes of one item, which read the same object patch, take every
+// eighth workgroup (one XCD's L2).
+__device__ __forceinline__ bool chain_tile(int n_items, int max_modes, bool reverse, int& b, int& m) {
+  const int g = blockIdx.x >> 3;
+  b = (blockIdx.x & 7) + 8 * (g / max_modes);
+  m = g % max_modes;
+  if (b >= n_items) return false;
+  if (reverse) b = n_items - 1 - b;
+  return true;
+}
+
+}  // namespace
+
+// ============================================================ kernels
+
+// First launch of a step, its work split over workgroup ranges: the spectra
+// of the probe modes (transposed), the item descriptors and ramps (one wave
+// per item), zeros for the dense position gradients.
+template <int N>
+__global__ __launch_bounds__(Ch<N>::T) void k_chain_begin(const ReqTable reqs, int n_reqs, int max_modes, int n_items,
+                                                          int item_blocks, int fill, Item* __restrict__ items,
+                                                          float2* __restrict__ ramps, const float2* __restrict__ tab,
+                                                          int* flags) {
+  __shared__ typename Ch<N>::Elem lds[Ch<N>::SIZE];
+  const int ffts = n_reqs * max_modes;
+  int blk = blockIdx.x;
+  if (blk < ffts) {
+    const ReqDev& r = reqs.r[blk / max_modes];
+    const int m = blk % max_modes;
+    if (m >= r.M) return;
+    const Fft2<N> fft(lds, tab);
+    float2 v[Ch<N>::EL];
+    fft.load_real(v, r.probe + (size_t)m * N * N);
+    fft.forward(v);
+    fft.store_spec(v, const_cast<float2*>(r.phat) + (size_t)m * N * N, 1.f / (float)N);
+    return;
+  }
+  blk -= ffts;
+  if (blk < item_blocks) {
+    const int b = blk * (Ch<N>::T / 64) + (threadIdx.x >> 6);
+    if (b < n_items) make_item(reqs, n_reqs, items, ramps, b, N, flags, threadIdx.x & 63, 64);
+    return;
+  }
+  blk -= item_blocks;
+  const ReqDev& r = reqs.r[blk / fill];
+  if (!r.gpos_dense || r.accumulate) return;
+  for (int e = (blk % fill) * Ch<N>::T + threadIdx.x; e < 2 * r.J; e += fill * Ch<N>::T) r.gpos_dense[e] = 0.f;
+}
+
+// Forward chain of one (item, mode) tile: shifted probe, every slice, far
+// field. Entry waves go to the checkpoint slots (p.store). With p.from >= 0 a
+// segment is recomputed instead: from the checkpoint of slice p.from, the entry
+// waves of slices p.from + 1 .. p.to go to the segment buffer.
+// Bound by vector arithmetic: at N = 128 a slice is about 100 operations per
+// value.
+template <int N>
+__global__ __launch_bounds__(Ch<N>::T, N == 192 ? 3 : 4) void k_chain_fwd(
+    const Item* __restrict__ items, const ReqTable reqs, float2* __restrict__ ws, float2* __restrict__ ck,
+    const float2* __restrict__ ramps, const float2* __restrict__ tab, int item_off, int n_items, int max_modes,
+    ChainFwd p) {
+  __shared__ typename Ch<N>::Elem lds[Ch<N>::SIZE];
+  int b, m;
+  if (!chain_tile(n_items, max_modes, false, b, m)) return;
+  b += item_off;
+  const Item it = items[b];
+  const ReqDev& r = reqs.r[it.req];
+  if (!it.valid || m >= r.M) return;
+  const Fft2<N> fft(lds, tab);
+  const ChThread<N>& th = fft.th;
+  const float inv = 1.f / (float)N;
+  float2 v[Ch<N>::EL];
+  int i = 0;
+  if (p.from < 0) {
+    const float2* ph = r.phat + (size_t)m * N * N;
+    const float2* ry = ramps + (size_t)b * 2 * N;
+    const ConstTab rx = const_tab(ry + N);
+#pragma unroll
+    for (int kb = 0; kb < Ch<N>::KB; ++kb) {
+      const float2 y = cscale(ry[th.ky(kb)], inv);
+#pragma unroll
+      for (int j2 = 0; j2 < 16; ++j2)
+        v[16 * kb + j2] = cmul(cmul(ph[th.kx(j2) * N + th.ky(kb)], y), as_f2(rx[th.kx(j2)]));
+    }
+    fft.inverse(v);
+  } else {
+    i = p.from;
+    fft.load_real(v, ck + ck_tile(it, r, m, i / r.ck_every) * N * N);
+  }
+  const int last = p.from < 0 ? r.S - 1 : p.to;
+  for (;; ++i) {
+    if (p.from >= 0) {
+      if (i > p.from) fft.store_real(v, p.seg + ((size_t)(it.tile0 + m) * p.seg_len + (i - p.from - 1)) * N * N);
+      if (i == last) return;
+    } else if (p.store && i % r.ck_every == 0) {
+      fft.store_real(v, ck + ck_tile(it, r, m, i / r.ck_every) * N * N);
+    }
+    const float2* o = r.obj + ((size_t)i * r.H + it.ny) * r.W + it.nx;
+    fft.template times_real<false>(v, o, r.W);
+    fft.forward(v);
+    if (i == r.S - 1) break;
+    propagate<N, false>(v, r, i, th);
+    fft.inverse(v);
+  }
+  fft.store_spec(v, ws + (size_t)(it.tile0 + m) * N * N, inv);
+}
+
+// Mode sum, noise model and detector gradient of the far fields Psi_m in the
+// work tiles: I = sum_m |Psi_m|^2, loss partials per 32 columns, intensities
+// if asked for and, with GRAD, tile_m = w Psi_m / N. Patterns and intensities
+// are row-major; the tiles are transposed, so both go through LDS.
+template <int N, bool GRAD>
+__global__ __launch_bounds__(256) void k_chain_far(const Item* __restrict__ items, const ReqTable reqs,
+                                                   float2* __restrict__ ws, float* __restrict__ loss_part, int* flags,
+                                                   int item_off) {
+  constexpr int PX = N * 32 / 256;
+  __shared__ float pat[N * 33];
+  __shared__ float red[4];
+  const int b = item_off + gridDim.y - 1 - blockIdx.y;
+  const Item it = items[b];
+  const ReqDev& r = reqs.r[it.req];
+  const int t = threadIdx.x, x0 = blockIdx.x * 32;
+  float* Io = r.I_out ? r.I_out + (size_t)(b - r.item0) * N * N : nullptr;
+  if (!it.valid) {
+    if (Io)
+      for (int q = 0; q < PX; ++q) { const int e = t + 256 * q; Io[(e >> 5) * N + x0 + (e & 31)] = 0.f; }
+    if (t == 0) loss_part[(size_t)b * (N / 32) + blockIdx.x] = 0.f;
+    return;
+  }
+  float2* tile = ws + (size_t)it.tile0 * N * N + (size_t)x0 * N;
+  const float* pt = r.patterns ? r.patterns + (size_t)it.j * N * N + x0 : nullptr;
+  if (pt) {
+#pragma unroll
+    for (int q = 0; q < PX; ++q) { const int e = t + 256 * q; pat[(e >> 5) * 33 + (e & 31)] = pt[(e >> 5) * N + (e & 31)]; }
+  }
+  float I[PX];
+#pragma unroll
+  for (int q = 0; q < PX; ++q) I[q] = 0.f;
+  for (int m = 0; m < r.M; ++m) {
+    const float2* s = tile + (size_t)m * N * N;
+#pragma unroll
+    for (int q = 0; q < PX; ++q) I[q] += cabs2(s[t + 256 * q]);
+  }
+  __syncthreads();
+  float w[PX];
+  float lsum = 0.f;
+  bool bad = false;
+#pragma unroll
+  for (int q = 0; q < PX; ++q) {
+    const int e = t + 256 * q;
+    float* c = pat + (e % N) * 33 + e / N;
+    float ell = 0.f, wt = 0.f;
+    if (pt) loss_weight(r.loss, I[q], *c, r.eps, r.inv_sigma2, ell, wt);
+    w[q] = wt;
+    lsum += ell;
+    bad |= !isfinite(ell) || !isfinite(wt);
+    if (Io) *c = I[q];
+  }
+  if (bad) raise_flag(flags, kFlagNonFinite);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
+  if ((t & 63) == 0) red[t >> 6] = lsum;
+  __syncthreads();
+  if (t == 0) loss_part[(size_t)b * (N / 32) + blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
+  if (Io) {
+#pragma unroll
+    for (int q = 0; q < PX; ++q) { const int e = t + 256 * q; Io[(e >> 5) * N + x0 + (e & 31)] = pat[(e >> 5) * 33 + (e & 31)]; }
+  }
+  if constexpr (GRAD) {
+    const float inv = 1.f / (float)N;
+    for (int m = 0; m < r.M; ++m) {
+      float2* s = tile + (size_t)m * N * N;
+#pragma unroll
+      for (int q = 0; q < PX; ++q) s[t + 256 * q] = cscale(s[t + 256 * q], w[q] * inv);
+    }
+  }
+}
+
+// Adjoint chain of one (item, mode) tile over slices p.hi .. p.lo (from the
+// last slice with p.first, down to 0 with p.last): g = gradient with respect
+// to the exit wave; the entry wave psi_i is read from its checkpoint (or
+// segment) slot and conj(psi_i) g, the mode's contribution to the object
+// gradient, is stored in its place; g <- F^-1 conj(H) F conj(O) g. Slice 0
+// ends with h_hat = F(conj(O) g) / N in the work tile and the sums of
+// Im(conj(h_hat) phat R) u for the position gradient. Between two segments g
+// waits in the work tile (real space).
+template <int N>
+__global__ __launch_bounds__(Ch<N>::T, N == 192 ? 3 : 4) void k_chain_adj(
+    const Item* __restrict__ items, const ReqTable reqs, float2* __restrict__ ws, float2* __restrict__ ck,
+    const float2* __restrict__ ramps, const float2* __restrict__ tab, float* __restrict__ pos_part, int item_off,
+    int n_items, int max_modes, ChainAdj p) {
+  __shared__ typename Ch<N>::Elem lds[Ch<N>::SIZE];
+  __shared__ double red[2][Ch<N>::WAVES];
+  int b, m;
+  if (!chain_tile(n_items, max_modes, true, b, m)) return;
+  b += item_off;
+  const Item it = items[b];
+  const ReqDev& r = reqs.r[it.req];
+  if (!it.valid || m >= r.M) return;
+  const Fft2<N> fft(lds, tab);
+  const ChThread<N>& th = fft.th;
+  float2* tile = ws + (size_t)(it.tile0 + m) * N * N;
+  float2 v[Ch<N>::EL];
+  if (p.first) {
+    fft.load_spec(v, tile);
+    fft.inverse(v);
+  } else {
+    fft.load_real(v, tile);
+  }
+  for (int i = p.first ? r.S - 1 : p.hi;; --i) {
+    float2* slot = p.seg && i % r.ck_every != 0
+                       ? p.seg + ((size_t)(it.tile0 + m) * p.seg_len + (i - p.seg_base)) * N * N
+                       : ck + ck_tile(it, r, m, i / r.ck_every) * N * N;
+    if (r.gobj) fft.contribute(v, slot);
+    const float2* o = r.obj + ((size_t)i * r.H + it.ny) * r.W + it.nx;
+    fft.template times_real<true>(v, o, r.W);
+    fft.forward(v);
+    if (i == 0) break;
+    propagate<N, true>(v, r, i - 1, th);
+    fft.inverse(v);
+    if (i == p.lo) {
+      fft.store_real(v, tile);
+      return;
+    }
+  }
+  const float inv = 1.f / (float)N;
+  const float2* ph = r.phat + (size_t)m * N * N;
+  const float2* ry = ramps + (size_t)b * 2 * N;
+  const ConstTab rx = const_tab(ry + N);
+  // the terms cancel to about a hundredth of their size: summed in double (in
+  // float the sum's rounding would be the largest error of the result)
+  double sy = 0.0, sx = 0.0;
+#pragma unroll
+  for (int kb = 0; kb < Ch<N>::KB; ++kb) {
+    const int uy = th.ky(kb);
+    const float2 ryk = ry[uy];
+    const double fy = (double)(uy < N / 2 ? uy : uy - N) / (double)N;
+#pragma unroll
+    for (int j2 = 0; j2 < 16; ++j2) {
+      const int ux = th.kx(j2);
+      const double fx = (double)(ux < N / 2 ? ux : ux - N) / (double)N;
+      float2& h = v[16 * kb + j2];
+      h = cscale(h, inv);
+      const float2 A = cmul(cmul(ph[ux * N + uy], ryk), as_f2(rx[ux]));
+      const double z = (double)cjmul(h, A).y;   // Im(conj(h_hat) A)
+      sy += fy * z;
+      sx += fx * z;
+    }
+  }
+  fft.store_spec(v, tile, 1.f);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    sy += __shfl_xor(sy, off);
+    sx += __shfl_xor(sx, off);
+  }
+  if (th.lane == 0) { red[0][th.wave] = sy; red[1][th.wave] = sx; }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < Ch<N>::WAVES; ++w) t += red[threadIdx.x][w];
+    pos_part[(size_t)(it.tile0 + m) * (N / 32) * 2 + threadIdx.x] = (float)t;
+  }
+}
+
+// Last launch of the adjoint: four independent sums, split over workgroup
+// ranges (all in a fixed order, so repeated calls give the same bits):
+//   - object gradient: one workgroup per 8 x 64 tile and slice lists the
+//     positions whose windows cover the tile in batch order, each of its 4
+//     waves sums a fixed quarter of the (position, mode) contributions, and
+//     the quarters are added in order;
+//   - probe-spectrum gradient: 16 pixels x 16 interleaved sums over the items;
+//   - loss; position gradients.
+// p.gather / p.rest select the parts (with recomputed segments the object
+// gradient is summed segment by segment).
+template <int N>
+__global__ __launch_bounds__(256) void k_chain_finish(const Item* __restrict__ items, const ReqTable reqs,
+                                                      const float2* __restrict__ ws, const float2* __restrict__ ck,
+                                                      const float2* __restrict__ ramps,
+                                                      const float* __restrict__ loss_part,
+                                                      const float* __restrict__ pos_part, int n_items, int max_modes,
+                                                      float scale, ChainFin p) {
+  constexpr int TY = 8;
+  __shared__ int list[256];
+  __shared__ int wcnt[4];
+  __shared__ float2 part[3 * TY * 64];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  int g = blockIdx.x;
+  const int n_gather = p.n_reqs * p.slices * p.ty * p.tx;
+  if (g < n_gather) {
+    const int tx = g % p.tx, ty = (g / p.tx) % p.ty, s = (g / (p.tx * p.ty)) % p.slices, q = g / (p.tx * p.ty * p.slices);
+    const ReqDev& r = reqs.r[q];
+    const int i = p.lo + s, x0 = tx * 64, y0 = ty * TY, x = x0 + lane;
+    if (i >= r.S || !r.gobj || x0 >= r.W || y0 >= r.H) return;
+    const float2* src = ck;
+    size_t tile_step = 1, mode_step = 1;
+    if (p.seg && i % r.ck_every != 0) {
+      src = p.seg + (size_t)(i - p.seg_base) * N * N;
+      tile_step = mode_step = (size_t)p.seg_len;
+    } else {
+      src = ck + (size_t)(i / r.ck_every) * r.n_items * r.M * N * N;
+    }
+    const bool in_seg = p.seg && i % r.ck_every != 0;
+    float2 acc[TY];
+#pragma unroll
+    for (int k = 0; k < TY; ++k) acc[k] = make_float2(0.f, 0.f);
+    int total = 0;
+    for (int b0 = r.item0; b0 < r.item0 + r.n_items; b0 += 256) {
+      const int b = b0 + t;
+      bool hit = false;
+      if (b < r.item0 + r.n_items) {
+        const Item it = items[b];
+        hit = it.valid && it.ny < y0 + TY && it.ny + N > y0 && it.nx < x0 + 64 && it.nx + N > x0;
+      }
+      const unsigned long long mk = __ballot(hit);
+      if (lane == 0) wcnt[w] = __popcll(mk);
+      __syncthreads();
+      int off = 0, cnt = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        off += k < w ? wcnt[k] : 0;
+        cnt += wcnt[k];
+      }
+      if (hit) list[off + __popcll(mk & ((1ull << lane) - 1ull))] = b;
+      __syncthreads();
+      total += cnt;
+      const int n = cnt * r.M, per = (n + 3) / 4;
+      const int beg = min(w * per, n), end = min(beg + per, n);
+      auto fetch = [&](int k, float2 (&z)[TY]) {
+        const int bi = __builtin_amdgcn_readfirstlane(list[k / r.M]), m = k % r.M;
+        const Item it = items[bi];
+        const size_t tile = in_seg ? (size_t)it.tile0 : (size_t)it.ck0;
+        const float2* c = src + (tile * tile_step + (size_t)m * mode_step) * N * N;
+        const int wx = x - it.nx, wy0 = y0 - it.ny;
+#pragma unroll
+        for (int k2 = 0; k2 < TY; ++k2) {
+          const int wy = wy0 + k2;
+          const bool in = wy >= 0 && wy < N && wx >= 0 && wx < N;
+          z[k2] = in ? c[wy * N + wx] : make_float2(0.f, 0.f);
+        }
+      };
+      int k = beg;
+      for (; k + 4 <= end; k += 4) {
+        float2 z0[TY], z1[TY], z2[TY], z3[TY];
+        fetch(k, z0);
+        fetch(k + 1, z1);
+        fetch(k + 2, z2);
+        fetch(k + 3, z3);
+#pragma unroll
+        for (int e = 0; e < TY; ++e) acc[e] = cadd(cadd(cadd(cadd(acc[e], z0[e]), z1[e]), z2[e]), z3[e]);
+      }
+      for (; k < end; ++k) {
+        float2 z0[TY];
+        fetch(k, z0);
+#pragma unroll
+        for (int e = 0; e < TY; ++e) acc[e] = cadd(acc[e], z0[e]);
+      }
+      __syncthreads();   // the list is rebuilt for the next items
+    }
+    if (total == 0 && r.accumulate) return;
+    if (w > 0) {
+#pragma unroll
+      for (int e = 0; e < TY; ++e) part[((w - 1) * TY + e) * 64 + lane] = acc[e];
+    }
+    __syncthreads();
+    if (w != 0 || x >= r.W) return;
+    const float sc = adj_scale(r, scale);
+    float2* go = r.gobj + (size_t)i * r.H * r.W;
+#pragma unroll
+    for (int e = 0; e < TY; ++e) {
+      const int y = y0 + e;
+      if (y >= r.H) continue;
+      float2 z = acc[e];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) z = cadd(z, part[(k * TY + e) * 64 + lane]);
+      z = cscale(z, sc);
+      go[(size_t)y * r.W + x] = r.accumulate ? cadd(go[(size_t)y * r.W + x], z) : z;
+    }
+    return;
+  }
+  g -= n_gather;
+  const int n_probe = p.n_reqs * max_modes * (N * N / 16);
+  if (g < n_probe) {
+    const ReqDev& r = reqs.r[g / (max_modes * (N * N / 16))];
+    const int m = (g / (N * N / 16)) % max_modes;
+    if (m >= r.M || !r.gphat) return;
+    const int px = (g % (N * N / 16)) * 16 + (t & 15), s = t >> 4;
+    const int ux = px / N, uy = px % N;
+    float2 acc = make_float2(0.f, 0.f);
+#pragma unroll 4
+    for (int b = r.item0 + s; b < r.item0 + r.n_items; b += 16) {
+      const Item it = items[b];
+      const float2 R = cmul(ramps[(size_t)b * 2 * N + uy], ramps[(size_t)b * 2 * N + N + ux]);
+      const float2 h = ws[(size_t)(it.tile0 + m) * N * N + px];
+      if (it.valid) acc = cadd(acc, cmul(h, cconj(R)));
+    }
+    part[t] = acc;
+    __syncthreads();
+    if (s == 0) {
+      float2 z = part[t];
+#pragma unroll
+      for (int k = 1; k < 16; ++k) z = cadd(z, part[16 * k + t]);
+      r.gphat[(size_t)m * N * N + px] = cscale(z, adj_scale(r, scale));
+    }
+    return;
+  }
+  g -= n_probe;
+  if (g < p.n_reqs) {
+    const ReqDev& r = reqs.r[g];
+    if (!r.loss_out) return;
+    double* red = reinterpret_cast<double*>(part);
+    double acc = 0.0;
+    const float* lp = loss_part + (size_t)r.item0 * (N / 32);
+    for (int e = t; e < r.n_items * (N / 32); e += 256) acc += (double)lp[e];
+    red[t] = acc;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+      if (t < s) red[t] += red[t + s];
+      __syncthreads();
+    }
+    if (t == 0) *r.loss_out = red[0];
+    return;
+  }
+  g -= p.n_reqs;
+  const int b = g * 256 + t;
+  if (b >= n_items) return;
+  const Item it = items[b];
+  const ReqDev& r = reqs.r[it.req];
+  float g0 = 0.f, g1 = 0.f;
+  if (it.valid)
+    for (int m = 0; m < r.M; ++m) {
+      const float* pp = pos_part + (size_t)(it.tile0 + m) * (N / 32) * 2;
+      g0 += pp[0];
+      g1 += pp[1];
+    }
+  const float f = 6.283185307179586f * adj_scale(r, scale);
+  g0 *= f;
+  g1 *= f;
+  const int local = b - r.item0;
+  if (r.gpos) {
+    if (r.accumulate) { r.gpos[2 * local] += g0; r.gpos[2 * local + 1] += g1; }
+    else { r.gpos[2 * local] = g0; r.gpos[2 * local + 1] = g1; }
+  }
+  if (r.gpos_dense && it.valid) {
+    atomicAdd(r.gpos_dense + 2 * it.j, g0);
+    atomicAdd(r.gpos_dense + 2 * it.j + 1, g1);
+  }
+}
+
+// dst = scale F^-1(src) of the probe-sized tiles (src transposed), added to dst if accumulate.
+template <int N>
+__global__ __launch_bounds__(Ch<N>::T) void k_chain_plain(const float2* __restrict__ src, float2* __restrict__ dst,
+                                                          const float2* __restrict__ tab, float scale, int accumulate) {
+  __shared__ typename Ch<N>::Elem lds[Ch<N>::SIZE];
+  const Fft2<N> fft(lds, tab);
+  float2 v[Ch<N>::EL];
+  fft.load_spec(v, src + (size_t)blockIdx.x * N * N);
+  fft.inverse(v);
+  float2* out = dst + (size_t)blockIdx.x * N * N;
+#pragma unroll
+  for (int e = 0; e < Ch<N>::EL; ++e) v[e] = cscale(v[e], scale);
+  if (accumulate) {
+    float2 u[Ch<N>::EL];
+    fft.load_real(u, out);
+#pragma unroll
+    for (int e = 0; e < Ch<N>::EL; ++e) v[e] = cadd(v[e], u[e]);
+  }
+  fft.store_real(v, out);
+}
+
+// ============================================================ launchers
+
+namespace {
+
+template <int N>
+struct Chain {
+  static const float2* tab(const LaunchCtx& L) { return L.tw + N; }
+  static dim3 tiles(const LaunchCtx& L) { return dim3(8 * ((L.n_items + 7) / 8) * L.max_modes); }
+
+  static void begin(const LaunchCtx& L) {
+    constexpr int W = Ch<N>::T / 64;
+    const int item_blocks = (L.n_items + W - 1) / W;
+    int J = 0;
+    for (int q = 0; q < L.n_reqs; ++q)
+      if (L.reqs.r[q].gpos_dense && !L.reqs.r[q].accumulate) J = std::max(J, L.reqs.r[q].J);
+    const int fill = J ? std::min(64, (2 * J + Ch<N>::T - 1) / Ch<N>::T) : 0;
+    hipLaunchKernelGGL((k_chain_begin<N>), dim3(L.n_reqs * L.max_modes + item_blocks + L.n_reqs * fill), dim3(Ch<N>::T),
+                       0, L.stream, L.reqs, L.n_reqs, L.max_modes, L.n_items, item_blocks, fill, L.items, L.ramps,
+                       tab(L), L.flags);
+  }
+  static void fwd(const LaunchCtx& L, const ChainFwd& p) {
+    hipLaunchKernelGGL((k_chain_fwd<N>), tiles(L), dim3(Ch<N>::T), 0, L.stream, L.items, L.reqs, L.ws,
+                       static_cast<float2*>(L.ck), L.ramps, tab(L), L.item_off, L.n_items, L.max_modes, p);
+  }
+  static void far(const LaunchCtx& L, bool grad) {
+    const dim3 g(N / 32, L.n_items);
+    if (grad)
+      hipLaunchKernelGGL((k_chain_far<N, true>), g, dim3(256), 0, L.stream, L.items, L.reqs, L.ws, L.loss_part, L.flags,
+                         L.item_off);
+    else
+      hipLaunchKernelGGL((k_chain_far<N, false>), g, dim3(256), 0, L.stream, L.items, L.reqs, L.ws, L.loss_part,
+                         L.flags, L.item_off);
+  }
+  static void adj(const LaunchCtx& L, const ChainAdj& p) {
+    hipLaunchKernelGGL((k_chain_adj<N>), tiles(L), dim3(Ch<N>::T), 0, L.stream, L.items, L.reqs, L.ws,
+                       static_cast<float2*>(L.ck), L.ramps, tab(L), L.pos_part, L.item_off, L.n_items, L.max_modes, p);
+  }
+  static void finish(const LaunchCtx& L, ChainFin p, bool gather, bool rest, float scale) {
+    p.n_reqs = L.n_reqs;
+    p.tx = p.ty = 0;
+    if (gather)
+      for (int q = 0; q < L.n_reqs; ++q) {
+        if (!L.reqs.r[q].gobj) continue;
+        p.tx = std::max(p.tx, (L.reqs.r[q].W + 63) / 64);
+        p.ty = std::max(p.ty, (L.reqs.r[q].H + 7) / 8);
+      }
+    size_t blocks = (size_t)p.n_reqs * p.slices * p.ty * p.tx;
+    if (rest) blocks += (size_t)p.n_reqs * L.max_modes * (N * N / 16) + p.n_reqs + (L.n_items + 255) / 256;
+    if (blocks == 0) return;
+    hipLaunchKernelGGL((k_chain_finish<N>), dim3((unsigned)blocks), dim3(256), 0, L.stream, L.items, L.reqs, L.ws,
+                       static_cast<const float2*>(L.ck), L.ramps, L.loss_part, L.pos_part, L.n_items, L.max_modes,
+                       scale, p);
+  }
+  static void plain_inv(hipStream_t s, const float2* tw, const float2* src, float2* dst, int n, float scale, bool acc) {
+    hipLaunchKernelGGL((k_chain_plain<N>), dim3(n), dim3(Ch<N>::T), 0, s, src, dst, tw + N, scale, acc ? 1 : 0);
+  }
+};
+
+}  // namespace
+
+bool chain_size(int N) { return N == 64 || N == 128; }
+
+#define CHAIN_DISPATCH(N, CALL)          \
+  switch (N) {                           \
+    case 64: Chain<64>::CALL; break;     \
+    default: Chain<128>::CALL; break;    \
+  }
+
+void launch_chain_begin(const LaunchCtx& L, int N) { CHAIN_DISPATCH(N, begin(L)); }
+void launch_chain_fwd(const LaunchCtx& L, int N, const ChainFwd& p) { CHAIN_DISPATCH(N, fwd(L, p)); }
+void launch_chain_far(const LaunchCtx& L, int N, bool grad) { CHAIN_DISPATCH(N, far(L, grad)); }
+void launch_chain_adj(const LaunchCtx& L, int N, const ChainAdj& p) { CHAIN_DISPATCH(N, adj(L, p)); }
+void launch_chain_finish(const LaunchCtx& L, int N, const ChainFin& p, bool gather, bool rest, float scale) {
+  CHAIN_DISPATCH(N, finish(L, p, gather, rest, scale));
+}
+void launch_chain_plain_inv(int N, hipStream_t s, const float2* tw, const float2* src, float2* dst, int n, float scale,
+                            bool acc) {
+  CHAIN_DISPATCH(N, plain_inv(s, tw, src, dst, n, scale, acc));
+}
+
+}  // namespace pty

@@ -79,7 +79,13 @@ __host__ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // x * w_n^k with w_n = exp(-2 pi i / n) (forward) or its conjugate (inverse).
-template <long k, long n, bool INV>
+// FINE adds the part of a component that its float misses where that is more
+// than 1.5e-8 (roots that are no eighth turns): the same roots meet the same
+// values slice after slice, so their rounding adds up coherently, where the
+// rounding of the products averages out. Left in, it is most of the error of a
+// position gradient taken through chained 16- and 32-point first stages
+// (128 x 128, 20 slices: 2.3e-5 without, 1.1e-5 with).
+template <long k, long n, bool INV, bool FINE = false>
 __host__ __device__ __forceinline__ float2 twiddle_const(float2 x) {
   constexpr long r = ((k % n) + n) % n;
   if constexpr (r == 0) {
@@ -94,6 +100,19 @@ __host__ __device__ __forceinline__ float2 twiddle_const(float2 x) {
     constexpr CosSin cs = unit_root(r, n);
     constexpr float c = (float)cs.c;
     constexpr float s = INV ? (float)cs.s : (float)(-cs.s);
+    if constexpr (FINE && (8 * r) % n != 0) {
+      // the small terms go into the accumulator before the large products (to
+      // a rounded sum they would be lost: they are below half a spacing of it)
+      constexpr double dc = cs.c - (double)c, ds = (INV ? cs.s : -cs.s) - (double)s;
+      constexpr bool use_c = dc > 1.5e-8 || dc < -1.5e-8, use_s = ds > 1.5e-8 || ds < -1.5e-8;
+      constexpr float fc = (float)dc, fs = (float)ds;
+      if constexpr (use_c || use_s) {
+        const float px = (use_c ? x.x * fc : 0.f) - (use_s ? x.y * fs : 0.f);
+        const float py = (use_s ? x.x * fs : 0.f) + (use_c ? x.y * fc : 0.f);
+        return make_float2(__builtin_fmaf(x.x, c, __builtin_fmaf(-x.y, s, px)),
+                           __builtin_fmaf(x.x, s, __builtin_fmaf(x.y, c, py)));
+      }
+    }
     return make_float2(x.x * c - x.y * s, x.x * s + x.y * c);
   }
 }
@@ -103,14 +122,14 @@ __host__ __device__ __forceinline__ float2 twiddle_const(float2 x) {
 template <int n>
 constexpr int first_radix() { return n % 4 == 0 ? 4 : (n % 2 == 0 ? 2 : (n % 3 == 0 ? 3 : n)); }
 
-template <int n, bool INV>
+template <int n, bool INV, bool FINE = false>
 struct Dft;
 
-template <bool INV>
-struct Dft<1, INV> { __host__ __device__ __forceinline__ static void run(float2*) {} };
+template <bool INV, bool FINE>
+struct Dft<1, INV, FINE> { __host__ __device__ __forceinline__ static void run(float2*) {} };
 
-template <bool INV>
-struct Dft<2, INV> {
+template <bool INV, bool FINE>
+struct Dft<2, INV, FINE> {
   __host__ __device__ __forceinline__ static void run(float2* x) {
     float2 a = x[0], b = x[1];
     x[0] = cadd(a, b);
@@ -118,8 +137,8 @@ struct Dft<2, INV> {
   }
 };
 
-template <bool INV>
-struct Dft<3, INV> {
+template <bool INV, bool FINE>
+struct Dft<3, INV, FINE> {
   __host__ __device__ __forceinline__ static void run(float2* x) {
     constexpr float h = (float)unit_root(1, 3).s;   // sin(2 pi / 3)
     float2 t1 = cadd(x[1], x[2]);
@@ -132,8 +151,8 @@ struct Dft<3, INV> {
   }
 };
 
-template <bool INV>
-struct Dft<4, INV> {
+template <bool INV, bool FINE>
+struct Dft<4, INV, FINE> {
   __host__ __device__ __forceinline__ static void run(float2* x) {
     float2 a0 = cadd(x[0], x[2]), a1 = csub(x[0], x[2]);
     float2 b0 = cadd(x[1], x[3]), b1 = csub(x[1], x[3]);
@@ -146,7 +165,7 @@ struct Dft<4, INV> {
 };
 
 // n = A * B:  X[k1 + A k2] = sum_b w_B^{b k2} w_n^{b k1} sum_a x[b + B a] w_A^{a k1}
-template <int n, bool INV>
+template <int n, bool INV, bool FINE>
 struct Dft {
   static constexpr int A = first_radix<n>();
   static constexpr int B = n / A;
@@ -157,17 +176,17 @@ struct Dft {
       constexpr int b = decltype(bI)::value;
       float2 t[A];
       static_for<0, A>([&](auto aI) { constexpr int a = decltype(aI)::value; t[a] = x[b + B * a]; });
-      Dft<A, INV>::run(t);
+      Dft<A, INV, FINE>::run(t);
       static_for<0, A>([&](auto kI) {
         constexpr int k1 = decltype(kI)::value;
-        y[b * A + k1] = twiddle_const<(long)b * k1, n, INV>(t[k1]);
+        y[b * A + k1] = twiddle_const<(long)b * k1, n, INV, FINE>(t[k1]);
       });
     });
     static_for<0, A>([&](auto kI) {
       constexpr int k1 = decltype(kI)::value;
       float2 t[B];
       static_for<0, B>([&](auto bI) { constexpr int b = decltype(bI)::value; t[b] = y[b * A + k1]; });
-      Dft<B, INV>::run(t);
+      Dft<B, INV, FINE>::run(t);
       static_for<0, B>([&](auto k2I) { constexpr int k2 = decltype(k2I)::value; x[k1 + A * k2] = t[k2]; });
     });
   }

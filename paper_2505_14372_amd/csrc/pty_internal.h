@@ -70,15 +70,15 @@ struct ReqDev {
   int item0, n_items;
   int tile_base;            // first workspace tile of this request
   long long ck_base;        // first checkpoint tile of this request
-  int ck_every, n_ck;       // checkpoint interval and stored slices per mode
-  int accumulate;           // add into gpos instead of overwriting
-  float* emax;              // [n_items][S][2] window maxima of sum_m |psi_i|^2 and |O_i|^2 (ePIE) or null
+  int ck_every;             // checkpoint interval
+  int accumulate;           // add into gpos (chain kernels: gobj too) instead of overwriting
+  int live_k;               // >= 0: the live columns are exactly |k_x| <= live_k (no table lookup)
   int modulus;              // far-field weight: 0 loss gradient, 1 modulus update (ePIE, LSQML)
+  float* emax;              // [n_items][S][2] window maxima of sum_m |psi_i|^2 and |O_i|^2 (ePIE) or null
   float* wsum;              // [S][H][W] scatter of sum_m |psi_i|^2 (LSQML) or null
   const uint8_t* live;      // [N] 1 where the propagators' column u_x has a nonzero value, or null
                             // (no band limit): a propagation column pass leaves the other
                             // columns of its output unwritten, and their consumers read zeros
-  int live_k;               // >= 0: the live columns are exactly |k_x| <= live_k (no table lookup)
   const float4* prop_y;     // [S-1][N] (Hy / N^2, K_y bits, 0): H = [|k_x| <= K_y] Hy Hx, or null
   const float2* prop_x;     // [S-1][N] Hx
   const double* scale_dev;  // device double multiplying the adjoint's outputs (gradient of the
@@ -87,6 +87,7 @@ struct ReqDev {
                             // chains and keeps the probe-gradient sums in registers
                             // (k_col_final_chain + k_probe_sum) instead of storing h_hat for
                             // k_probe_grad (set per launch by set_chain_final)
+  const float2* probe;      // [M][N][N] (chain kernels: transformed by their first launch)
 };
 
 // Scale of the adjoint outputs: the launch's host factor times the request's
@@ -142,6 +143,7 @@ struct LaunchCtx {
   int n_reqs, n_items, max_modes;
   int item_off;             // first item of this launch (chunked schedules)
   int resident;             // use the LDS-resident chain kernels
+  int chain;                // use the register-tile chain kernels (pty_chain.hip)
   Item* items;
   float2* ws;               // tile workspace
   void* ck;                 // checkpoint buffer (float2, or __half2 when ck_half)
@@ -239,6 +241,34 @@ void launch_lsq_object(hipStream_t s, float2* O, const float2* g, const float* w
 // transparency sum wp [N][N]; alpha: 2 doubles (step, max B).
 void launch_lsq_probe(hipStream_t s, float2* P, const float2* g, const float* wp, float* cur, const float* prev,
                       int M, int N2, float delta, double gamma, float beta, double* alpha);
+
+// Chain kernels (pty_chain.hip): every slice of a tile in one launch.
+struct ChainFwd {
+  int store;                // store the entry waves in the checkpoint slots
+  int from, to;             // from >= 0: recompute slices from + 1 .. to into seg instead
+  float2* seg;              // [tiles][seg_len][N][N]
+  int seg_len;
+};
+struct ChainAdj {
+  int first;                // start at every request's last slice, from the detector gradient
+  int hi, lo;               // slices hi .. lo (hi unused with first)
+  float2* seg;              // entry waves of slices that are no multiples of ck_every, or null
+  int seg_len, seg_base;
+};
+struct ChainFin {
+  int lo, slices;           // slices of the object-gradient sum
+  const float2* seg;        // as in ChainAdj
+  int seg_len, seg_base;
+  int n_reqs, tx, ty;       // (set by the launcher)
+};
+bool chain_size(int N);
+void launch_chain_begin(const LaunchCtx& L, int N);
+void launch_chain_fwd(const LaunchCtx& L, int N, const ChainFwd& p);
+void launch_chain_far(const LaunchCtx& L, int N, bool grad);
+void launch_chain_adj(const LaunchCtx& L, int N, const ChainAdj& p);
+void launch_chain_finish(const LaunchCtx& L, int N, const ChainFin& p, bool gather, bool rest, float scale);
+void launch_chain_plain_inv(int N, hipStream_t s, const float2* tw, const float2* src, float2* dst, int n, float scale,
+                            bool acc);
 
 // LDS-resident forward / adjoint chains (N = 64, 128; every slice checkpointed)
 bool resident_supported(int N);

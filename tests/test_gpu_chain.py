@@ -1,0 +1,130 @@
+"""The chain kernels (the default path at 64 x 64 and 128 x 128): loss and
+gradients against the FP64 oracle where their work splits unevenly (one
+position, a position count that is no multiple of 8, more than 256 positions for
+the object-gradient lists, several modes), recomputed segments, accumulation
+and skipped windows; and the same bits from every route to a result."""
+import numpy as np
+import pytest
+
+from paper_2505_14372_amd import synth
+
+from _cases import Case, max_rel, rel_l2
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+TOL_I, TOL_G = 1e-4, 1e-3   # the bounds of the other parity tests
+
+
+def _np(t):
+    return t.detach().cpu().numpy()
+
+
+def _case(N, M, S, B, seed=5, **kw):
+    scan = int(np.ceil(np.sqrt(B)))
+    wl = synth.make_small(N=N, M=M, S=S, scan=scan, step=3, seed=seed, loss="poisson", eps=0.8, amp_noise=0.2, **kw)
+    rng = np.random.default_rng(seed)
+    return Case(wl, batch=rng.permutation(scan * scan)[:B].astype(np.int32))
+
+
+def _grad(prob, d, **kw):
+    out = prob.loss_and_grad(d["probe"], d["obj"], d["pos"], d["pats"], d["batch"], **kw)
+    prob.check()
+    return out
+
+
+@pytest.mark.parametrize("N,M,S,B", [(64, 1, 1, 1), (64, 3, 2, 9), (64, 1, 5, 260), (128, 1, 2, 1), (128, 5, 3, 7),
+                                     (128, 2, 1, 17)])
+def test_chain_gradients_match_oracle(N, M, S, B):
+    c = _case(N, M, S, B)
+    ref = c.oracle_grad()
+    d = c.device()
+    prob = c.problem()
+    runs = [_grad(prob, d) for _ in range(2)]
+    loss, gO, gP, gX = runs[0]
+    I, _ = prob.forward(d["probe"], d["obj"], d["pos"], d["batch"])
+    assert rel_l2(_np(I), c.oracle_forward()) < TOL_I
+    assert abs(loss.item() - ref["loss"]) < TOL_I * abs(ref["loss"])
+    for got, key in ((gO, "g_object"), (gP, "g_probe"), (gX, "g_pos")):
+        assert rel_l2(_np(got), ref[key]) < TOL_G and max_rel(_np(got), ref[key]) < TOL_G, key
+    # no atomics: the default reduction repeats its bits
+    for a, b in zip(runs[0], runs[1]):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("N,k,chunk,streams", [(64, 2, 0, 1), (64, 3, 4, 1), (128, 5, 3, 1), (64, 1, 4, 3),
+                                               (128, 1, 2, 2)])
+def test_every_route_gives_the_same_bits(N, k, chunk, streams):
+    """Recomputed segments, chunks, concurrent streams, the split call and the
+    ordered reduction against the plain call."""
+    c = _case(N, 2, 7, 13)
+    d = c.device()
+    want = _grad(c.problem(), d)
+    prob = c.problem(checkpoint_every=k)
+    prob.set_chunk(chunk)
+    prob.set_streams(streams)
+    prob.set_reduction("ordered" if k > 1 else "atomic")
+    for a, b in zip(want, _grad(prob, d)):
+        assert torch.equal(a, b)
+    loss, _ = prob.forward_save(d["probe"], d["obj"], d["pos"], d["pats"], d["batch"])
+    split = [torch.empty_like(t) for t in want[1:]]
+    prob.backward(1.0, *split)
+    prob.check()
+    assert loss.item() == want[0].item()
+    for a, b in zip(want[1:], split):
+        assert torch.equal(a, b)
+
+
+def test_chain_accumulates_and_skips_windows_outside():
+    """accumulate adds to every gradient; a window outside the object
+    contributes nothing and the others are unchanged by it."""
+    from paper_2505_14372_amd._lib import PtyError
+    c = _case(64, 2, 3, 9)
+    d = c.device()
+    prob = c.problem()
+    _, gO, gP, gX = _grad(prob, d)
+    acc = [torch.ones_like(t) for t in (gO, gP, gX)]
+    _grad(prob, d, g_object=acc[0], g_probe=acc[1], g_pos=acc[2], accumulate=True)
+    for a, t in zip(acc, (gO, gP, gX)):
+        scale = t.abs().max().item()
+        # one rounding of 1 + t in float32
+        assert (a - (t + 1)).abs().max().item() <= 2.0 ** -23 * (1 + scale)
+    keep = d["batch"][1:].contiguous()
+    want = _grad(prob, dict(d, batch=keep))
+    pos = d["pos"].clone()
+    pos[int(d["batch"][0])] = -5.0
+    prob.loss_and_grad(d["probe"], d["obj"], pos, d["pats"], d["batch"])
+    with pytest.raises(PtyError):
+        prob.check()
+    dense = torch.empty((len(c.pos), 2), dtype=torch.float32, device="cuda")
+    loss, gO2, gP2, _ = prob.loss_and_grad(d["probe"], d["obj"], pos, d["pats"], d["batch"], g_pos=dense,
+                                           dense_pos=True)
+    # the sums are the same terms, split differently over the lanes
+    assert abs(loss.item() - want[0].item()) < 1e-9 * abs(want[0].item())
+    assert rel_l2(_np(gO2), _np(want[1])) < 1e-6 and rel_l2(_np(gP2), _np(want[2])) < 1e-6
+    assert torch.equal(dense[keep.long()], want[3])
+    assert dense[int(d["batch"][0])].abs().max().item() == 0.0
+
+
+def test_grouped_step_of_mixed_paths_gives_the_single_step_bits():
+    """A grouped step of requests on the chain kernels (several M, S) and one set
+    to the two-pass kernels: each has the bits of its step alone."""
+    from paper_2505_14372_amd import api
+    opt = api.Optimizer(kind="adam", lr_object=1e-2, lr_probe=1e-3, lr_pos=1e-2)
+    runs = []
+    for q, (M, S, B, strategy) in enumerate([(2, 3, 9, "auto"), (1, 5, 6, "two_pass"), (3, 1, 4, "auto")]):
+        c = _case(64, M, S, B, seed=30 + q)
+        d = c.device()
+        one, many = c.problem(), c.problem(max_batch=0)
+        for p in (one, many):
+            p.set_strategy(strategy)
+            p.set_reduction("ordered")
+        st = [api.ReconState(d["probe"].clone(), d["obj"].clone(), d["pos"].clone()) for _ in range(2)]
+        runs.append((one, many, d, st, torch.zeros(1, dtype=torch.float64, device="cuda")))
+    grp = api.Group(64, max_items=32, max_tiles=64, max_ckpt_tiles=256)
+    grp.step([(many, st[1], d["pats"], d["batch"], opt, loss) for _, many, d, st, loss in runs])
+    for one, _, d, st, loss in runs:
+        alone = one.reconstruct_step(st[0], d["pats"], d["batch"], opt)
+        assert alone.item() == loss.item()
+        for f in ("object", "probe", "positions"):
+            assert torch.equal(getattr(st[0], f), getattr(st[1], f)), f
