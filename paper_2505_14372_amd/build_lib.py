@@ -29,6 +29,10 @@ HIP_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
 
+# the register-tile kernels sit at the 128 registers of four waves per SIMD: with
+# the target's own pressure tracking the scheduler spills fewer of them
+SOURCE_FLAGS = {"pty_chain.hip": ["-mllvm", "-amdgpu-use-amdgpu-trackers=1"]}
+
 
 def hipcc():
     for cand in (os.environ.get("HIPCC"), shutil.which("hipcc"), "/opt/rocm/bin/hipcc"):
@@ -48,7 +52,7 @@ def build(verbose: bool = False, jobs: int = 3, defines=(), out: str = LIB) -> s
     os.makedirs(BUILD_DIR, exist_ok=True)
     for src in SOURCES:
         obj = os.path.join(BUILD_DIR, f"{src}.{tag}.o")
-        cmd = [cc, *HIP_FLAGS, *[f"-D{d}" for d in defines], "-I", INCLUDE, "-I", CSRC, "-c",
+        cmd = [cc, *HIP_FLAGS, *SOURCE_FLAGS.get(src, []), *[f"-D{d}" for d in defines], "-I", INCLUDE, "-I", CSRC, "-c",
                os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)

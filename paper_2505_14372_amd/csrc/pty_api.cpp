@@ -166,12 +166,12 @@ pty_status validate_geometry(const pty_geometry* g, std::string& err) {
 enum ProfClass {
   P_ITEMS, P_COL_SHIFT, P_ROW_FWD, P_COL_PROP, P_FAR_LOSS, P_LOSS_REDUCE, P_ROW_ADJ, P_COL_PROP_ADJ,
   P_COL_FINAL, P_PROBE_GRAD, P_POS_REDUCE, P_PLAIN2D, P_FILL, P_OPTIM, P_RECOMPUTE, P_REG, P_RES_FWD, P_RES_ADJ,
-  P_OBJ_GATHER, P_CHAIN_FWD, P_CHAIN_ADJ, P_NCLASS
+  P_OBJ_GATHER, P_CHAIN, P_NCLASS
 };
 const char* kProfNames[P_NCLASS] = {"items", "col_shift", "row_fwd", "col_prop", "far_loss", "loss_reduce",
                                     "row_adj", "col_prop_adj", "col_final", "probe_grad", "pos_reduce",
                                     "plain2d", "fill", "optimizer", "recompute", "regularizers", "res_fwd",
-                                    "res_adj", "obj_gather", "chain_fwd", "chain_adj"};
+                                    "res_adj", "obj_gather", "chain"};
 
 struct ProfRec { int cls; hipEvent_t a, b; };
 
@@ -309,8 +309,8 @@ bool use_resident(int strategy, int N, int ck_every) {
 // N x N table, which the chains' lane order would read one line per lane). A
 // window's rows are addressed with 32-bit offsets, hence the limit on obj_w.
 // Measured against two-pass (group step or gradients): 64 x 64, 2 modes, 8
-// slices, 225 positions 612 -> 231 us; 128 x 128, 2 modes, 5 slices, 77
-// positions 500 -> 332 us; 4 modes, 8 slices, 1024 positions 7.14 -> 6.13 ms.
+// slices, 225 positions 611 -> 218 us; 128 x 128, 2 modes, 5 slices, 77
+// positions 500 -> 327 us; 4 modes, 8 slices, 1024 positions 7.17 -> 6.05 ms.
 // The rule looks at the context alone, so a reconstruction takes the same
 // path, and has the same bits, alone and in a grouped step.
 bool use_chain(const pty_ctx* c) {
@@ -427,12 +427,11 @@ void probe_from_spectrum(int N, bool chain, hipStream_t s, const float2* tw, con
 // its inverse column DFT) in the workspace.
 void run_forward_chunk(const LaunchCtx& L, int N, int S_max, const std::vector<int>& far_steps, bool save) {
   if (L.chain) {
-    ChainFwd p{};
+    ChainRun p{};
+    p.what = kForward | kFar | (save ? kSeed : 0);
     p.store = save ? 1 : 0;
-    p.from = -1;
-    { ProfScope q(P_CHAIN_FWD, L.stream); launch_chain_fwd(L, N, p); }
-    ProfScope q(P_FAR_LOSS, L.stream);
-    launch_chain_far(L, N, save);
+    ProfScope q(P_CHAIN, L.stream);
+    launch_chain(L, N, p);
     return;
   }
   if (L.resident) {
@@ -470,11 +469,11 @@ void run_finish_forward(const LaunchCtx& L, int N) {
 void run_backward_chunk(const LaunchCtx& L, int N, int S_max, const std::vector<int>& final_steps, float scale,
                         int k, float2* ws2, void* seg) {
   if (L.chain && k == 1) {
-    ChainAdj p{};
-    p.first = 1;
+    ChainRun p{};
+    p.what = kAdjoint | kFirst;
     p.lo = -1;
-    ProfScope q(P_CHAIN_ADJ, L.stream);
-    launch_chain_adj(L, N, p);
+    ProfScope q(P_CHAIN, L.stream);
+    launch_chain(L, N, p);
     return;
   }
   if (L.chain) {
@@ -485,22 +484,23 @@ void run_backward_chunk(const LaunchCtx& L, int N, int S_max, const std::vector<
     for (int i1 = S_max - 1; i1 >= 0;) {
       const int i0 = (i1 / k) * k;
       if (i1 > i0) {
-        ChainFwd f{};
+        ChainRun f{};
+        f.what = kRecompute;
         f.from = i0;
         f.to = i1;
         f.seg = sg;
         f.seg_len = k - 1;
         ProfScope q(P_RECOMPUTE, L.stream);
-        launch_chain_fwd(L, N, f);
+        launch_chain(L, N, f);
       }
-      ChainAdj a{};
-      a.first = i1 == S_max - 1;
+      ChainRun a{};
+      a.what = kAdjoint | (i1 == S_max - 1 ? kFirst : 0);
       a.hi = i1;
       a.lo = i0 > 0 ? i0 : -1;
       a.seg = sg;
       a.seg_len = k - 1;
       a.seg_base = i0 + 1;
-      { ProfScope q(P_CHAIN_ADJ, L.stream); launch_chain_adj(L, N, a); }
+      { ProfScope q(P_CHAIN, L.stream); launch_chain(L, N, a); }
       ChainFin g{};
       g.lo = i0;
       g.slices = i1 - i0 + 1;
@@ -592,6 +592,22 @@ void run_backward_chunk(const LaunchCtx& L, int N, int S_max, const std::vector<
   }
 }
 
+// Forward and adjoint of the items of L, one launch where the chain kernels store every slice.
+void run_chunk(const LaunchCtx& L, int N, int S_max, const std::vector<int>& last, float scale, int k, float2* ws2,
+               void* seg) {
+  if (L.chain && k == 1) {
+    ChainRun p{};
+    p.what = kForward | kFar | kSeed | kAdjoint | kFirst;
+    p.store = 1;
+    p.lo = -1;
+    ProfScope q(P_CHAIN, L.stream);
+    launch_chain(L, N, p);
+    return;
+  }
+  run_forward_chunk(L, N, S_max, last, true);
+  run_backward_chunk(L, N, S_max, last, scale, k, ws2, seg);
+}
+
 void run_finish_backward(const LaunchCtx& L, int N, int S_max, int k, float scale) {
   if (L.chain) {
     ChainFin p{};
@@ -638,8 +654,7 @@ void run_fused(pty_ctx* c, const LaunchCtx& L0, float scale) {
   for (size_t q = 0; q < chunks.size(); ++q) {
     LaunchCtx C = sub(L, chunks[q].first, chunks[q].second);
     if (ns > 1) C.stream = c->streams[q % ns];
-    run_forward_chunk(C, N, S, {S - 1}, true);
-    run_backward_chunk(C, N, S, {S - 1}, scale, c->ck_every, c->ws2, c->seg);
+    run_chunk(C, N, S, {S - 1}, scale, c->ck_every, c->ws2, c->seg);
   }
   if (ns > 1) {
     for (int k = 0; k < ns; ++k) {
@@ -1556,8 +1571,7 @@ pty_status pty_group_reconstruct_step(pty_group* G, void* stream, const pty_grou
     // adjoint step t handles slice S_q - 1 - t of request q; slice 0 at t = S_q - 1
     run_prepare(L, N);
     set_chain_final(L, N, true);
-    run_forward_chunk(L, N, S_max, last_steps, true);
-    run_backward_chunk(L, N, S_max, last_steps, 1.f, 1, nullptr, nullptr);
+    run_chunk(L, N, S_max, last_steps, 1.f, 1, nullptr, nullptr);
     if (!L.chain) run_finish_forward(L, N);
     run_finish_backward(L, N, S_max, 1, 1.f);
     for (int q : mine) {

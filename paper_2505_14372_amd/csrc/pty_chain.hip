@@ -11,10 +11,11 @@
 // transposed, [k_x][k_y], the order in which the lanes hold them.
 //
 // A step is: k_chain_begin (probe spectra, item descriptors, zeroed position
-// gradient), k_chain_fwd, k_chain_far (mode sum, noise model), k_chain_adj,
-// k_chain_finish (object gradient, probe-spectrum sum, loss, position
-// gradient: independent of each other, one launch) and k_chain_plain (probe
-// gradient), where the two-pass kernels take 4 S + 11.
+// gradient), k_chain (forward and adjoint; with several modes a launch each and
+// k_chain_far, the noise model, between them), k_chain_finish (object gradient,
+// probe-spectrum sum, loss, position gradient: independent of each other, one
+// launch) and k_chain_plain (probe gradient), where the two-pass kernels take
+// 4 S + 11 launches.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -43,6 +44,8 @@ __device__ __forceinline__ ConstTab here(ConstTab p) {
   return p;
 }
 
+constexpr int kChainTY = 4;   // rows of an object-gradient tile
+
 enum Side { A1, B1, B2, C2 };
 template <int N, int SIDE>
 __device__ __forceinline__ constexpr int xoff(int e) {
@@ -56,18 +59,23 @@ __device__ __forceinline__ void exchange(float2 (&v)[Ch<N>::EL], typename Ch<N>:
   constexpr int EL = Ch<N>::EL;
   __syncthreads();
   if constexpr (Ch<N>::SPLIT) {
+    // (volatile: merged in pairs, the accesses would need a base register for
+    // each pair, more than there are)
+    typedef volatile float __attribute__((address_space(3))) Lds;
+    Lds* put = (Lds*)(lds + wb);
+    Lds* get = (Lds*)(lds + rb);
     float u[EL];
 #pragma unroll
-    for (int e = 0; e < EL; ++e) lds[wb + xoff<N, W>(e)] = v[e].x;
+    for (int e = 0; e < EL; ++e) put[xoff<N, W>(e)] = v[e].x;
     __syncthreads();
 #pragma unroll
-    for (int e = 0; e < EL; ++e) u[e] = lds[rb + xoff<N, R>(e)];
+    for (int e = 0; e < EL; ++e) u[e] = get[xoff<N, R>(e)];
     __syncthreads();
 #pragma unroll
-    for (int e = 0; e < EL; ++e) lds[wb + xoff<N, W>(e)] = v[e].y;
+    for (int e = 0; e < EL; ++e) put[xoff<N, W>(e)] = v[e].y;
     __syncthreads();
 #pragma unroll
-    for (int e = 0; e < EL; ++e) v[e] = make_float2(u[e], lds[rb + xoff<N, R>(e)]);
+    for (int e = 0; e < EL; ++e) v[e] = make_float2(u[e], get[xoff<N, R>(e)]);
   } else {
 #pragma unroll
     for (int e = 0; e < EL; ++e) lds[wb + xoff<N, W>(e)] = v[e];
@@ -166,7 +174,7 @@ struct Fft2 {
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[r] = row.ld(r0 + r);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) v[r0 + r] = CONJ ? cjmul(o[r], v[r0 + r]) : cmul(v[r0 + r], o[r]);
+      for (int r = 0; r < 16; ++r) v[r0 + r] = CONJ ? xjmul(o[r], v[r0 + r]) : xmul(v[r0 + r], o[r]);
       if (r0 + 16 < Ch<N>::EL) __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -179,8 +187,8 @@ struct Fft2 {
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[r] = row.ld(r0 + r);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) row.st(r0 + r, cjmul(o[r], v[r0 + r]));
-      if (r0 + 16 < Ch<N>::EL) __builtin_amdgcn_sched_barrier(0);
+      for (int r = 0; r < 16; ++r) row.st(r0 + r, xjmul(o[r], v[r0 + r]));
+      sched_fence();
     }
   }
 };
@@ -189,6 +197,7 @@ struct Fft2 {
 // H = [|k_x| <= K_y] Hy(k_y) Hx(k_x); Hx is wave-uniform
 template <int N, bool CONJ>
 __device__ __forceinline__ void propagate(float2 (&v)[Ch<N>::EL], const ReqDev& r, int gap, const ChThread<N>& th) {
+  asm volatile("" : "+s"(gap));   // table rows addressed here, not by pointers kept across the slice loop
   const ConstTab px = const_tab(r.prop_x) + (size_t)gap * N;
   const float4* py = r.prop_y + (size_t)gap * N;
 #pragma unroll
@@ -201,11 +210,21 @@ __device__ __forceinline__ void propagate(float2 (&v)[Ch<N>::EL], const ReqDev& 
       const int ux = th.kx(j2);
       const int akx = abs(ux < N / 2 ? ux : ux - N);
       const float2 hx = as_f2(px[ux]), hy = make_float2(q.x, q.y), z = v[16 * kb + j2];
-      const float2 w = CONJ ? cjmul(hy, cjmul(hx, z)) : cmul(cmul(z, hx), hy);
+      const float2 w = CONJ ? xjmul(hy, xjmul(hx, z)) : xmul(xmul(z, hx), hy);
       v[16 * kb + j2] = akx > K ? make_float2(0.f, 0.f) : w;
     }
   }
 }
+
+// Does the chain take the far field and the noise model too? With one mode
+// nothing has to be summed between workgroups (one launch instead of three:
+// 64 x 64, 1 slice, 256 positions, 49 -> 31 us). Several modes in one workgroup,
+// summing far fields and object-gradient contributions through LDS, measured
+// slower: the tiles then wait for each other at every barrier (64 x 64, 2 modes,
+// 8 slices: 155 -> 185 us; 128 x 128, 2 modes, 5 slices: 254 -> 439 us).
+constexpr bool far_in_chain_at(int N) { return N == 64; }
+template <int N>
+__host__ __device__ __forceinline__ bool far_in_chain(int M) { return far_in_chain_at(N) && M == 1; }
 
 // (item, mode) of a workgroup: consecutive workgroups go to the 8 XCDs in
 // turn, so the modes of one item, which read the same object patch, take every
@@ -257,65 +276,222 @@ __global__ __launch_bounds__(Ch<N>::T) void k_chain_begin(const ReqTable reqs, i
   for (int e = (blk % fill) * Ch<N>::T + threadIdx.x; e < 2 * r.J; e += fill * Ch<N>::T) r.gpos_dense[e] = 0.f;
 }
 
-// Forward chain of one (item, mode) tile: shifted probe, every slice, far
-// field. Entry waves go to the checkpoint slots (p.store). With p.from >= 0 a
-// segment is recomputed instead: from the checkpoint of slice p.from, the entry
-// waves of slices p.from + 1 .. p.to go to the segment buffer.
-// Bound by vector arithmetic: at N = 128 a slice is about 100 operations per
-// value.
-template <int N>
-__global__ __launch_bounds__(Ch<N>::T, N == 192 ? 3 : 4) void k_chain_fwd(
+// The chains: one workgroup per (item, mode) tile. p.what selects, in this order:
+//   kForward    shifted probe, every slice, far field; entry waves go to the
+//               checkpoint slots (p.store);
+//   kRecompute  instead: from the checkpoint of slice p.from, the entry waves
+//               of slices p.from + 1 .. p.to go to the segment buffer;
+//   kFar        (far_in_chain) noise model, intensities, and with kSeed the
+//               detector gradient w Psi / N;
+//   kAdjoint    g = gradient with respect to the exit wave, from slice p.hi (with
+//               kFirst the last one, from the detector gradient) down to p.lo
+//               (or 0): the entry wave psi_i is read from its checkpoint (or
+//               segment) slot, conj(psi_i) g, the mode's contribution to the
+//               object gradient, is stored in its place, and g <-
+//               F^-1 conj(H) F conj(O) g. Slice 0 ends with h_hat = F(conj(O) g) / N
+//               in the work tile and the sums of Im(conj(h_hat) phat R) u for the
+//               position gradient. Between two segments g waits in the work
+//               tile (real space).
+// A far field or detector gradient that the next launch takes over waits in
+// the work tile (transposed).
+// Bound by vector arithmetic where there are fewer tiles than the CUs hold
+// (about 100 operations per value and slice; 8 us a slice with two 64 x 64
+// tiles per CU), by the checkpoints' traffic beyond (128 x 128, 4 modes, 8 slices,
+// 1024 positions: forward 1.9, adjoint 2.7 ms; the two passes took 2.6 and 3.7).
+template <int N, int WHAT>
+__global__ __launch_bounds__(Ch<N>::T, 4) void k_chain(
     const Item* __restrict__ items, const ReqTable reqs, float2* __restrict__ ws, float2* __restrict__ ck,
-    const float2* __restrict__ ramps, const float2* __restrict__ tab, int item_off, int n_items, int max_modes,
-    ChainFwd p) {
-  __shared__ typename Ch<N>::Elem lds[Ch<N>::SIZE];
+    const float2* __restrict__ ramps, const float2* __restrict__ tab, float* __restrict__ loss_part,
+    float* __restrict__ pos_part, int* flags, int item_off, int n_items, int max_modes,
+    ChainRun p) {
+  using Elem = typename Ch<N>::Elem;
+  constexpr int EL = Ch<N>::EL, T = Ch<N>::T, NBLK = N / 32;
+  __shared__ Elem lds[Ch<N>::SIZE];
+  __shared__ double red[2][Ch<N>::WAVES];
   int b, m;
-  if (!chain_tile(n_items, max_modes, false, b, m)) return;
+  if (!chain_tile(n_items, max_modes, (WHAT & kAdjoint) != 0, b, m)) return;
   b += item_off;
   const Item it = items[b];
   const ReqDev& r = reqs.r[it.req];
-  if (!it.valid || m >= r.M) return;
+  if (m >= r.M) return;
+  const bool far = (WHAT & kFar) && far_in_chain<N>(r.M);
+  if (!it.valid) {
+    if (far) {
+      if (r.I_out)
+        for (int e = threadIdx.x; e < N * N; e += T) r.I_out[(size_t)(b - r.item0) * N * N + e] = 0.f;
+      if (threadIdx.x < NBLK) loss_part[(size_t)b * NBLK + threadIdx.x] = 0.f;
+    }
+    return;
+  }
   const Fft2<N> fft(lds, tab);
   const ChThread<N>& th = fft.th;
   const float inv = 1.f / (float)N;
-  float2 v[Ch<N>::EL];
-  int i = 0;
-  if (p.from < 0) {
-    const float2* ph = r.phat + (size_t)m * N * N;
-    const float2* ry = ramps + (size_t)b * 2 * N;
-    const ConstTab rx = const_tab(ry + N);
+  float2* tile = ws + (size_t)(it.tile0 + m) * N * N;
+  float2 v[EL];
+
+  if constexpr ((WHAT & (kForward | kRecompute)) != 0) {
+    constexpr bool rec = (WHAT & kRecompute) != 0;
+    int i = 0;
+    if constexpr (!rec) {
+      const float2* ph = r.phat + (size_t)m * N * N;
+      const float2* ry = ramps + (size_t)b * 2 * N;
+      const ConstTab rx = const_tab(ry + N);
 #pragma unroll
-    for (int kb = 0; kb < Ch<N>::KB; ++kb) {
-      const float2 y = cscale(ry[th.ky(kb)], inv);
+      for (int kb = 0; kb < Ch<N>::KB; ++kb) {
+        const float2 y = cscale(ry[th.ky(kb)], inv);
 #pragma unroll
-      for (int j2 = 0; j2 < 16; ++j2)
-        v[16 * kb + j2] = cmul(cmul(ph[th.kx(j2) * N + th.ky(kb)], y), as_f2(rx[th.kx(j2)]));
+        for (int j2 = 0; j2 < 16; ++j2)
+          v[16 * kb + j2] = xmul(xmul(ph[th.kx(j2) * N + th.ky(kb)], y), as_f2(rx[th.kx(j2)]));
+      }
+      fft.inverse(v);
+    } else {
+      i = p.from;
+      fft.load_real(v, ck + ck_tile(it, r, m, i / r.ck_every) * N * N);
     }
-    fft.inverse(v);
+    for (;; ++i) {
+      if constexpr (rec) {
+        if (i > p.from) fft.store_real(v, p.seg + ((size_t)(it.tile0 + m) * p.seg_len + (i - p.from - 1)) * N * N);
+        if (i == p.to) return;
+      } else if (p.store && i % r.ck_every == 0) {
+        fft.store_real(v, ck + ck_tile(it, r, m, i / r.ck_every) * N * N);
+      }
+      fft.template times_real<false>(v, r.obj + ((size_t)i * r.H + it.ny) * r.W + it.nx, r.W);
+      fft.forward(v);
+      if (i == r.S - 1) break;
+      propagate<N, false>(v, r, i, th);
+      fft.inverse(v);
+    }
+  }
+
+  if (far) {
+    // the lanes hold the spectrum transposed: patterns and intensities, which
+    // are row-major, go through LDS
+    float* sh = reinterpret_cast<float*>(lds);
+    static_assert(N * (N + 1) * 4 <= (int)sizeof(lds), "a pattern fits the space");
+    const int t = threadIdx.x;
+    auto at = [&](int e) { return th.ky(e >> 4) * (N + 1) + th.kx(e & 15); };
+    float w[EL];
+#pragma unroll
+    for (int e = 0; e < EL; ++e) {
+      v[e] = cscale(v[e], inv);
+      w[e] = xabs2(v[e]);
+    }
+    if (r.I_out) {
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < EL; ++e) sh[at(e)] = w[e];
+      __syncthreads();
+      float* out = r.I_out + (size_t)(b - r.item0) * N * N;
+#pragma unroll 4
+      for (int e = t; e < N * N; e += T) out[e] = sh[(e / N) * (N + 1) + e % N];
+    }
+    float l = 0.f;
+    if (r.patterns) {
+      const float* pt = r.patterns + (size_t)it.j * N * N;
+      __syncthreads();
+#pragma unroll 4
+      for (int e = t; e < N * N; e += T) sh[(e / N) * (N + 1) + e % N] = pt[e];
+      __syncthreads();
+      bool bad = false;
+#pragma unroll
+      for (int e = 0; e < EL; ++e) {
+        float ell = 0.f, wt = 0.f;
+        loss_weight(r.loss, w[e], sh[at(e)], r.eps, r.inv_sigma2, ell, wt);
+        w[e] = wt;
+        l += ell;
+        bad |= !isfinite(ell) || !isfinite(wt);
+      }
+      if (bad) raise_flag(flags, kFlagNonFinite);
+    }
+    double lsum = (double)l;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
+    if (th.lane == 0) red[0][th.wave] = lsum;
+    __syncthreads();
+    if (t < NBLK) {
+      double s = 0.0;
+      if (t == 0)
+        for (int q = 0; q < Ch<N>::WAVES; ++q) s += red[0][q];
+      loss_part[(size_t)b * NBLK + t] = (float)s;   // (one sum for the item)
+    }
+    if (!(p.what & kSeed)) return;
+#pragma unroll
+    for (int e = 0; e < EL; ++e) {
+      v[e] = cscale(v[e], w[e] * inv);
+      // rounded here, as where the value is stored for a later launch (the
+      // transform's first additions must not be fused with this product)
+      asm volatile("" : "+v"(v[e].x), "+v"(v[e].y));
+    }
+    if constexpr (!(WHAT & kAdjoint)) fft.store_spec(v, tile, 1.f);
+  } else if (WHAT & kForward) {
+    fft.store_spec(v, tile, inv);
+    return;
+  }
+  if constexpr (!(WHAT & kAdjoint)) return;
+
+  if (!(p.what & kFirst)) {
+    fft.load_real(v, tile);
   } else {
-    i = p.from;
-    fft.load_real(v, ck + ck_tile(it, r, m, i / r.ck_every) * N * N);
-  }
-  const int last = p.from < 0 ? r.S - 1 : p.to;
-  for (;; ++i) {
-    if (p.from >= 0) {
-      if (i > p.from) fft.store_real(v, p.seg + ((size_t)(it.tile0 + m) * p.seg_len + (i - p.from - 1)) * N * N);
-      if (i == last) return;
-    } else if (p.store && i % r.ck_every == 0) {
-      fft.store_real(v, ck + ck_tile(it, r, m, i / r.ck_every) * N * N);
-    }
-    const float2* o = r.obj + ((size_t)i * r.H + it.ny) * r.W + it.nx;
-    fft.template times_real<false>(v, o, r.W);
-    fft.forward(v);
-    if (i == r.S - 1) break;
-    propagate<N, false>(v, r, i, th);
+    if (!far) fft.load_spec(v, tile);
     fft.inverse(v);
   }
-  fft.store_spec(v, ws + (size_t)(it.tile0 + m) * N * N, inv);
+  for (int i = (p.what & kFirst) ? r.S - 1 : p.hi;; --i) {
+    if (r.gobj)
+      fft.contribute(v, p.seg && i % r.ck_every != 0
+                            ? p.seg + ((size_t)(it.tile0 + m) * p.seg_len + (i - p.seg_base)) * N * N
+                            : ck + ck_tile(it, r, m, i / r.ck_every) * N * N);
+    fft.template times_real<true>(v, r.obj + ((size_t)i * r.H + it.ny) * r.W + it.nx, r.W);
+    fft.forward(v);
+    if (i == 0) break;
+    propagate<N, true>(v, r, i - 1, th);
+    fft.inverse(v);
+    if (i == p.lo) {
+      fft.store_real(v, tile);
+      return;
+    }
+  }
+  const float2* ph = r.phat + (size_t)m * N * N;
+  const float2* ry = ramps + (size_t)b * 2 * N;
+  const ConstTab rx = const_tab(ry + N);
+  // the terms cancel to about a hundredth of their size: summed in double (in
+  // float the sum's rounding would be the largest error of the result)
+  double sy = 0.0, sx = 0.0;
+#pragma unroll
+  for (int kb = 0; kb < Ch<N>::KB; ++kb) {
+    const int uy = th.ky(kb);
+    const float2 ryk = ry[uy];
+    const double fy = (double)(uy < N / 2 ? uy : uy - N) / (double)N;
+#pragma unroll
+    for (int j2 = 0; j2 < 16; ++j2) {
+      const int ux = th.kx(j2);
+      const double fx = (double)(ux < N / 2 ? ux : ux - N) / (double)N;
+      float2& h = v[16 * kb + j2];
+      h = cscale(h, inv);
+      const float2 A = xmul(xmul(ph[ux * N + uy], ryk), as_f2(rx[ux]));
+      const double z = (double)xjmul(h, A).y;   // Im(conj(h_hat) A)
+      sy += fy * z;
+      sx += fx * z;
+    }
+  }
+  fft.store_spec(v, tile, 1.f);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    sy += __shfl_xor(sy, off);
+    sx += __shfl_xor(sx, off);
+  }
+  __syncthreads();
+  if (th.lane == 0) { red[0][th.wave] = sy; red[1][th.wave] = sx; }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    double s = 0.0;
+#pragma unroll
+    for (int q = 0; q < Ch<N>::WAVES; ++q) s += red[threadIdx.x][q];
+    pos_part[(size_t)(it.tile0 + m) * NBLK * 2 + threadIdx.x] = (float)s;
+  }
 }
 
-// Mode sum, noise model and detector gradient of the far fields Psi_m in the
-// work tiles: I = sum_m |Psi_m|^2, loss partials per 32 columns, intensities
+// Far field of the requests whose chains do not take it: mode sum, noise
+// model and detector gradient of the Psi_m in the work tiles: I = sum_m |Psi_m|^2, loss partials per 32 columns, intensities
 // if asked for and, with GRAD, tile_m = w Psi_m / N. Patterns and intensities
 // are row-major; the tiles are transposed, so both go through LDS.
 template <int N, bool GRAD>
@@ -328,6 +504,7 @@ __global__ __launch_bounds__(256) void k_chain_far(const Item* __restrict__ item
   const int b = item_off + gridDim.y - 1 - blockIdx.y;
   const Item it = items[b];
   const ReqDev& r = reqs.r[it.req];
+  if (far_in_chain<N>(r.M)) return;
   const int t = threadIdx.x, x0 = blockIdx.x * 32;
   float* Io = r.I_out ? r.I_out + (size_t)(b - r.item0) * N * N : nullptr;
   if (!it.valid) {
@@ -348,7 +525,7 @@ __global__ __launch_bounds__(256) void k_chain_far(const Item* __restrict__ item
   for (int m = 0; m < r.M; ++m) {
     const float2* s = tile + (size_t)m * N * N;
 #pragma unroll
-    for (int q = 0; q < PX; ++q) I[q] += cabs2(s[t + 256 * q]);
+    for (int q = 0; q < PX; ++q) I[q] += xabs2(s[t + 256 * q]);
   }
   __syncthreads();
   float w[PX];
@@ -385,115 +562,31 @@ __global__ __launch_bounds__(256) void k_chain_far(const Item* __restrict__ item
   }
 }
 
-// Adjoint chain of one (item, mode) tile over slices p.hi .. p.lo (from the
-// last slice with p.first, down to 0 with p.last): g = gradient with respect
-// to the exit wave; the entry wave psi_i is read from its checkpoint (or
-// segment) slot and conj(psi_i) g, the mode's contribution to the object
-// gradient, is stored in its place; g <- F^-1 conj(H) F conj(O) g. Slice 0
-// ends with h_hat = F(conj(O) g) / N in the work tile and the sums of
-// Im(conj(h_hat) phat R) u for the position gradient. Between two segments g
-// waits in the work tile (real space).
-template <int N>
-__global__ __launch_bounds__(Ch<N>::T, N == 192 ? 3 : 4) void k_chain_adj(
-    const Item* __restrict__ items, const ReqTable reqs, float2* __restrict__ ws, float2* __restrict__ ck,
-    const float2* __restrict__ ramps, const float2* __restrict__ tab, float* __restrict__ pos_part, int item_off,
-    int n_items, int max_modes, ChainAdj p) {
-  __shared__ typename Ch<N>::Elem lds[Ch<N>::SIZE];
-  __shared__ double red[2][Ch<N>::WAVES];
-  int b, m;
-  if (!chain_tile(n_items, max_modes, true, b, m)) return;
-  b += item_off;
-  const Item it = items[b];
-  const ReqDev& r = reqs.r[it.req];
-  if (!it.valid || m >= r.M) return;
-  const Fft2<N> fft(lds, tab);
-  const ChThread<N>& th = fft.th;
-  float2* tile = ws + (size_t)(it.tile0 + m) * N * N;
-  float2 v[Ch<N>::EL];
-  if (p.first) {
-    fft.load_spec(v, tile);
-    fft.inverse(v);
-  } else {
-    fft.load_real(v, tile);
-  }
-  for (int i = p.first ? r.S - 1 : p.hi;; --i) {
-    float2* slot = p.seg && i % r.ck_every != 0
-                       ? p.seg + ((size_t)(it.tile0 + m) * p.seg_len + (i - p.seg_base)) * N * N
-                       : ck + ck_tile(it, r, m, i / r.ck_every) * N * N;
-    if (r.gobj) fft.contribute(v, slot);
-    const float2* o = r.obj + ((size_t)i * r.H + it.ny) * r.W + it.nx;
-    fft.template times_real<true>(v, o, r.W);
-    fft.forward(v);
-    if (i == 0) break;
-    propagate<N, true>(v, r, i - 1, th);
-    fft.inverse(v);
-    if (i == p.lo) {
-      fft.store_real(v, tile);
-      return;
-    }
-  }
-  const float inv = 1.f / (float)N;
-  const float2* ph = r.phat + (size_t)m * N * N;
-  const float2* ry = ramps + (size_t)b * 2 * N;
-  const ConstTab rx = const_tab(ry + N);
-  // the terms cancel to about a hundredth of their size: summed in double (in
-  // float the sum's rounding would be the largest error of the result)
-  double sy = 0.0, sx = 0.0;
-#pragma unroll
-  for (int kb = 0; kb < Ch<N>::KB; ++kb) {
-    const int uy = th.ky(kb);
-    const float2 ryk = ry[uy];
-    const double fy = (double)(uy < N / 2 ? uy : uy - N) / (double)N;
-#pragma unroll
-    for (int j2 = 0; j2 < 16; ++j2) {
-      const int ux = th.kx(j2);
-      const double fx = (double)(ux < N / 2 ? ux : ux - N) / (double)N;
-      float2& h = v[16 * kb + j2];
-      h = cscale(h, inv);
-      const float2 A = cmul(cmul(ph[ux * N + uy], ryk), as_f2(rx[ux]));
-      const double z = (double)cjmul(h, A).y;   // Im(conj(h_hat) A)
-      sy += fy * z;
-      sx += fx * z;
-    }
-  }
-  fft.store_spec(v, tile, 1.f);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    sy += __shfl_xor(sy, off);
-    sx += __shfl_xor(sx, off);
-  }
-  if (th.lane == 0) { red[0][th.wave] = sy; red[1][th.wave] = sx; }
-  __syncthreads();
-  if (threadIdx.x < 2) {
-    double t = 0.0;
-#pragma unroll
-    for (int w = 0; w < Ch<N>::WAVES; ++w) t += red[threadIdx.x][w];
-    pos_part[(size_t)(it.tile0 + m) * (N / 32) * 2 + threadIdx.x] = (float)t;
-  }
-}
-
 // Last launch of the adjoint: four independent sums, split over workgroup
 // ranges (all in a fixed order, so repeated calls give the same bits):
-//   - object gradient: one workgroup per 8 x 64 tile and slice lists the
-//     positions whose windows cover the tile in batch order, each of its 4
-//     waves sums a fixed quarter of the (position, mode) contributions, and
-//     the quarters are added in order;
-//   - probe-spectrum gradient: 16 pixels x 16 interleaved sums over the items;
+//   - object gradient: one workgroup per 4 x 64 tile and slice; wave w adds,
+//     in batch order, the contributions of the positions b = w mod 8 whose
+//     windows cover the tile (a position that does not cover a pixel adds
+//     nothing to it, so a pixel's sum does not depend on the tile's shape), and
+//     the eight sums are added in wave order. No list and no barrier before the
+//     end: with one list per workgroup, 8 x 64 tiles and 4 waves this launch took
+//     36 us at 64 x 64, 1 slice, 256 positions (now 15), 53 us at 2 modes, 8 slices
+//     (35; 118 MB of contributions) and 1.15 ms at 128 x 128, 4 modes, 8 slices,
+//     1024 positions (1.07; 4.3 GB, read at 4.0 TB/s);
+//   - probe-spectrum gradient: 32 pixels x 16 interleaved sums over the items;
 //   - loss; position gradients.
 // p.gather / p.rest select the parts (with recomputed segments the object
 // gradient is summed segment by segment).
 template <int N>
-__global__ __launch_bounds__(256) void k_chain_finish(const Item* __restrict__ items, const ReqTable reqs,
+__global__ __launch_bounds__(512) void k_chain_finish(const Item* __restrict__ items, const ReqTable reqs,
                                                       const float2* __restrict__ ws, const float2* __restrict__ ck,
                                                       const float2* __restrict__ ramps,
                                                       const float* __restrict__ loss_part,
                                                       const float* __restrict__ pos_part, int n_items, int max_modes,
                                                       float scale, ChainFin p) {
-  constexpr int TY = 8;
-  __shared__ int list[256];
-  __shared__ int wcnt[4];
-  __shared__ float2 part[3 * TY * 64];
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  constexpr int TY = kChainTY, W = 8;
+  __shared__ float2 part[(W - 1) * TY * 64 > 512 ? (W - 1) * TY * 64 : 512];
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
   int g = blockIdx.x;
   const int n_gather = p.n_reqs * p.slices * p.ty * p.tx;
   if (g < n_gather) {
@@ -501,72 +594,58 @@ __global__ __launch_bounds__(256) void k_chain_finish(const Item* __restrict__ i
     const ReqDev& r = reqs.r[q];
     const int i = p.lo + s, x0 = tx * 64, y0 = ty * TY, x = x0 + lane;
     if (i >= r.S || !r.gobj || x0 >= r.W || y0 >= r.H) return;
-    const float2* src = ck;
-    size_t tile_step = 1, mode_step = 1;
-    if (p.seg && i % r.ck_every != 0) {
-      src = p.seg + (size_t)(i - p.seg_base) * N * N;
-      tile_step = mode_step = (size_t)p.seg_len;
-    } else {
-      src = ck + (size_t)(i / r.ck_every) * r.n_items * r.M * N * N;
-    }
-    const bool in_seg = p.seg && i % r.ck_every != 0;
+    const bool sg = p.seg && i % r.ck_every != 0;
+    // contribution tile of (item, mode): base + (first tile of the item + mode) * step
+    const float2* base = sg ? p.seg + (size_t)(i - p.seg_base) * N * N
+                            : ck + (size_t)(i / r.ck_every) * r.n_items * r.M * N * N;
+    const size_t step = (size_t)(sg ? p.seg_len : 1) * N * N;
     float2 acc[TY];
 #pragma unroll
     for (int k = 0; k < TY; ++k) acc[k] = make_float2(0.f, 0.f);
-    int total = 0;
-    for (int b0 = r.item0; b0 < r.item0 + r.n_items; b0 += 256) {
-      const int b = b0 + t;
+    for (int b0 = r.item0; b0 < r.item0 + r.n_items; b0 += 64 * W) {
+      const int b = b0 + lane * W + w;
+      int ny = 0, nx = 0, t0 = 0;
       bool hit = false;
       if (b < r.item0 + r.n_items) {
         const Item it = items[b];
-        hit = it.valid && it.ny < y0 + TY && it.ny + N > y0 && it.nx < x0 + 64 && it.nx + N > x0;
+        ny = it.ny;
+        nx = it.nx;
+        t0 = sg ? it.tile0 : (int)it.ck0;
+        hit = it.valid && ny < y0 + TY && ny + N > y0 && nx < x0 + 64 && nx + N > x0;
       }
-      const unsigned long long mk = __ballot(hit);
-      if (lane == 0) wcnt[w] = __popcll(mk);
-      __syncthreads();
-      int off = 0, cnt = 0;
+      unsigned long long todo = __ballot(hit);
+      // up to four contributions at a time, the loads of all issued before the additions
+      int l = -1, m = r.M;
+      while (todo || m < r.M) {
+        float2 z[4][TY];
+        int got = 0;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        off += k < w ? wcnt[k] : 0;
-        cnt += wcnt[k];
-      }
-      if (hit) list[off + __popcll(mk & ((1ull << lane) - 1ull))] = b;
-      __syncthreads();
-      total += cnt;
-      const int n = cnt * r.M, per = (n + 3) / 4;
-      const int beg = min(w * per, n), end = min(beg + per, n);
-      auto fetch = [&](int k, float2 (&z)[TY]) {
-        const int bi = __builtin_amdgcn_readfirstlane(list[k / r.M]), m = k % r.M;
-        const Item it = items[bi];
-        const size_t tile = in_seg ? (size_t)it.tile0 : (size_t)it.ck0;
-        const float2* c = src + (tile * tile_step + (size_t)m * mode_step) * N * N;
-        const int wx = x - it.nx, wy0 = y0 - it.ny;
+        for (int k = 0; k < 4; ++k) {
+          if (m >= r.M) {
+            if (!todo) break;
+            l = __builtin_ctzll(todo);
+            todo &= todo - 1;
+            m = 0;
+          }
+          const int wx = x - __builtin_amdgcn_readlane(nx, l), wy0 = y0 - __builtin_amdgcn_readlane(ny, l);
+          const float2* c = base + ((size_t)__builtin_amdgcn_readlane(t0, l) + (size_t)m) * step;
 #pragma unroll
-        for (int k2 = 0; k2 < TY; ++k2) {
-          const int wy = wy0 + k2;
-          const bool in = wy >= 0 && wy < N && wx >= 0 && wx < N;
-          z[k2] = in ? c[wy * N + wx] : make_float2(0.f, 0.f);
+          for (int e = 0; e < TY; ++e) {
+            const int wy = wy0 + e;
+            const bool in = wy >= 0 && wy < N && wx >= 0 && wx < N;
+            z[k][e] = in ? c[wy * N + wx] : make_float2(0.f, 0.f);
+          }
+          ++m;
+          ++got;
         }
-      };
-      int k = beg;
-      for (; k + 4 <= end; k += 4) {
-        float2 z0[TY], z1[TY], z2[TY], z3[TY];
-        fetch(k, z0);
-        fetch(k + 1, z1);
-        fetch(k + 2, z2);
-        fetch(k + 3, z3);
 #pragma unroll
-        for (int e = 0; e < TY; ++e) acc[e] = cadd(cadd(cadd(cadd(acc[e], z0[e]), z1[e]), z2[e]), z3[e]);
-      }
-      for (; k < end; ++k) {
-        float2 z0[TY];
-        fetch(k, z0);
+        for (int k = 0; k < 4; ++k)
+          if (k < got) {
 #pragma unroll
-        for (int e = 0; e < TY; ++e) acc[e] = cadd(acc[e], z0[e]);
+            for (int e = 0; e < TY; ++e) acc[e] = cadd(acc[e], z[k][e]);
+          }
       }
-      __syncthreads();   // the list is rebuilt for the next items
     }
-    if (total == 0 && r.accumulate) return;
     if (w > 0) {
 #pragma unroll
       for (int e = 0; e < TY; ++e) part[((w - 1) * TY + e) * 64 + lane] = acc[e];
@@ -581,34 +660,34 @@ __global__ __launch_bounds__(256) void k_chain_finish(const Item* __restrict__ i
       if (y >= r.H) continue;
       float2 z = acc[e];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) z = cadd(z, part[(k * TY + e) * 64 + lane]);
+      for (int k = 0; k < W - 1; ++k) z = cadd(z, part[(k * TY + e) * 64 + lane]);
       z = cscale(z, sc);
       go[(size_t)y * r.W + x] = r.accumulate ? cadd(go[(size_t)y * r.W + x], z) : z;
     }
     return;
   }
   g -= n_gather;
-  const int n_probe = p.n_reqs * max_modes * (N * N / 16);
+  const int n_probe = p.n_reqs * max_modes * (N * N / 32);
   if (g < n_probe) {
-    const ReqDev& r = reqs.r[g / (max_modes * (N * N / 16))];
-    const int m = (g / (N * N / 16)) % max_modes;
+    const ReqDev& r = reqs.r[g / (max_modes * (N * N / 32))];
+    const int m = (g / (N * N / 32)) % max_modes;
     if (m >= r.M || !r.gphat) return;
-    const int px = (g % (N * N / 16)) * 16 + (t & 15), s = t >> 4;
+    const int px = (g % (N * N / 32)) * 32 + (t & 31), s = t >> 5;
     const int ux = px / N, uy = px % N;
     float2 acc = make_float2(0.f, 0.f);
 #pragma unroll 4
     for (int b = r.item0 + s; b < r.item0 + r.n_items; b += 16) {
       const Item it = items[b];
-      const float2 R = cmul(ramps[(size_t)b * 2 * N + uy], ramps[(size_t)b * 2 * N + N + ux]);
+      const float2 R = xmul(ramps[(size_t)b * 2 * N + uy], ramps[(size_t)b * 2 * N + N + ux]);
       const float2 h = ws[(size_t)(it.tile0 + m) * N * N + px];
-      if (it.valid) acc = cadd(acc, cmul(h, cconj(R)));
+      if (it.valid) acc = cadd(acc, xmul(h, cconj(R)));
     }
     part[t] = acc;
     __syncthreads();
     if (s == 0) {
       float2 z = part[t];
 #pragma unroll
-      for (int k = 1; k < 16; ++k) z = cadd(z, part[16 * k + t]);
+      for (int k = 1; k < 16; ++k) z = cadd(z, part[32 * k + t]);
       r.gphat[(size_t)m * N * N + px] = cscale(z, adj_scale(r, scale));
     }
     return;
@@ -620,10 +699,10 @@ __global__ __launch_bounds__(256) void k_chain_finish(const Item* __restrict__ i
     double* red = reinterpret_cast<double*>(part);
     double acc = 0.0;
     const float* lp = loss_part + (size_t)r.item0 * (N / 32);
-    for (int e = t; e < r.n_items * (N / 32); e += 256) acc += (double)lp[e];
+    for (int e = t; e < r.n_items * (N / 32); e += 512) acc += (double)lp[e];
     red[t] = acc;
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
+    for (int s = 256; s > 0; s >>= 1) {
       if (t < s) red[t] += red[t + s];
       __syncthreads();
     }
@@ -631,7 +710,7 @@ __global__ __launch_bounds__(256) void k_chain_finish(const Item* __restrict__ i
     return;
   }
   g -= p.n_reqs;
-  const int b = g * 256 + t;
+  const int b = g * 512 + t;
   if (b >= n_items) return;
   const Item it = items[b];
   const ReqDev& r = reqs.r[it.req];
@@ -684,8 +763,6 @@ namespace {
 template <int N>
 struct Chain {
   static const float2* tab(const LaunchCtx& L) { return L.tw + N; }
-  static dim3 tiles(const LaunchCtx& L) { return dim3(8 * ((L.n_items + 7) / 8) * L.max_modes); }
-
   static void begin(const LaunchCtx& L) {
     constexpr int W = Ch<N>::T / 64;
     const int item_blocks = (L.n_items + W - 1) / W;
@@ -697,22 +774,39 @@ struct Chain {
                        0, L.stream, L.reqs, L.n_reqs, L.max_modes, L.n_items, item_blocks, fill, L.items, L.ramps,
                        tab(L), L.flags);
   }
-  static void fwd(const LaunchCtx& L, const ChainFwd& p) {
-    hipLaunchKernelGGL((k_chain_fwd<N>), tiles(L), dim3(Ch<N>::T), 0, L.stream, L.items, L.reqs, L.ws,
-                       static_cast<float2*>(L.ck), L.ramps, tab(L), L.item_off, L.n_items, L.max_modes, p);
+  template <int WHAT>
+  static void run_as(const LaunchCtx& L, const ChainRun& p) {
+    hipLaunchKernelGGL((k_chain<N, WHAT>), dim3(8 * ((L.n_items + 7) / 8) * L.max_modes), dim3(Ch<N>::T), 0, L.stream,
+                       L.items, L.reqs, L.ws, static_cast<float2*>(L.ck), L.ramps, tab(L), L.loss_part, L.pos_part,
+                       L.flags, L.item_off, L.n_items, L.max_modes, p);
   }
-  static void far(const LaunchCtx& L, bool grad) {
-    const dim3 g(N / 32, L.n_items);
-    if (grad)
-      hipLaunchKernelGGL((k_chain_far<N, true>), g, dim3(256), 0, L.stream, L.items, L.reqs, L.ws, L.loss_part, L.flags,
-                         L.item_off);
-    else
-      hipLaunchKernelGGL((k_chain_far<N, false>), g, dim3(256), 0, L.stream, L.items, L.reqs, L.ws, L.loss_part,
-                         L.flags, L.item_off);
-  }
-  static void adj(const LaunchCtx& L, const ChainAdj& p) {
-    hipLaunchKernelGGL((k_chain_adj<N>), tiles(L), dim3(Ch<N>::T), 0, L.stream, L.items, L.reqs, L.ws,
-                       static_cast<float2*>(L.ck), L.ramps, tab(L), L.pos_part, L.item_off, L.n_items, L.max_modes, p);
+  static void run(const LaunchCtx& L, ChainRun p) {
+    bool far = false;   // a far-field launch between the chains
+    if (p.what & kFar)
+      for (int q = 0; q < L.n_reqs; ++q) far |= !far_in_chain<N>(L.reqs.r[q].M);
+    const int later = far ? p.what & (kAdjoint | kFirst) : 0;
+    p.what &= ~later;
+    if (p.what & kRecompute) run_as<kRecompute>(L, p);
+    else if (!(p.what & kForward)) run_as<kAdjoint>(L, p);
+    else if constexpr (far_in_chain_at(N)) {
+      if (p.what & kAdjoint) run_as<kForward | kFar | kAdjoint>(L, p);
+      else run_as<kForward | kFar>(L, p);
+    } else {
+      run_as<kForward>(L, p);
+    }
+    if (far) {
+      const dim3 g(N / 32, L.n_items);
+      if (p.what & kSeed)
+        hipLaunchKernelGGL((k_chain_far<N, true>), g, dim3(256), 0, L.stream, L.items, L.reqs, L.ws, L.loss_part,
+                           L.flags, L.item_off);
+      else
+        hipLaunchKernelGGL((k_chain_far<N, false>), g, dim3(256), 0, L.stream, L.items, L.reqs, L.ws, L.loss_part,
+                           L.flags, L.item_off);
+    }
+    if (later) {
+      p.what = later;
+      run_as<kAdjoint>(L, p);
+    }
   }
   static void finish(const LaunchCtx& L, ChainFin p, bool gather, bool rest, float scale) {
     p.n_reqs = L.n_reqs;
@@ -721,12 +815,12 @@ struct Chain {
       for (int q = 0; q < L.n_reqs; ++q) {
         if (!L.reqs.r[q].gobj) continue;
         p.tx = std::max(p.tx, (L.reqs.r[q].W + 63) / 64);
-        p.ty = std::max(p.ty, (L.reqs.r[q].H + 7) / 8);
+        p.ty = std::max(p.ty, (L.reqs.r[q].H + kChainTY - 1) / kChainTY);
       }
     size_t blocks = (size_t)p.n_reqs * p.slices * p.ty * p.tx;
-    if (rest) blocks += (size_t)p.n_reqs * L.max_modes * (N * N / 16) + p.n_reqs + (L.n_items + 255) / 256;
+    if (rest) blocks += (size_t)p.n_reqs * L.max_modes * (N * N / 32) + p.n_reqs + (L.n_items + 511) / 512;
     if (blocks == 0) return;
-    hipLaunchKernelGGL((k_chain_finish<N>), dim3((unsigned)blocks), dim3(256), 0, L.stream, L.items, L.reqs, L.ws,
+    hipLaunchKernelGGL((k_chain_finish<N>), dim3((unsigned)blocks), dim3(512), 0, L.stream, L.items, L.reqs, L.ws,
                        static_cast<const float2*>(L.ck), L.ramps, L.loss_part, L.pos_part, L.n_items, L.max_modes,
                        scale, p);
   }
@@ -746,9 +840,7 @@ bool chain_size(int N) { return N == 64 || N == 128; }
   }
 
 void launch_chain_begin(const LaunchCtx& L, int N) { CHAIN_DISPATCH(N, begin(L)); }
-void launch_chain_fwd(const LaunchCtx& L, int N, const ChainFwd& p) { CHAIN_DISPATCH(N, fwd(L, p)); }
-void launch_chain_far(const LaunchCtx& L, int N, bool grad) { CHAIN_DISPATCH(N, far(L, grad)); }
-void launch_chain_adj(const LaunchCtx& L, int N, const ChainAdj& p) { CHAIN_DISPATCH(N, adj(L, p)); }
+void launch_chain(const LaunchCtx& L, int N, const ChainRun& p) { CHAIN_DISPATCH(N, run(L, p)); }
 void launch_chain_finish(const LaunchCtx& L, int N, const ChainFin& p, bool gather, bool rest, float scale) {
   CHAIN_DISPATCH(N, finish(L, p, gather, rest, scale));
 }

@@ -1,5 +1,8 @@
 // pty_chain.hpp -- 2D transform of an N x N tile held in the registers of one
-// workgroup (N = 64, 128, 192), the building block of the chain kernels.
+// workgroup (N = 64, 128), the building block of the chain kernels. (At N = 192
+// the same tile, 768 threads and 157 KB of LDS, one workgroup per CU, measured
+// slower than the two passes: 15.1 -> 17.9 ms at 6 modes, 20 slices, 256
+// positions.)
 //
 // A workgroup of 4 N threads holds the tile as EL = N / 4 complex values per
 // thread and goes through three layouts; indices: y = yl + 4 r, x = xl + 16 xh,
@@ -18,9 +21,9 @@
 // (k1, yl, x) at P1 k1 + N yl + x; B<->C element (j1, k1, k2, xl) at
 // JS (j1 + XH (k1 / 16)) + XLS xl + 16 k2 + k1 mod 16. The pads P1 = 4 N + 16
 // and XLS let the 64 lanes of a wave hit distinct banks on both sides. For
-// N = 64 a whole complex value is exchanged at once (34 KB); for N = 128 and
-// 192 the real parts go first, then the imaginary ones, through half the space
-// (70 and 157 KB), which leaves room for two workgroups per CU at N = 128.
+// N = 64 a whole complex value is exchanged at once (34 KB a tile); for N = 128
+// the real parts go first, then the imaginary ones, through half the space
+// (68 KB), which leaves room for two tiles per CU.
 // Transforms are unnormalised.
 #pragma once
 
@@ -32,7 +35,7 @@ namespace pty {
 
 template <int N>
 struct Ch {
-  static_assert(N == 64 || N == 128 || N == 192, "register tiles exist for these sizes");
+  static_assert(N == 64 || N == 128, "register tiles exist for these sizes");
   static constexpr int EL = N / 4, T = 4 * N, XH = N / 16, KB = N / 64, WAVES = T / 64;
   static constexpr bool SPLIT = N > 64;
   static constexpr int P1 = 4 * N + 16;
@@ -114,26 +117,18 @@ template <int N> __host__ __device__ __forceinline__ constexpr int off_c2(int e)
 
 // ---- register stages
 
-// Keeps the instructions of one sub-transform together: interleaved by the
-// scheduler, their temporaries exceed the 128 registers of four waves per SIMD.
-__host__ __device__ __forceinline__ void sched_fence() {
-#if defined(__HIP_DEVICE_COMPILE__)
-  __builtin_amdgcn_sched_barrier(0);
-#endif
-}
-
 // A: EL-point DFT over r and the twiddle (tw: the wave's EL roots)
 template <int N, bool INV>
 __host__ __device__ __forceinline__ void ch_stage_a(float2 (&v)[Ch<N>::EL], const float2* tw) {
   constexpr int EL = Ch<N>::EL;
   if (INV) {
 #pragma unroll
-    for (int k = 1; k < EL; ++k) v[k] = cjmul(tw[k], v[k]);
+    for (int k = 1; k < EL; ++k) v[k] = xjmul(tw[k], v[k]);
     Dft<EL, true, true>::run(v);
   } else {
     Dft<EL, false, true>::run(v);
 #pragma unroll
-    for (int k = 1; k < EL; ++k) v[k] = cmul(v[k], tw[k]);
+    for (int k = 1; k < EL; ++k) v[k] = xmul(v[k], tw[k]);
   }
 }
 
@@ -166,10 +161,10 @@ __host__ __device__ __forceinline__ void ch_stage_c(float2 (&v)[Ch<N>::EL], cons
     if (INV) {
       Dft<16, true, true>::run(&v[16 * kb]);
 #pragma unroll
-      for (int k = 1; k < 16; ++k) v[16 * kb + k] = cjmul(tw[k], v[16 * kb + k]);
+      for (int k = 1; k < 16; ++k) v[16 * kb + k] = xjmul(tw[k], v[16 * kb + k]);
     } else {
 #pragma unroll
-      for (int k = 1; k < 16; ++k) v[16 * kb + k] = cmul(v[16 * kb + k], tw[k]);
+      for (int k = 1; k < 16; ++k) v[16 * kb + k] = xmul(v[16 * kb + k], tw[k]);
       Dft<16, false, true>::run(&v[16 * kb]);
     }
   }

@@ -37,6 +37,18 @@ __host__ __device__ __forceinline__ float2 cscale(float2 a, float s) { return ma
 __host__ __device__ __forceinline__ float2 cconj(float2 a) { return make_float2(a.x, -a.y); }
 __host__ __device__ __forceinline__ float cabs2(float2 a) { return a.x * a.x + a.y * a.y; }
 
+// The same products with their fused operations written out, so that every
+// kernel they are inlined into rounds alike (of a.x b.x - a.y b.y the compiler
+// may fuse either product).
+__host__ __device__ __forceinline__ float2 xmul(float2 a, float2 b) {
+  return make_float2(__builtin_fmaf(a.x, b.x, -(a.y * b.y)), __builtin_fmaf(a.x, b.y, a.y * b.x));
+}
+// conj(a) * b
+__host__ __device__ __forceinline__ float2 xjmul(float2 a, float2 b) {
+  return make_float2(__builtin_fmaf(a.x, b.x, a.y * b.y), __builtin_fmaf(a.x, b.y, -(a.y * b.x)));
+}
+__host__ __device__ __forceinline__ float xabs2(float2 a) { return __builtin_fmaf(a.x, a.x, a.y * a.y); }
+
 // ---------------------------------------------------------------- compile-time roots
 
 constexpr double kPi = 3.141592653589793238462643383279502884;
@@ -79,7 +91,7 @@ __host__ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // x * w_n^k with w_n = exp(-2 pi i / n) (forward) or its conjugate (inverse).
-// FINE adds the part of a component that its float misses where that is more
+// FINE rounds alike everywhere (xmul) and adds the part of a component that its float misses where that is more
 // than 1.5e-8 (roots that are no eighth turns): the same roots meet the same
 // values slice after slice, so their rounding adds up coherently, where the
 // rounding of the products averages out. Left in, it is most of the error of a
@@ -100,17 +112,25 @@ __host__ __device__ __forceinline__ float2 twiddle_const(float2 x) {
     constexpr CosSin cs = unit_root(r, n);
     constexpr float c = (float)cs.c;
     constexpr float s = INV ? (float)cs.s : (float)(-cs.s);
-    if constexpr (FINE && (8 * r) % n != 0) {
+    if constexpr (FINE) {
       // the small terms go into the accumulator before the large products (to
       // a rounded sum they would be lost: they are below half a spacing of it)
       constexpr double dc = cs.c - (double)c, ds = (INV ? cs.s : -cs.s) - (double)s;
-      constexpr bool use_c = dc > 1.5e-8 || dc < -1.5e-8, use_s = ds > 1.5e-8 || ds < -1.5e-8;
+      constexpr bool part = (8 * r) % n != 0;
+      constexpr bool use_c = part && (dc > 1.5e-8 || dc < -1.5e-8), use_s = part && (ds > 1.5e-8 || ds < -1.5e-8);
       constexpr float fc = (float)dc, fs = (float)ds;
-      if constexpr (use_c || use_s) {
-        const float px = (use_c ? x.x * fc : 0.f) - (use_s ? x.y * fs : 0.f);
-        const float py = (use_s ? x.x * fs : 0.f) + (use_c ? x.y * fc : 0.f);
-        return make_float2(__builtin_fmaf(x.x, c, __builtin_fmaf(-x.y, s, px)),
-                           __builtin_fmaf(x.x, s, __builtin_fmaf(x.y, c, py)));
+      if constexpr (use_c && use_s) {
+        return make_float2(
+            __builtin_fmaf(x.x, c, __builtin_fmaf(-x.y, s, __builtin_fmaf(x.x, fc, -(x.y * fs)))),
+            __builtin_fmaf(x.x, s, __builtin_fmaf(x.y, c, __builtin_fmaf(x.x, fs, x.y * fc))));
+      } else if constexpr (use_c) {
+        return make_float2(__builtin_fmaf(x.x, c, __builtin_fmaf(-x.y, s, x.x * fc)),
+                           __builtin_fmaf(x.x, s, __builtin_fmaf(x.y, c, x.y * fc)));
+      } else if constexpr (use_s) {
+        return make_float2(__builtin_fmaf(x.x, c, __builtin_fmaf(-x.y, s, -(x.y * fs))),
+                           __builtin_fmaf(x.x, s, __builtin_fmaf(x.y, c, x.x * fs)));
+      } else {
+        return xmul(x, make_float2(c, s));
       }
     }
     return make_float2(x.x * c - x.y * s, x.x * s + x.y * c);
@@ -118,6 +138,14 @@ __host__ __device__ __forceinline__ float2 twiddle_const(float2 x) {
 }
 
 // ---------------------------------------------------------------- register DFTs
+
+// Keeps the instructions of one sub-transform together: interleaved by the
+// scheduler, their temporaries exceed the 128 registers of four waves per SIMD.
+__host__ __device__ __forceinline__ void sched_fence() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_sched_barrier(0);
+#endif
+}
 
 template <int n>
 constexpr int first_radix() { return n % 4 == 0 ? 4 : (n % 2 == 0 ? 2 : (n % 3 == 0 ? 3 : n)); }

@@ -243,29 +243,24 @@ void launch_lsq_probe(hipStream_t s, float2* P, const float2* g, const float* wp
                       int M, int N2, float delta, double gamma, float beta, double* alpha);
 
 // Chain kernels (pty_chain.hip): every slice of a tile in one launch.
-struct ChainFwd {
-  int store;                // store the entry waves in the checkpoint slots
-  int from, to;             // from >= 0: recompute slices from + 1 .. to into seg instead
-  float2* seg;              // [tiles][seg_len][N][N]
-  int seg_len;
-};
-struct ChainAdj {
-  int first;                // start at every request's last slice, from the detector gradient
-  int hi, lo;               // slices hi .. lo (hi unused with first)
-  float2* seg;              // entry waves of slices that are no multiples of ck_every, or null
-  int seg_len, seg_base;
+enum { kForward = 1, kRecompute = 2, kFar = 4, kSeed = 8, kAdjoint = 16, kFirst = 32 };   // see k_chain
+struct ChainRun {
+  int what;
+  int store;                // kForward: store the entry waves in the checkpoint slots
+  int from, to;             // kRecompute
+  int hi, lo;               // kAdjoint: slices hi .. lo (hi unused with kFirst; lo -1: down to slice 0)
+  float2* seg;              // entry waves of slices that are no multiples of ck_every, or null:
+  int seg_len, seg_base;    // slice i at slot i - seg_base of [tiles][seg_len][N][N]
 };
 struct ChainFin {
   int lo, slices;           // slices of the object-gradient sum
-  const float2* seg;        // as in ChainAdj
+  const float2* seg;        // as in ChainRun
   int seg_len, seg_base;
   int n_reqs, tx, ty;       // (set by the launcher)
 };
 bool chain_size(int N);
 void launch_chain_begin(const LaunchCtx& L, int N);
-void launch_chain_fwd(const LaunchCtx& L, int N, const ChainFwd& p);
-void launch_chain_far(const LaunchCtx& L, int N, bool grad);
-void launch_chain_adj(const LaunchCtx& L, int N, const ChainAdj& p);
+void launch_chain(const LaunchCtx& L, int N, const ChainRun& p);
 void launch_chain_finish(const LaunchCtx& L, int N, const ChainFin& p, bool gather, bool rest, float scale);
 void launch_chain_plain_inv(int N, hipStream_t s, const float2* tw, const float2* src, float2* dst, int n, float scale,
                             bool acc);
