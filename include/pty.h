@@ -177,18 +177,17 @@ pty_status pty_set_strategy(pty_ctx* ctx, int32_t strategy);
 
 /* How the object gradient (Sec. 3.2: the sum over the group of every
  * position's windowed contribution, slice by slice) is accumulated.
- * ATOMIC (default): the adjoint row pass adds each contribution with float
- * atomics; the summation order, and so the last bits of the gradient, vary
- * from run to run (the chain kernels of PTY_STRATEGY_AUTO use no atomics: under
- * either mode their sum is in batch order). ORDERED: the adjoint row pass stores each position's
- * contribution in a scratch area allocated at create (max_batch x N x N
- * complex64) and a second kernel adds them tile by tile in batch order, so
+ * ATOMIC (default): no order is promised. Large groups of many modes at N = 256
+ * add each contribution with float atomics in the adjoint row pass (the last
+ * bits of the gradient then vary from run to run); the others, faster so, take
+ * the sum of the ORDERED mode. ORDERED: the adjoint stores each position's
+ * contribution (in the slice's checkpoint, or in a scratch area allocated at
+ * create, max_batch x N x N complex64, with half checkpoints, recomputed slices
+ * and LSQML) and a later kernel adds them tile by tile in batch order, so
  * loss_and_grad and reconstruct_step give bit-identical results on repeated
  * calls with the same inputs, and a reconstruction gives the same bits alone
  * or in a grouped step (the dense position gradient excepted when a batch
- * lists one position twice). ORDERED also avoids the contention of many
- * overlapping windows (a whole dense scan in one group). It applies to the
- * two-pass kernels; with it set, RESIDENT runs two-pass. The LSQML
+ * lists one position twice). With it set, RESIDENT runs two-pass. The LSQML
  * illumination sums follow the same mode (a context created with lsqml also
  * holds max_batch x N x N floats of scratch for them). Returns PTY_EINVAL for
  * another mode. */
@@ -436,8 +435,7 @@ void pty_destroy(pty_ctx* ctx);
  * S, object size, loss) in shared kernel launches. Entry waves are stored for
  * every slice (no recompute) in the group's workspace. A grouped step uses
  * the ordered object-gradient reduction when every context in it is set to
- * PTY_REDUCE_ORDERED (the group holds max_items x N x N complex64 of scratch
- * for it), else atomics. */
+ * PTY_REDUCE_ORDERED, else that of PTY_REDUCE_ATOMIC. */
 typedef struct pty_group pty_group;
 
 typedef struct {

@@ -17,7 +17,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libpty.so")
 BUILD_DIR = os.path.join(PKG, "_build")   # object files (git-ignored)
 
-SOURCES = ["pty_kernels.hip", "pty_chain.hip", "pty_api.cpp"]
+SOURCES = ["pty_kernels.hip", "pty_chain.hip", "pty_finish.hip", "pty_api.cpp"]
 
 HIP_FLAGS = [
     "--offload-arch=gfx950",
@@ -41,7 +41,7 @@ def hipcc():
     raise RuntimeError("hipcc not found")
 
 
-def build(verbose: bool = False, jobs: int = 3, defines=(), out: str = LIB) -> str:
+def build(verbose: bool = False, jobs: int = 4, defines=(), out: str = LIB) -> str:
     """Compile every source and link libpty.so (or `out`); returns its path.
     `defines` are extra -D macros (tuning constants of the kernels)."""
     cc = hipcc()

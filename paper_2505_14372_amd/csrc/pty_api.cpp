@@ -281,7 +281,6 @@ struct pty_group {
   float2 *tw = nullptr, *ws = nullptr, *ck = nullptr, *ramps = nullptr;
   Item* items = nullptr;
   float *loss_part = nullptr, *pos_part = nullptr;
-  float2* cscr = nullptr;   // ordered object-gradient reduction scratch [max_items][N][N]
   int* flags = nullptr;
   std::string err;
 };
@@ -339,6 +338,31 @@ ReqDev base_req(pty_ctx* c) {
   return r;
 }
 
+// Two-pass kernels: the object gradient from stored contributions, or by float
+// atomics in the adjoint row pass? The atomics of overlapping windows cost a
+// fixed time per position and slice, which the row pass hides only behind many
+// modes; stored contributions cost their own traffic. Measured (loss and
+// gradients, stored against atomics): 256 x 256, 1 mode, 8 slices, 300 positions
+// 2.7 against 4.2 - 4.9 ms; 3 modes, 10 slices, 128 positions 3.2 against 3.8 -
+// 4.0; 4 modes, 4 slices, 512 positions 6.7 against 7.0 - 7.4; 8 modes, 10 slices,
+// 128 positions 7.3 against 7.5 - 7.7; 8 modes, 30 slices, 512 positions 84.2
+// against 83.8. So under PTY_REDUCE_ATOMIC the atomics keep the large groups of
+// many modes at the largest window (a slice's contributions then exceed half the
+// memory-side cache), and chunks on concurrent streams where the sum is taken
+// slice by slice.
+bool store_contributions(bool ordered, int N, int M, int B) { return ordered || !(N == 256 && M >= 8 && B > 256); }
+
+// Sets where the stored contributions of L wait: in the checkpoint slots until
+// the last launch (every slice stored in float), else in the scratch area, summed
+// slice by slice.
+void set_sum(const pty_ctx* c, LaunchCtx& L) {
+  const bool ordered = c->reduce == PTY_REDUCE_ORDERED;
+  const bool stored = !L.chain && !L.resident && store_contributions(ordered, c->g.N, c->g.n_modes, L.n_items);
+  L.defer = stored && !L.wsum && !c->ck_half && c->ck_every == 1 ? 1 : 0;
+  L.cscr = stored && !L.defer && (ordered || c->n_streams <= 1) ? c->cscr : nullptr;
+  L.wscr = L.wsum && L.cscr ? c->lsq_wscr : nullptr;
+}
+
 LaunchCtx ctx_launch(pty_ctx* c, hipStream_t s, const ReqDev& r, int B) {
   LaunchCtx L{};
   L.stream = s;
@@ -359,7 +383,7 @@ LaunchCtx ctx_launch(pty_ctx* c, hipStream_t s, const ReqDev& r, int B) {
   L.flags = c->flags;
   L.chain = use_chain(c) ? 1 : 0;
   L.resident = (use_resident(c->strategy, c->g.N, c->ck_every) && c->reduce != PTY_REDUCE_ORDERED) ? 1 : 0;
-  L.cscr = c->reduce == PTY_REDUCE_ORDERED ? c->cscr : nullptr;
+  set_sum(c, L);
   // float checkpoints: the column passes write the stored entry waves' row
   // spectra straight into the checkpoint slots (the resident chains ignore it)
   L.ck_spec = c->ck_half ? 0 : 1;
@@ -401,15 +425,15 @@ void run_prepare(const LaunchCtx& L, int N) {
   launch_items(L, N);
 }
 
-// Zeros the adjoint adds into: the object gradient (the chain kernels write
-// theirs whole) and the dense position gradient (zeroed by run_prepare of a
+// Zeros the adjoint adds into: the object gradient (one that is summed from
+// stored contributions is written whole) and the dense position gradient (zeroed by run_prepare of a
 // chain step; `prepared`: that has run in this call).
 void clear_grads(const LaunchCtx& L, bool prepared) {
   for (int q = 0; q < L.n_reqs; ++q) {
     const ReqDev& r = L.reqs.r[q];
     if (r.accumulate) continue;
     ProfScope p(P_FILL, L.stream);
-    if (r.gobj && !L.chain) launch_fill(L.stream, (float*)r.gobj, (size_t)r.S * r.H * r.W * 2, 0.f);
+    if (r.gobj && !L.chain && !L.defer) launch_fill(L.stream, (float*)r.gobj, (size_t)r.S * r.H * r.W * 2, 0.f);
     if (r.gpos_dense && !(L.chain && prepared)) launch_fill(L.stream, r.gpos_dense, (size_t)r.J * 2, 0.f);
   }
 }
@@ -501,13 +525,13 @@ void run_backward_chunk(const LaunchCtx& L, int N, int S_max, const std::vector<
       a.seg_len = k - 1;
       a.seg_base = i0 + 1;
       { ProfScope q(P_CHAIN, L.stream); launch_chain(L, N, a); }
-      ChainFin g{};
+      FinishRun g{};
       g.lo = i0;
       g.slices = i1 - i0 + 1;
       g.seg = sg;
       g.seg_len = k - 1;
       g.seg_base = i0 + 1;
-      { ProfScope q(P_OBJ_GATHER, L.stream); launch_chain_finish(L, N, g, true, false, scale); }
+      { ProfScope q(P_OBJ_GATHER, L.stream); launch_finish(L, N, g, true, false, scale); }
       i1 = i0 - 1;
     }
     return;
@@ -608,16 +632,14 @@ void run_chunk(const LaunchCtx& L, int N, int S_max, const std::vector<int>& las
   run_backward_chunk(L, N, S_max, last, scale, k, ws2, seg);
 }
 
+// Stored contributions of every slice (chain kernels, or deferred by the row
+// passes) are summed here too; with recomputed segments that is done.
 void run_finish_backward(const LaunchCtx& L, int N, int S_max, int k, float scale) {
-  if (L.chain) {
-    ChainFin p{};
-    p.slices = k == 1 ? S_max : 0;
-    ProfScope q(P_OBJ_GATHER, L.stream);
-    launch_chain_finish(L, N, p, k == 1, true, scale);
-    return;
-  }
-  { ProfScope p(P_PROBE_GRAD, L.stream); launch_probe_grad(L, N, scale); }
-  { ProfScope p(P_POS_REDUCE, L.stream); launch_pos_reduce(L, N, scale); }
+  const bool gather = (L.chain && k == 1) || L.defer;
+  FinishRun p{};
+  p.slices = gather ? S_max : 0;
+  ProfScope q(gather ? P_OBJ_GATHER : P_PROBE_GRAD, L.stream);
+  launch_finish(L, N, p, gather, true, scale);
 }
 
 pty_status check_call(pty_ctx* c, const void* probe, const void* object, const void* positions,
@@ -662,7 +684,6 @@ void run_fused(pty_ctx* c, const LaunchCtx& L0, float scale) {
       (void)hipStreamWaitEvent(L.stream, c->ev_join[k], 0);
     }
   }
-  if (L.reqs.r[0].loss_out && !L.chain) run_finish_forward(L, N);
   run_finish_backward(L, N, S, c->ck_every, scale);
 }
 
@@ -923,6 +944,7 @@ pty_status pty_forward_static(pty_ctx* c, void* stream, const pty_c64* probe, co
   L.ck = nullptr;
   L.pos_part = nullptr;
   L.cscr = nullptr;
+  L.defer = 0;
   run_prepare(L, N);
   for (auto& ch : split_chunks(B, c->chunk)) run_forward_chunk(sub(L, ch.first, ch.second), N, S, {S - 1}, false);
   if (r.loss_out) run_finish_forward(L, N);
@@ -1309,8 +1331,8 @@ extern "C" pty_status pty_reconstruct_step(pty_ctx* c, void* stream, pty_state* 
   LaunchCtx L = ctx_launch(c, s, r, B);
   if (epie) {
     L.emax = 1;
-    L.resident = 0;
-    L.chain = 0;
+    L.resident = L.chain = 0;   // the two-pass kernels
+    set_sum(c, L);
   }
   clear_grads(L, true);
   if (epie) {
@@ -1378,10 +1400,9 @@ extern "C" pty_status pty_lsqml_step(pty_ctx* c, void* stream, pty_state* st, co
   r.modulus = 1;
   r.wsum = c->lsq_w;
   LaunchCtx L = ctx_launch(c, s, r, B);
-  L.resident = 0;
-  L.chain = 0;
+  L.resident = L.chain = 0;   // the two-pass kernels
   L.wsum = 1;
-  L.wscr = L.cscr ? c->lsq_wscr : nullptr;   // the illumination sums follow the reduction mode
+  set_sum(c, L);   // (the illumination sums go the same way)
   clear_grads(L, true);
   {
     ProfScope p(P_FILL, s);
@@ -1423,7 +1444,6 @@ Sizes group_sizes(int N, int max_items, int max_tiles, long long max_ck) {
   b += align256((size_t)max_items * nblk * sizeof(float));
   b += align256((size_t)max_tiles * nblk * 2 * sizeof(float));
   b += align256(4 * sizeof(int));
-  b += align256((size_t)max_items * N2 * sizeof(float2));   // ordered reduction scratch
   s.bytes = b;
   return s;
 }
@@ -1459,8 +1479,7 @@ pty_status pty_group_create(int32_t N, int32_t max_items, int32_t max_tiles, int
       (st = dmalloc(&G->ck, (size_t)max_ckpt_tiles * N2, G->err)) || (st = dmalloc(&G->items, (size_t)max_items, G->err)) ||
       (st = dmalloc(&G->ramps, (size_t)max_items * 2 * N, G->err)) ||
       (st = dmalloc(&G->loss_part, (size_t)max_items * nblk, G->err)) ||
-      (st = dmalloc(&G->pos_part, (size_t)max_tiles * nblk * 2, G->err)) || (st = dmalloc(&G->flags, 4, G->err)) ||
-      (st = dmalloc(&G->cscr, (size_t)max_items * N2, G->err)))
+      (st = dmalloc(&G->pos_part, (size_t)max_tiles * nblk * 2, G->err)) || (st = dmalloc(&G->flags, 4, G->err)))
     return fail(st);
   std::vector<float2> tw = roots(N);
   if (hipMemcpy(G->tw, tw.data(), tw.size() * sizeof(float2), hipMemcpyHostToDevice) != hipSuccess) return fail(PTY_EHIP);
@@ -1472,7 +1491,7 @@ pty_status pty_group_create(int32_t N, int32_t max_items, int32_t max_tiles, int
 void pty_group_destroy(pty_group* G) {
   if (!G) return;
   dfree(G->tw); dfree(G->ws); dfree(G->ck); dfree(G->items); dfree(G->ramps);
-  dfree(G->loss_part); dfree(G->pos_part); dfree(G->flags); dfree(G->cscr);
+  dfree(G->loss_part); dfree(G->pos_part); dfree(G->flags);
   delete G;
 }
 
@@ -1524,7 +1543,6 @@ pty_status pty_group_reconstruct_step(pty_group* G, void* stream, const pty_grou
     L.loss_part = G->loss_part;
     L.pos_part = G->pos_part;
     L.flags = G->flags;
-    L.cscr = ordered ? G->cscr : nullptr;
     int item0 = 0, tile0 = 0, S_max = 0, M_max = 0, nq = 0;
     long long ck0 = 0;
     bool all_live = false;
@@ -1565,6 +1583,7 @@ pty_status pty_group_reconstruct_step(pty_group* G, void* stream, const pty_grou
     L.n_reqs = nq;
     L.n_items = item0;
     L.max_modes = M_max;
+    L.defer = !chain && !resident && store_contributions(ordered, N, M_max, item0);
     clear_grads(L, true);
     std::sort(last_steps.begin(), last_steps.end());
     last_steps.erase(std::unique(last_steps.begin(), last_steps.end()), last_steps.end());
@@ -1572,7 +1591,6 @@ pty_status pty_group_reconstruct_step(pty_group* G, void* stream, const pty_grou
     run_prepare(L, N);
     set_chain_final(L, N, true);
     run_chunk(L, N, S_max, last_steps, 1.f, 1, nullptr, nullptr);
-    if (!L.chain) run_finish_forward(L, N);
     run_finish_backward(L, N, S_max, 1, 1.f);
     for (int q : mine) {
       pty_ctx* c = items[q].ctx;

@@ -12,7 +12,7 @@
 //
 // A step is: k_chain_begin (probe spectra, item descriptors, zeroed position
 // gradient), k_chain (forward and adjoint; with several modes a launch each and
-// k_chain_far, the noise model, between them), k_chain_finish (object gradient,
+// k_chain_far, the noise model, between them), k_finish (object gradient,
 // probe-spectrum sum, loss, position gradient: independent of each other, one
 // launch) and k_chain_plain (probe gradient), where the two-pass kernels take
 // 4 S + 11 launches.
@@ -43,8 +43,6 @@ __device__ __forceinline__ ConstTab here(ConstTab p) {
   asm volatile("" : "+s"(p));
   return p;
 }
-
-constexpr int kChainTY = 4;   // rows of an object-gradient tile
 
 enum Side { A1, B1, B2, C2 };
 template <int N, int SIDE>
@@ -562,179 +560,6 @@ __global__ __launch_bounds__(256) void k_chain_far(const Item* __restrict__ item
   }
 }
 
-// Last launch of the adjoint: four independent sums, split over workgroup
-// ranges (all in a fixed order, so repeated calls give the same bits):
-//   - object gradient: one workgroup per 4 x 64 tile and slice; wave w adds,
-//     in batch order, the contributions of the positions b = w mod 8 whose
-//     windows cover the tile (a position that does not cover a pixel adds
-//     nothing to it, so a pixel's sum does not depend on the tile's shape), and
-//     the eight sums are added in wave order. No list and no barrier before the
-//     end: with one list per workgroup, 8 x 64 tiles and 4 waves this launch took
-//     36 us at 64 x 64, 1 slice, 256 positions (now 15), 53 us at 2 modes, 8 slices
-//     (35; 118 MB of contributions) and 1.15 ms at 128 x 128, 4 modes, 8 slices,
-//     1024 positions (1.07; 4.3 GB, read at 4.0 TB/s);
-//   - probe-spectrum gradient: 32 pixels x 16 interleaved sums over the items;
-//   - loss; position gradients.
-// p.gather / p.rest select the parts (with recomputed segments the object
-// gradient is summed segment by segment).
-template <int N>
-__global__ __launch_bounds__(512) void k_chain_finish(const Item* __restrict__ items, const ReqTable reqs,
-                                                      const float2* __restrict__ ws, const float2* __restrict__ ck,
-                                                      const float2* __restrict__ ramps,
-                                                      const float* __restrict__ loss_part,
-                                                      const float* __restrict__ pos_part, int n_items, int max_modes,
-                                                      float scale, ChainFin p) {
-  constexpr int TY = kChainTY, W = 8;
-  __shared__ float2 part[(W - 1) * TY * 64 > 512 ? (W - 1) * TY * 64 : 512];
-  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
-  int g = blockIdx.x;
-  const int n_gather = p.n_reqs * p.slices * p.ty * p.tx;
-  if (g < n_gather) {
-    const int tx = g % p.tx, ty = (g / p.tx) % p.ty, s = (g / (p.tx * p.ty)) % p.slices, q = g / (p.tx * p.ty * p.slices);
-    const ReqDev& r = reqs.r[q];
-    const int i = p.lo + s, x0 = tx * 64, y0 = ty * TY, x = x0 + lane;
-    if (i >= r.S || !r.gobj || x0 >= r.W || y0 >= r.H) return;
-    const bool sg = p.seg && i % r.ck_every != 0;
-    // contribution tile of (item, mode): base + (first tile of the item + mode) * step
-    const float2* base = sg ? p.seg + (size_t)(i - p.seg_base) * N * N
-                            : ck + (size_t)(i / r.ck_every) * r.n_items * r.M * N * N;
-    const size_t step = (size_t)(sg ? p.seg_len : 1) * N * N;
-    float2 acc[TY];
-#pragma unroll
-    for (int k = 0; k < TY; ++k) acc[k] = make_float2(0.f, 0.f);
-    for (int b0 = r.item0; b0 < r.item0 + r.n_items; b0 += 64 * W) {
-      const int b = b0 + lane * W + w;
-      int ny = 0, nx = 0, t0 = 0;
-      bool hit = false;
-      if (b < r.item0 + r.n_items) {
-        const Item it = items[b];
-        ny = it.ny;
-        nx = it.nx;
-        t0 = sg ? it.tile0 : (int)it.ck0;
-        hit = it.valid && ny < y0 + TY && ny + N > y0 && nx < x0 + 64 && nx + N > x0;
-      }
-      unsigned long long todo = __ballot(hit);
-      // up to four contributions at a time, the loads of all issued before the additions
-      int l = -1, m = r.M;
-      while (todo || m < r.M) {
-        float2 z[4][TY];
-        int got = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          if (m >= r.M) {
-            if (!todo) break;
-            l = __builtin_ctzll(todo);
-            todo &= todo - 1;
-            m = 0;
-          }
-          const int wx = x - __builtin_amdgcn_readlane(nx, l), wy0 = y0 - __builtin_amdgcn_readlane(ny, l);
-          const float2* c = base + ((size_t)__builtin_amdgcn_readlane(t0, l) + (size_t)m) * step;
-#pragma unroll
-          for (int e = 0; e < TY; ++e) {
-            const int wy = wy0 + e;
-            const bool in = wy >= 0 && wy < N && wx >= 0 && wx < N;
-            z[k][e] = in ? c[wy * N + wx] : make_float2(0.f, 0.f);
-          }
-          ++m;
-          ++got;
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-          if (k < got) {
-#pragma unroll
-            for (int e = 0; e < TY; ++e) acc[e] = cadd(acc[e], z[k][e]);
-          }
-      }
-    }
-    if (w > 0) {
-#pragma unroll
-      for (int e = 0; e < TY; ++e) part[((w - 1) * TY + e) * 64 + lane] = acc[e];
-    }
-    __syncthreads();
-    if (w != 0 || x >= r.W) return;
-    const float sc = adj_scale(r, scale);
-    float2* go = r.gobj + (size_t)i * r.H * r.W;
-#pragma unroll
-    for (int e = 0; e < TY; ++e) {
-      const int y = y0 + e;
-      if (y >= r.H) continue;
-      float2 z = acc[e];
-#pragma unroll
-      for (int k = 0; k < W - 1; ++k) z = cadd(z, part[(k * TY + e) * 64 + lane]);
-      z = cscale(z, sc);
-      go[(size_t)y * r.W + x] = r.accumulate ? cadd(go[(size_t)y * r.W + x], z) : z;
-    }
-    return;
-  }
-  g -= n_gather;
-  const int n_probe = p.n_reqs * max_modes * (N * N / 32);
-  if (g < n_probe) {
-    const ReqDev& r = reqs.r[g / (max_modes * (N * N / 32))];
-    const int m = (g / (N * N / 32)) % max_modes;
-    if (m >= r.M || !r.gphat) return;
-    const int px = (g % (N * N / 32)) * 32 + (t & 31), s = t >> 5;
-    const int ux = px / N, uy = px % N;
-    float2 acc = make_float2(0.f, 0.f);
-#pragma unroll 4
-    for (int b = r.item0 + s; b < r.item0 + r.n_items; b += 16) {
-      const Item it = items[b];
-      const float2 R = xmul(ramps[(size_t)b * 2 * N + uy], ramps[(size_t)b * 2 * N + N + ux]);
-      const float2 h = ws[(size_t)(it.tile0 + m) * N * N + px];
-      if (it.valid) acc = cadd(acc, xmul(h, cconj(R)));
-    }
-    part[t] = acc;
-    __syncthreads();
-    if (s == 0) {
-      float2 z = part[t];
-#pragma unroll
-      for (int k = 1; k < 16; ++k) z = cadd(z, part[32 * k + t]);
-      r.gphat[(size_t)m * N * N + px] = cscale(z, adj_scale(r, scale));
-    }
-    return;
-  }
-  g -= n_probe;
-  if (g < p.n_reqs) {
-    const ReqDev& r = reqs.r[g];
-    if (!r.loss_out) return;
-    double* red = reinterpret_cast<double*>(part);
-    double acc = 0.0;
-    const float* lp = loss_part + (size_t)r.item0 * (N / 32);
-    for (int e = t; e < r.n_items * (N / 32); e += 512) acc += (double)lp[e];
-    red[t] = acc;
-    __syncthreads();
-    for (int s = 256; s > 0; s >>= 1) {
-      if (t < s) red[t] += red[t + s];
-      __syncthreads();
-    }
-    if (t == 0) *r.loss_out = red[0];
-    return;
-  }
-  g -= p.n_reqs;
-  const int b = g * 512 + t;
-  if (b >= n_items) return;
-  const Item it = items[b];
-  const ReqDev& r = reqs.r[it.req];
-  float g0 = 0.f, g1 = 0.f;
-  if (it.valid)
-    for (int m = 0; m < r.M; ++m) {
-      const float* pp = pos_part + (size_t)(it.tile0 + m) * (N / 32) * 2;
-      g0 += pp[0];
-      g1 += pp[1];
-    }
-  const float f = 6.283185307179586f * adj_scale(r, scale);
-  g0 *= f;
-  g1 *= f;
-  const int local = b - r.item0;
-  if (r.gpos) {
-    if (r.accumulate) { r.gpos[2 * local] += g0; r.gpos[2 * local + 1] += g1; }
-    else { r.gpos[2 * local] = g0; r.gpos[2 * local + 1] = g1; }
-  }
-  if (r.gpos_dense && it.valid) {
-    atomicAdd(r.gpos_dense + 2 * it.j, g0);
-    atomicAdd(r.gpos_dense + 2 * it.j + 1, g1);
-  }
-}
-
 // dst = scale F^-1(src) of the probe-sized tiles (src transposed), added to dst if accumulate.
 template <int N>
 __global__ __launch_bounds__(Ch<N>::T) void k_chain_plain(const float2* __restrict__ src, float2* __restrict__ dst,
@@ -808,22 +633,6 @@ struct Chain {
       run_as<kAdjoint>(L, p);
     }
   }
-  static void finish(const LaunchCtx& L, ChainFin p, bool gather, bool rest, float scale) {
-    p.n_reqs = L.n_reqs;
-    p.tx = p.ty = 0;
-    if (gather)
-      for (int q = 0; q < L.n_reqs; ++q) {
-        if (!L.reqs.r[q].gobj) continue;
-        p.tx = std::max(p.tx, (L.reqs.r[q].W + 63) / 64);
-        p.ty = std::max(p.ty, (L.reqs.r[q].H + kChainTY - 1) / kChainTY);
-      }
-    size_t blocks = (size_t)p.n_reqs * p.slices * p.ty * p.tx;
-    if (rest) blocks += (size_t)p.n_reqs * L.max_modes * (N * N / 32) + p.n_reqs + (L.n_items + 511) / 512;
-    if (blocks == 0) return;
-    hipLaunchKernelGGL((k_chain_finish<N>), dim3((unsigned)blocks), dim3(512), 0, L.stream, L.items, L.reqs, L.ws,
-                       static_cast<const float2*>(L.ck), L.ramps, L.loss_part, L.pos_part, L.n_items, L.max_modes,
-                       scale, p);
-  }
   static void plain_inv(hipStream_t s, const float2* tw, const float2* src, float2* dst, int n, float scale, bool acc) {
     hipLaunchKernelGGL((k_chain_plain<N>), dim3(n), dim3(Ch<N>::T), 0, s, src, dst, tw + N, scale, acc ? 1 : 0);
   }
@@ -841,9 +650,6 @@ bool chain_size(int N) { return N == 64 || N == 128; }
 
 void launch_chain_begin(const LaunchCtx& L, int N) { CHAIN_DISPATCH(N, begin(L)); }
 void launch_chain(const LaunchCtx& L, int N, const ChainRun& p) { CHAIN_DISPATCH(N, run(L, p)); }
-void launch_chain_finish(const LaunchCtx& L, int N, const ChainFin& p, bool gather, bool rest, float scale) {
-  CHAIN_DISPATCH(N, finish(L, p, gather, rest, scale));
-}
 void launch_chain_plain_inv(int N, hipStream_t s, const float2* tw, const float2* src, float2* dst, int n, float scale,
                             bool acc) {
   CHAIN_DISPATCH(N, plain_inv(s, tw, src, dst, n, scale, acc));

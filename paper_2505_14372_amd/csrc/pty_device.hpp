@@ -13,6 +13,96 @@ __device__ __forceinline__ void raise_flag(int* flags, int bit) {
   if (flags) atomicOr(flags, bit);
 }
 
+// Sum over a request's items lo .. hi - 1, in a fixed order, of their
+// contributions to the TY x 64 tile of an object slice at (y0, x0), by a
+// workgroup of 8 waves: wave w adds, in batch order, those of the items
+// b = item0 + w mod 8 whose windows cover the tile (an item that does not cover
+// a pixel adds nothing to it, so a pixel's sum does not depend on the tile's
+// shape), and wave 0 adds the eight sums in wave order. Contribution `p` of item
+// b is tile index(b, item) + p of `src` (tiles `step` apart, parts per item);
+// with WS the floats of wsrc are summed alike. part / wpart: LDS for 7 waves.
+// Returns whether this thread (of wave 0, column x0 + lane) holds the sums.
+template <int N, int TY, bool WS, typename INDEX>
+__device__ __forceinline__ bool object_sum(const Item* __restrict__ items, int item0, int lo, int hi, int y0, int x0,
+                                           const float2* __restrict__ src, const float* __restrict__ wsrc, size_t step,
+                                           int parts, INDEX&& index, float2 (&acc)[TY], float (&wacc)[TY], float2* part,
+                                           float* wpart) {
+  constexpr int W = 8;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), x = x0 + lane;
+#pragma unroll
+  for (int k = 0; k < TY; ++k) {
+    acc[k] = make_float2(0.f, 0.f);
+    wacc[k] = 0.f;
+  }
+  for (int b0 = item0 + (lo - item0) / (64 * W) * (64 * W); b0 < hi; b0 += 64 * W) {
+    const int b = b0 + lane * W + w;
+    int ny = 0, nx = 0, t0 = 0;
+    bool hit = false;
+    if (b >= lo && b < hi) {
+      const Item it = items[b];
+      ny = it.ny;
+      nx = it.nx;
+      t0 = index(b, it);
+      hit = it.valid && ny < y0 + TY && ny + N > y0 && nx < x0 + 64 && nx + N > x0;
+    }
+    unsigned long long todo = __ballot(hit);
+    // up to four contributions at a time, the loads of all issued before the additions
+    int l = -1, m = parts;
+    while (todo || m < parts) {
+      float2 z[4][TY];
+      float zw[4][TY];
+      int got = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (m >= parts) {
+          if (!todo) break;
+          l = __builtin_ctzll(todo);
+          todo &= todo - 1;
+          m = 0;
+        }
+        const int wx = x - __builtin_amdgcn_readlane(nx, l), wy0 = y0 - __builtin_amdgcn_readlane(ny, l);
+        const size_t at = ((size_t)__builtin_amdgcn_readlane(t0, l) + (size_t)m) * step;
+        const float2* c = src + at;
+#pragma unroll
+        for (int e = 0; e < TY; ++e) {
+          const int wy = wy0 + e;
+          const bool in = wy >= 0 && wy < N && wx >= 0 && wx < N;
+          z[k][e] = in ? c[wy * N + wx] : make_float2(0.f, 0.f);
+          if constexpr (WS) zw[k][e] = in ? (wsrc + at)[wy * N + wx] : 0.f;
+        }
+        ++m;
+        ++got;
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (k < got) {
+#pragma unroll
+          for (int e = 0; e < TY; ++e) {
+            acc[e] = cadd(acc[e], z[k][e]);
+            if constexpr (WS) wacc[e] += zw[k][e];
+          }
+        }
+    }
+  }
+  if (w > 0) {
+#pragma unroll
+    for (int e = 0; e < TY; ++e) {
+      part[((w - 1) * TY + e) * 64 + lane] = acc[e];
+      if constexpr (WS) wpart[((w - 1) * TY + e) * 64 + lane] = wacc[e];
+    }
+  }
+  __syncthreads();
+  if (w != 0) return false;
+#pragma unroll
+  for (int e = 0; e < TY; ++e)
+#pragma unroll
+    for (int k = 0; k < W - 1; ++k) {
+      acc[e] = cadd(acc[e], part[(k * TY + e) * 64 + lane]);
+      if constexpr (WS) wacc[e] += wpart[(k * TY + e) * 64 + lane];
+    }
+  return true;
+}
+
 // Descriptor of batch entry b, written by nt threads (t: this one's index):
 // its request, integer window offset and
 // subpixel remainder (in double, so n = floor(X + 0.5) is exact for float32

@@ -85,8 +85,8 @@ struct ReqDev {
                             // caller's objective with respect to the loss), or null (1)
   int chain_final;          // the final column pass walks this request's items in kProbeSplit
                             // chains and keeps the probe-gradient sums in registers
-                            // (k_col_final_chain + k_probe_sum) instead of storing h_hat for
-                            // k_probe_grad (set per launch by set_chain_final)
+                            // (k_col_final_chain) instead of storing h_hat (set per launch by
+                            // set_chain_final); k_finish adds either
   const float2* probe;      // [M][N][N] (chain kernels: transformed by their first launch)
 };
 
@@ -160,6 +160,9 @@ struct LaunchCtx {
   float2* cscr;             // ordered object-gradient reduction: per-item contribution scratch
                             // [items][N][N] (the adjoint row pass stores, k_obj_gather adds), or
                             // null (float atomics)
+  int defer;                // the adjoint row pass leaves each position's object-gradient
+                            // contribution in its first mode's checkpoint slot of the slice
+                            // (every slice stored in float), summed by the last launch
   unsigned col_live_blocks; // column blocks a propagation column pass runs (bit q: columns of
                             // block q; 0: all), the union over the launch's requests
   SegOut seg_out;           // recompute with spectral checkpoints: column-pass output slots
@@ -174,12 +177,10 @@ void launch_rows_adj(const LaunchCtx& L, int N, int step, PsiLoad psi, float sca
 void launch_col(const LaunchCtx& L, int N, int op, int step);
 void launch_far_loss(const LaunchCtx& L, int N, int step, bool grad);
 void launch_obj_gather(const LaunchCtx& L, int N, int step, int max_h, int max_w);
-void launch_probe_grad(const LaunchCtx& L, int N, float scale);
 // Marks the requests of L whose final column pass runs as chains (unchunked
 // launches with enough (column block, mode, chain) workgroups to fill the GPU).
 void set_chain_final(LaunchCtx& L, int N, bool unchunked);
 void launch_loss_reduce(const LaunchCtx& L, int N);
-void launch_pos_reduce(const LaunchCtx& L, int N, float scale);
 void launch_plain2d(int N, hipStream_t s, const float2* tw, const float2* src, float2* dst, int n_tiles,
                     bool inverse, float scale, bool accumulate);
 void launch_fill(hipStream_t s, float* p, size_t n, float v);
@@ -242,6 +243,16 @@ void launch_lsq_object(hipStream_t s, float2* O, const float2* g, const float* w
 void launch_lsq_probe(hipStream_t s, float2* P, const float2* g, const float* wp, float* cur, const float* prev,
                       int M, int N2, float delta, double gamma, float beta, double* alpha);
 
+// Last sums of the adjoint (pty_finish.hip): gather: the object gradient of slices lo ..
+// lo + slices - 1 from stored contributions; rest: probe spectrum, loss, positions.
+struct FinishRun {
+  int lo, slices;           // slices of the object-gradient sum
+  const float2* seg;        // as in ChainRun
+  int seg_len, seg_base;
+  int n_reqs, tx, ty;       // (set by the launcher)
+};
+void launch_finish(const LaunchCtx& L, int N, const FinishRun& p, bool gather, bool rest, float scale);
+
 // Chain kernels (pty_chain.hip): every slice of a tile in one launch.
 enum { kForward = 1, kRecompute = 2, kFar = 4, kSeed = 8, kAdjoint = 16, kFirst = 32 };   // see k_chain
 struct ChainRun {
@@ -252,16 +263,9 @@ struct ChainRun {
   float2* seg;              // entry waves of slices that are no multiples of ck_every, or null:
   int seg_len, seg_base;    // slice i at slot i - seg_base of [tiles][seg_len][N][N]
 };
-struct ChainFin {
-  int lo, slices;           // slices of the object-gradient sum
-  const float2* seg;        // as in ChainRun
-  int seg_len, seg_base;
-  int n_reqs, tx, ty;       // (set by the launcher)
-};
 bool chain_size(int N);
 void launch_chain_begin(const LaunchCtx& L, int N);
 void launch_chain(const LaunchCtx& L, int N, const ChainRun& p);
-void launch_chain_finish(const LaunchCtx& L, int N, const ChainFin& p, bool gather, bool rest, float scale);
 void launch_chain_plain_inv(int N, hipStream_t s, const float2* tw, const float2* src, float2* dst, int n, float scale,
                             bool acc);
 

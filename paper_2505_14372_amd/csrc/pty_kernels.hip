@@ -346,7 +346,8 @@ __global__ __launch_bounds__(kThreads) void k_row_adj(const Item* __restrict__ i
                                                       float2* __restrict__ ws, const void* __restrict__ ck_,
                                                       const float2* __restrict__ twg, int step,
                                                       PsiLoad psi, float scale, int item_off,
-                                                      float2* __restrict__ cscr, float* __restrict__ wscr) {
+                                                      float2* __restrict__ cscr, float* __restrict__ wscr,
+                                                      int defer) {
   // items in reverse order (the column passes run them forward; see Launch::col)
   const int by = gridDim.y - 1 - blockIdx.y;
   constexpr int L = Pass<N>::L, E = Pass<N>::E, LINES = Pass<N>::LINES;
@@ -453,9 +454,11 @@ __global__ __launch_bounds__(kThreads) void k_row_adj(const Item* __restrict__ i
   flush();
   if (r.gobj) {
     const float sc = adj_scale(r, scale) * sa;
-    if (cscr) {
-      // ordered reduction: this position's contribution, added in batch order by k_obj_gather
-      float2* dst = cscr + ((size_t)(item_off + by) * N + y) * N;
+    if (cscr || defer) {
+      // this position's contribution, stored for k_obj_gather, or, with defer, for the
+      // last launch, in the rows of the first mode's checkpoint that this workgroup read
+      float2* dst = defer ? const_cast<float2*>(static_cast<const float2*>(ck_)) + (ck_tile(it, r, 0, i / r.ck_every) * N + y) * N
+                          : cscr + ((size_t)(item_off + by) * N + y) * N;
 #pragma unroll
       for (int a = 0; a < E; ++a) dst[l + L * a] = cscale(acc[a], sc);
     } else {
@@ -864,208 +867,51 @@ __global__ void k_loss_reduce(const ReqTable reqs, const float* __restrict__ los
 }
 
 // Ordered object-gradient reduction for slice i = S - 1 - step of every
-// request: one workgroup per TY x 64 tile of the object gradient sums the
-// stored contributions of the positions whose windows cover the tile and adds
-// the sum to the gradient. Each tile has one owner (no atomics) and the
-// summation order is fixed by the batch order and the tile shape alone: the
-// covering positions are listed in batch order (a block-wide ordered
-// compaction over the request's items, 64 W at a time), wave w sums the w-th
-// contiguous part of each list in list order (loads for four positions issued
-// ahead of their additions), and the W wave sums are added in wave order at
-// the end. With WS the stored illumination sums of LSQML (wscr) are added the
-// same way into r.wsum.
-// Tile shape per window size (the same for a request alone or in a group, so
-// both give the same bits): 8 rows and 4 waves; at N = 128, where a scan's
-// object is small for its many positions (a 384 x 384 slice under 1024 windows
-// gives 288 tiles of 8 rows for 256 CUs, each summing about 120 positions),
-// 2 rows and 8 waves: four times the workgroups and twice the waves per list
-// (0.071 -> 0.044 ms per slice, 138.8k -> 142.9k positions/s). Other shapes
-// measured no better at 192 and slower at 256.
-template <int N> struct Gather { static constexpr int TY = 8, W = 4; };
-template <> struct Gather<128> { static constexpr int TY = 2, W = 8; };
+// request, where the contributions of a slice wait in the scratch area (half
+// checkpoints, recomputed segments, LSQML): one workgroup per 4 x 64 tile of the
+// slice adds their sum (object_sum) to the gradient, and with WS that of the
+// stored illuminations (wscr) to r.wsum.
+constexpr int kGatherTY = 4;
 template <int N, bool WS>
-__global__ __launch_bounds__(64 * Gather<N>::W) void k_obj_gather(const Item* __restrict__ items, const ReqTable reqs,
-                                                              const float2* __restrict__ cscr,
-                                                              const float* __restrict__ wscr, int step,
-                                                              int item_off, int n_items) {
-  constexpr int kGatherTY = Gather<N>::TY, kGatherW = Gather<N>::W;
+__global__ __launch_bounds__(512) void k_obj_gather(const Item* __restrict__ items, const ReqTable reqs,
+                                                    const float2* __restrict__ cscr, const float* __restrict__ wscr,
+                                                    int step, int item_off, int n_items) {
   const ReqDev& r = reqs.r[blockIdx.z];
   const int i = r.S - 1 - step;
-  const int x0 = blockIdx.x * 64, y0 = blockIdx.y * kGatherTY;
+  const int x0 = blockIdx.x * 64, y0 = blockIdx.y * kGatherTY, x = x0 + (threadIdx.x & 63);
   if (i < 0 || !r.gobj || x0 >= r.W || y0 >= r.H) return;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, x = x0 + lane;
   const int lo = max(r.item0, item_off), hi = min(r.item0 + r.n_items, item_off + n_items);
-  __shared__ int list[64 * kGatherW];
-  __shared__ int wcnt[kGatherW];
-  __shared__ float2 part[kGatherW - 1][kGatherTY][64];
-  __shared__ float wpart[WS ? kGatherW - 1 : 1][kGatherTY][64];
+  __shared__ float2 part[7 * kGatherTY * 64];
+  __shared__ float wpart[WS ? 7 * kGatherTY * 64 : 1];
   float2 acc[kGatherTY];
   float wacc[kGatherTY];
+  if (!object_sum<N, kGatherTY, WS>(items, r.item0, lo, hi, y0, x0, cscr, wscr, (size_t)N * N, 1,
+                                    [](int b, const Item&) { return b; }, acc, wacc, part, wpart) ||
+      x >= r.W)
+    return;
 #pragma unroll
-  for (int t = 0; t < kGatherTY; ++t) {
-    acc[t] = make_float2(0.f, 0.f);
-    wacc[t] = 0.f;
-  }
-  // contribution of position bj to row y0 + t of this thread's column (zero
-  // outside its window), and with WS its illumination
-  auto fetch = [&](int bj, float2 (&v)[kGatherTY], float (&w)[kGatherTY]) {
-    const Item it = items[bj];
-    const int wx = x - it.nx;
-    const float2* src = cscr + (size_t)bj * N * N;
-    const float* wsrc = WS ? wscr + (size_t)bj * N * N : nullptr;
-#pragma unroll
-    for (int t = 0; t < kGatherTY; ++t) {
-      const int wy = y0 + t - it.ny;
-      const bool in = wy >= 0 && wy < N && wx >= 0 && wx < N;
-      v[t] = in ? src[wy * N + wx] : make_float2(0.f, 0.f);
-      if constexpr (WS) w[t] = in ? wsrc[wy * N + wx] : 0.f;
-    }
-  };
-  int total = 0;
-  for (int b0 = lo; b0 < hi; b0 += 64 * kGatherW) {
-    const int b = b0 + (int)threadIdx.x;
-    bool hit = false;
-    if (b < hi) {
-      const Item it = items[b];
-      hit = it.valid && it.ny < y0 + kGatherTY && it.ny + N > y0 && it.nx < x0 + 64 && it.nx + N > x0;
-    }
-    const unsigned long long m = __ballot(hit);
-    if (lane == 0) wcnt[w] = __popcll(m);
-    __syncthreads();
-    int off = 0, cnt = 0;
-#pragma unroll
-    for (int q = 0; q < kGatherW; ++q) {
-      off += q < w ? wcnt[q] : 0;
-      cnt += wcnt[q];
-    }
-    if (hit) list[off + __popcll(m & ((1ull << lane) - 1ull))] = b;
-    __syncthreads();
-    total += cnt;
-    const int per = (cnt + kGatherW - 1) / kGatherW;
-    const int beg = min(w * per, cnt), end = min(beg + per, cnt);
-    int k = beg;
-    for (; k + 4 <= end; k += 4) {
-      float2 v0[kGatherTY], v1[kGatherTY], v2[kGatherTY], v3[kGatherTY];
-      float w0[kGatherTY], w1[kGatherTY], w2[kGatherTY], w3[kGatherTY];
-      fetch(__builtin_amdgcn_readfirstlane(list[k]), v0, w0);
-      fetch(__builtin_amdgcn_readfirstlane(list[k + 1]), v1, w1);
-      fetch(__builtin_amdgcn_readfirstlane(list[k + 2]), v2, w2);
-      fetch(__builtin_amdgcn_readfirstlane(list[k + 3]), v3, w3);
-#pragma unroll
-      for (int t = 0; t < kGatherTY; ++t) {
-        acc[t] = cadd(cadd(cadd(cadd(acc[t], v0[t]), v1[t]), v2[t]), v3[t]);
-        if constexpr (WS) wacc[t] = (((wacc[t] + w0[t]) + w1[t]) + w2[t]) + w3[t];
-      }
-    }
-    for (; k < end; ++k) {
-      float2 v0[kGatherTY];
-      float w0[kGatherTY];
-      fetch(__builtin_amdgcn_readfirstlane(list[k]), v0, w0);
-#pragma unroll
-      for (int t = 0; t < kGatherTY; ++t) {
-        acc[t] = cadd(acc[t], v0[t]);
-        if constexpr (WS) wacc[t] += w0[t];
-      }
-    }
-    __syncthreads();   // the list is rebuilt for the next items
-  }
-  if (total == 0) return;
-  if (w > 0) {
-#pragma unroll
-    for (int t = 0; t < kGatherTY; ++t) {
-      part[w - 1][t][lane] = acc[t];
-      if constexpr (WS) wpart[w - 1][t][lane] = wacc[t];
-    }
-  }
-  __syncthreads();
-  if (w != 0 || x >= r.W) return;
-  float2* g = r.gobj + (size_t)i * r.H * r.W;
-#pragma unroll
-  for (int t = 0; t < kGatherTY; ++t) {
-    float2 s = acc[t];
-#pragma unroll
-    for (int q = 1; q < kGatherW; ++q) s = cadd(s, part[q - 1][t][lane]);
-    const int y = y0 + t;
-    if (y < r.H) g[(size_t)y * r.W + x] = cadd(g[(size_t)y * r.W + x], s);
-  }
-  if constexpr (WS) {
-    if (!r.wsum) return;
-    float* ws = r.wsum + (size_t)i * r.H * r.W;
-#pragma unroll
-    for (int t = 0; t < kGatherTY; ++t) {
-      float s = wacc[t];
-#pragma unroll
-      for (int q = 1; q < kGatherW; ++q) s += wpart[q - 1][t][lane];
-      const int y = y0 + t;
-      if (y < r.H) ws[(size_t)y * r.W + x] += s;
+  for (int e = 0; e < kGatherTY; ++e) {
+    const int y = y0 + e;
+    if (y >= r.H) continue;
+    const size_t at = ((size_t)i * r.H + y) * r.W + x;
+    r.gobj[at] = cadd(r.gobj[at], acc[e]);
+    if constexpr (WS) {
+      if (r.wsum) r.wsum[at] += wacc[e];
     }
   }
 }
 
 constexpr int kProbeSplit = 16;
-// Probe-spectrum gradient per request: gphat_m(u) = scale * sum_b h_hat_{b,m}(u) conj(R_b(u)).
-// A workgroup of PIX x SPLIT threads covers PIX consecutive pixels; thread
-// row s sums the items b = item0 + s, s + SPLIT, ... and the rows are added
-// in a fixed order (deterministic for a given launch shape).
-template <int N, int PIX, int SPLIT>
-__global__ __launch_bounds__(PIX * SPLIT) void k_probe_grad(const Item* __restrict__ items, const ReqTable reqs,
-                                                            const float2* __restrict__ ws,
-                                                            const float2* __restrict__ ramps, float scale) {
-  const ReqDev& r = reqs.r[blockIdx.z];
-  const int m = blockIdx.y;
-  if (m >= r.M || !r.gphat || r.chain_final) return;
-  constexpr int split = SPLIT, pix = PIX;
-  const int px = threadIdx.x % pix, s = threadIdx.x / pix;
-  const int p = blockIdx.x * pix + px;
-  const int uy = p / N, ux = p % N;
-  auto term = [&](int b) {
-    const Item it = items[b];
-    if (!it.valid) return make_float2(0.f, 0.f);
-    float2 R = cmul(ramps[(size_t)b * 2 * N + uy], ramps[(size_t)b * 2 * N + N + ux]);
-    float2 h = ws[(size_t)(it.tile0 + m) * N * N + p];
-    return cmul(h, cconj(R));
-  };
-  if constexpr (SPLIT == 1) {
-    // the same summation order as the split form: kProbeSplit interleaved
-    // partial sums over the request's items, added in order (so a request's
-    // gradient has the same bits whichever form its launch uses)
-    float2 part[kProbeSplit];
-#pragma unroll
-    for (int q = 0; q < kProbeSplit; ++q) part[q] = make_float2(0.f, 0.f);
-    for (int b0 = 0; b0 < r.n_items; b0 += kProbeSplit) {
-#pragma unroll
-      for (int q = 0; q < kProbeSplit; ++q)
-        if (b0 + q < r.n_items) part[q] = cadd(part[q], term(r.item0 + b0 + q));
-    }
-    float2 t = part[0];
-#pragma unroll
-    for (int q = 1; q < kProbeSplit; ++q) t = cadd(t, part[q]);
-    r.gphat[(size_t)m * N * N + p] = cscale(t, adj_scale(r, scale));
-  } else {
-    static_assert(SPLIT == kProbeSplit, "the split form takes kProbeSplit interleaved partial sums");
-    float2 acc = make_float2(0.f, 0.f);
-    for (int b = r.item0 + s; b < r.item0 + r.n_items; b += split) acc = cadd(acc, term(b));
-    __shared__ float2 red[PIX * SPLIT];
-    red[s * pix + px] = acc;
-    __syncthreads();
-    if (s == 0) {
-      float2 t = red[px];
-      for (int q = 1; q < split; ++q) t = cadd(t, red[q * pix + px]);
-      r.gphat[(size_t)m * N * N + p] = cscale(t, adj_scale(r, scale));
-    }
-  }
-}
-
 // Final column pass and probe-gradient sums in one, for the requests marked
 // chain_final. Workgroup (column block, mode, chain), chain = request r and
 // residue q < kProbeSplit, walks the request's items q, q + kProbeSplit, ...
 // in order: for each it forms h_hat = DFT_y(tile) / N and the block's
 // position-gradient partials exactly as COL_FINAL does, and adds
-// h_hat conj(R_b) into a sum held in registers. These are k_probe_grad's
+// h_hat conj(R_b) into a sum held in registers. These are k_finish's
 // kProbeSplit interleaved sums, added in the same order, so no h_hat tile is
 // stored and read back: the chain's sum is stored once, into the column block
 // of its first item's tile (that item's work tile is free by then, and no
-// other workgroup touches that block), where k_probe_sum adds the chains.
+// other workgroup touches that block), where k_finish adds the chains.
 template <int N>
 __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col_final_chain(const Item* __restrict__ items,
                                                                  const ReqTable reqs, float2* __restrict__ ws,
@@ -1097,7 +943,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col_final_chain(const I
   for (int b = r.item0 + q; b < r.item0 + r.n_items; b += kProbeSplit) {
     const Item it = items[b];
     if (!it.valid) {
-      // k_probe_grad adds a zero term for a window outside the object
+      // (a window outside the object adds a zero term)
 #pragma unroll
       for (int a = 0; a < E; ++a) acc[a] = cadd(acc[a], make_float2(0.f, 0.f));
       continue;
@@ -1141,57 +987,6 @@ __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col_final_chain(const I
   float2* dst = ws + (size_t)(items[r.item0 + q].tile0 + m) * N * N;
 #pragma unroll
   for (int a = 0; a < E; ++a) dst[(size_t)(l + L * a) * N + ux] = acc[a];
-}
-
-// Probe-spectrum gradient of the chain_final requests: the kProbeSplit chain
-// sums (zero for a residue with no item) added in residue order, as k_probe_grad
-// adds its interleaved sums, times the adjoint scale.
-template <int N>
-__global__ __launch_bounds__(256) void k_probe_sum(const Item* __restrict__ items, const ReqTable reqs,
-                                                   const float2* __restrict__ ws, float scale) {
-  const ReqDev& r = reqs.r[blockIdx.z];
-  const int m = blockIdx.y;
-  if (!r.chain_final || m >= r.M || !r.gphat) return;
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  float2 t = make_float2(0.f, 0.f);
-#pragma unroll
-  for (int q = 0; q < kProbeSplit; ++q) {
-    const float2 part = q < r.n_items ? ws[(size_t)(items[r.item0 + q].tile0 + m) * N * N + p]
-                                      : make_float2(0.f, 0.f);
-    t = q == 0 ? part : cadd(t, part);
-  }
-  r.gphat[(size_t)m * N * N + p] = cscale(t, adj_scale(r, scale));
-}
-
-// Per item: dL/dX = 2 pi * scale * sum over modes and blocks of the partials;
-// written to g_pos[local] (per batch entry) and/or added to a dense [J][2] gradient.
-__global__ void k_pos_reduce(const Item* __restrict__ items, const ReqTable reqs,
-                             const float* __restrict__ pos_part, int nblk, int n_items, float scale) {
-  int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= n_items) return;
-  const Item it = items[b];
-  const ReqDev& r = reqs.r[it.req];
-  float g0 = 0.f, g1 = 0.f;
-  if (it.valid) {
-    for (int m = 0; m < r.M; ++m)
-      for (int k = 0; k < nblk; ++k) {
-        const float* p = pos_part + ((size_t)(it.tile0 + m) * nblk + k) * 2;
-        g0 += p[0];
-        g1 += p[1];
-      }
-  }
-  const float f = 6.283185307179586f * adj_scale(r, scale);
-  g0 *= f;
-  g1 *= f;
-  int local = b - r.item0;
-  if (r.gpos) {
-    if (r.accumulate) { r.gpos[2 * local] += g0; r.gpos[2 * local + 1] += g1; }
-    else { r.gpos[2 * local] = g0; r.gpos[2 * local + 1] = g1; }
-  }
-  if (r.gpos_dense && it.valid) {
-    atomicAdd(r.gpos_dense + 2 * it.j, g0);
-    atomicAdd(r.gpos_dense + 2 * it.j + 1, g1);
-  }
 }
 
 // ============================================================ elementwise
@@ -1287,20 +1082,20 @@ struct Launch {
     dim3 g(Pass<N>::NBLK, L.n_items);
     if (psi.spec) {
       if (L.wsum)
-        hipLaunchKernelGGL((k_row_adj<N, false, true, true>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, psi, scale, L.item_off, L.cscr, L.wscr);
+        hipLaunchKernelGGL((k_row_adj<N, false, true, true>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, psi, scale, L.item_off, L.cscr, L.wscr, L.defer);
       else
-        hipLaunchKernelGGL((k_row_adj<N, false, false, true>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, psi, scale, L.item_off, L.cscr, L.wscr);
+        hipLaunchKernelGGL((k_row_adj<N, false, false, true>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, psi, scale, L.item_off, L.cscr, L.wscr, L.defer);
       return;
     }
     if (L.wsum) {
       if (L.ck_half)
-        hipLaunchKernelGGL((k_row_adj<N, true, true>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, psi, scale, L.item_off, L.cscr, L.wscr);
+        hipLaunchKernelGGL((k_row_adj<N, true, true>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, psi, scale, L.item_off, L.cscr, L.wscr, L.defer);
       else
-        hipLaunchKernelGGL((k_row_adj<N, false, true>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, psi, scale, L.item_off, L.cscr, L.wscr);
+        hipLaunchKernelGGL((k_row_adj<N, false, true>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, psi, scale, L.item_off, L.cscr, L.wscr, L.defer);
     } else if (L.ck_half) {
-      hipLaunchKernelGGL((k_row_adj<N, true>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, psi, scale, L.item_off, L.cscr, L.wscr);
+      hipLaunchKernelGGL((k_row_adj<N, true>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, psi, scale, L.item_off, L.cscr, L.wscr, L.defer);
     } else {
-      hipLaunchKernelGGL((k_row_adj<N, false>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, psi, scale, L.item_off, L.cscr, L.wscr);
+      hipLaunchKernelGGL((k_row_adj<N, false>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, psi, scale, L.item_off, L.cscr, L.wscr, L.defer);
     }
   }
   static void col(const LaunchCtx& L, int op, int step) {
@@ -1335,13 +1130,12 @@ struct Launch {
     }
   }
   static void obj_gather(const LaunchCtx& L, int step, int max_h, int max_w) {
-    constexpr int TY = Gather<N>::TY, W = Gather<N>::W;
-    dim3 g((max_w + 63) / 64, (max_h + TY - 1) / TY, L.n_reqs);
+    dim3 g((max_w + 63) / 64, (max_h + kGatherTY - 1) / kGatherTY, L.n_reqs);
     if (L.wsum && L.wscr)
-      hipLaunchKernelGGL((k_obj_gather<N, true>), g, dim3(64 * W), 0, L.stream, L.items, L.reqs, L.cscr,
+      hipLaunchKernelGGL((k_obj_gather<N, true>), g, dim3(512), 0, L.stream, L.items, L.reqs, L.cscr,
                          L.wscr, step, L.item_off, L.n_items);
     else
-      hipLaunchKernelGGL((k_obj_gather<N, false>), g, dim3(64 * W), 0, L.stream, L.items, L.reqs, L.cscr,
+      hipLaunchKernelGGL((k_obj_gather<N, false>), g, dim3(512), 0, L.stream, L.items, L.reqs, L.cscr,
                          nullptr, step, L.item_off, L.n_items);
   }
   static void far_loss(const LaunchCtx& L, int step, bool grad) {
@@ -1350,24 +1144,6 @@ struct Launch {
       hipLaunchKernelGGL((k_far_loss<N, true>), g, dim3(ColPass<N>::THREADS), 0, L.stream, L.items, L.reqs, L.ws, L.tw, step, L.loss_part, L.flags, L.item_off);
     else
       hipLaunchKernelGGL((k_far_loss<N, false>), g, dim3(ColPass<N>::THREADS), 0, L.stream, L.items, L.reqs, L.ws, L.tw, step, L.loss_part, L.flags, L.item_off);
-  }
-  static void probe_grad(const LaunchCtx& L, float scale) {
-    // many (pixel block, mode) pairs: 256 pixels per workgroup, every thread
-    // walks all items; few: 64 pixels per workgroup and the items split 16 ways
-    static_assert((N * N) % 256 == 0, "pixel blocks must tile the probe");
-    bool any_chain = false, any_plain = false;
-    for (int q = 0; q < L.n_reqs; ++q) (L.reqs.r[q].chain_final ? any_chain : any_plain) = true;
-    if (any_chain)
-      hipLaunchKernelGGL((k_probe_sum<N>), dim3(N * N / 256, L.max_modes, L.n_reqs), dim3(256), 0, L.stream,
-                         L.items, L.reqs, L.ws, scale);
-    if (!any_plain) return;
-    const bool small = (N * N / 256) * L.max_modes * L.n_reqs < 1024;
-    if (small)
-      hipLaunchKernelGGL((k_probe_grad<N, 64, kProbeSplit>), dim3(N * N / 64, L.max_modes, L.n_reqs), dim3(1024), 0, L.stream,
-                         L.items, L.reqs, L.ws, L.ramps, scale);
-    else
-      hipLaunchKernelGGL((k_probe_grad<N, 256, 1>), dim3(N * N / 256, L.max_modes, L.n_reqs), dim3(256), 0, L.stream,
-                         L.items, L.reqs, L.ws, L.ramps, scale);
   }
   static void plain2d(hipStream_t s, const float2* tw, const float2* src, float2* dst, int n_tiles, bool inverse,
                       float scale, bool accumulate) {
@@ -1409,7 +1185,6 @@ void launch_obj_gather(const LaunchCtx& L, int N, int step, int max_h, int max_w
   PTY_DISPATCH(N, obj_gather(L, step, max_h, max_w));
 }
 void launch_far_loss(const LaunchCtx& L, int N, int step, bool grad) { PTY_DISPATCH(N, far_loss(L, step, grad)); }
-void launch_probe_grad(const LaunchCtx& L, int N, float scale) { PTY_DISPATCH(N, probe_grad(L, scale)); }
 void set_chain_final(LaunchCtx& L, int N, bool unchunked) {
   // Chains where they measured faster: N = 256 (16 values per lane; at 24 per
   // lane, N = 192, the chain kernel runs one wave per SIMD and loses) with
@@ -1427,10 +1202,6 @@ void launch_plain2d(int N, hipStream_t s, const float2* tw, const float2* src, f
 void launch_loss_reduce(const LaunchCtx& L, int N) {
   hipLaunchKernelGGL(k_loss_reduce, dim3(L.n_reqs), dim3(kThreads), 0, L.stream, L.reqs, L.loss_part,
                      col_blocks(N));
-}
-void launch_pos_reduce(const LaunchCtx& L, int N, float scale) {
-  hipLaunchKernelGGL(k_pos_reduce, dim3((L.n_items + 127) / 128), dim3(128), 0, L.stream, L.items, L.reqs,
-                     L.pos_part, col_blocks(N), L.n_items, scale);
 }
 void launch_fill(hipStream_t s, float* p, size_t n, float v) {
   if (n == 0) return;
