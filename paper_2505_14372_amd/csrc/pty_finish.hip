@@ -74,7 +74,7 @@ __global__ __launch_bounds__(512) void k_finish(const Item* __restrict__ items, 
     const int m = (g / (N * N / 32)) % max_modes;
     if (m >= r.M || !r.gphat) return;
     const int px = (g % (N * N / 32)) * 32 + (t & 31), s = t >> 5;
-    const int ux = CHAIN ? px / N : px % N, uy = CHAIN ? px % N : px / N;
+    const int ux = CHAIN ? px / N : mem_column<N>(px % N), uy = CHAIN ? px % N : px / N;
     float2 acc = make_float2(0.f, 0.f);
     if (!CHAIN && r.chain_final) {
       if (s < r.n_items) acc = ws[(size_t)(items[r.item0 + s].tile0 + m) * N * N + px];
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(512) void k_finish(const Item* __restrict__ items, 
       float2 z = part[t];
 #pragma unroll
       for (int k = 1; k < kProbeSplit; ++k) z = cadd(z, part[32 * k + t]);
-      r.gphat[(size_t)m * N * N + px] = cscale(z, adj_scale(r, scale));
+      r.gphat[(size_t)m * N * N + (CHAIN ? px : uy * N + ux)] = cscale(z, adj_scale(r, scale));
     }
     return;
   }

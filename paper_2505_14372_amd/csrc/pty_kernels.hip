@@ -2,7 +2,8 @@
 // noise-model loss and exact adjoint of arXiv 2505.14372 (Sec. 3 - 3.2).
 //
 // Data layout (all row-major, complex = float2):
-//   workspace tile (item b, mode m):  ws[(tile0(b) + m) * N*N + y*N + x]
+//   workspace tile (item b, mode m):  ws[(tile0(b) + m) * N*N + y*N + x], where a row spectrum
+//                                     has its columns in the order of mem_column
 //   object slice i:                   obj[(i*H + y)*W + x]
 //   propagator for the gap after slice i (already divided by N^2):
 //                                     prop[i*N*N + u_y*N + u_x]
@@ -93,27 +94,45 @@ __device__ __forceinline__ bool col_live(const ReqDev& r, int x) {
   return r.live[x] != 0;
 }
 
-// Does one row-pass slot (L lanes x 8 bytes of a row) cover whole 128-byte
-// lines (L = 16, N = 256)? Only then are read-once rows loaded non-temporally:
-// with L = 8 an instruction reads half of each line and the next slot the
-// other half, which a non-temporal load does not keep, so every line would be
-// fetched twice. The store forms that write whole lines at the band edges
-// (whole slots in the adjoint row pass, whole column blocks in the
-// propagation passes) are used at that size too.
+// Does a store of a partly live column block write it whole? At N = 256 the
+// propagation passes do, so that the lines at the band edges are written whole.
 template <int N>
 struct WholeLines {
   static constexpr bool on = Cfg<N>::L * sizeof(float2) >= 128;
 };
-template <int N, bool NT>
-struct RowNT {
-  static constexpr bool on = NT && WholeLines<N>::on;
-};
 
-// Row-pass load of x[l + L a] for the register slots a set in `mask`, zero in
-// the others. A masked slot loads the lane's slot-0 element of the same row
-// instead (a line the wave reads anyway), so the loads are unconditional: no
-// per-slot branch, and the compiler may issue them together.
-// (NT: non-temporal loads, for rows read once; see RowNT.)
+// Row-pass accesses of a row spectrum. A step is one access of a lane: register
+// a (16 lanes, 8 bytes each) or, where the columns are stored in pairs (see
+// row_pairs), registers 2 c and 2 c + 1 (8 lanes, 16 bytes each); either way the
+// lanes of a row cover a whole 128-byte line, which a non-temporal load (NT, for
+// rows read once) needs: of a line read in two halves it would not keep the
+// second one.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+template <int N> struct RowSteps {
+  static constexpr int W = row_pairs<N>() ? 2 : 1;        // registers of a step
+  static constexpr int COUNT = Cfg<N>::E / W;
+  static constexpr unsigned BITS = W == 2 ? 3u : 1u;      // their bits in a slot mask
+};
+// the values of one step, index i of the row counted in steps (i = l: the first)
+template <int N, bool NT>
+__device__ __forceinline__ void load_step(float2 (&t)[RowSteps<N>::W], const float2* row, int i) {
+  if constexpr (row_pairs<N>()) {
+    const f32x4* p = reinterpret_cast<const f32x4*>(row) + i;
+    const f32x4 q = NT ? __builtin_nontemporal_load(p) : *p;
+    t[0] = make_float2(q.x, q.y);
+    t[1] = make_float2(q.z, q.w);
+  } else if constexpr (NT) {
+    const float2* p = row + i;
+    t[0] = make_float2(__builtin_nontemporal_load(&p->x), __builtin_nontemporal_load(&p->y));
+  } else {
+    t[0] = row[i];
+  }
+}
+
+// Row-pass load of the register slots a set in `mask`, zero in the others, of the
+// adjoint row pass at N = 256. A masked slot loads the lane's slot-0 element of
+// the same row instead (a line the wave reads anyway), so the loads are
+// unconditional: no branch, and the compiler may issue them together.
 template <int N, bool NT = false>
 __device__ __forceinline__ void load_row_masked(float2 (&v)[Cfg<N>::E], const float2* row, int l, unsigned mask) {
   constexpr int L = Cfg<N>::L, E = Cfg<N>::E;
@@ -121,7 +140,7 @@ __device__ __forceinline__ void load_row_masked(float2 (&v)[Cfg<N>::E], const fl
   for (int a = 0; a < E; ++a) {
     const bool on = (mask >> a) & 1u;
     float2 t;
-    if constexpr (RowNT<N, NT>::on) {
+    if constexpr (NT) {
       const float2* p = row + (on ? l + L * a : l);
       t = make_float2(__builtin_nontemporal_load(&p->x), __builtin_nontemporal_load(&p->y));
     } else {
@@ -141,45 +160,54 @@ __device__ __forceinline__ unsigned wave_slots(unsigned mask) {
   return __builtin_amdgcn_readfirstlane(mask);
 }
 
-// Row-pass load of x[l + L a] for the register slots a set in `mask`, zero in
-// the others. `any` (wave_slots(mask)) is uniform, so a slot no lane of the
-// wave needs is skipped by a scalar branch and costs no request; the other
-// slots are read by every lane from one base address with immediate offsets
-// (no per-slot address registers), and the lanes whose slot is dead take zero.
+// Row-pass load of the register slots a set in `mask`, zero in the others. `any`
+// (wave_slots(mask)) is uniform, so a step no lane of the wave needs is skipped
+// by a scalar branch and costs no request; the other steps are read by every
+// lane from one base address with immediate offsets (no per-slot address
+// registers), and the lanes whose slot is dead take zero.
 // A dead column of a tile holds whatever was last written there (stale data,
 // or a value a pass stored only to write its line whole), so what a dead lane
 // reads is discarded, never used.
-// (NT: non-temporal loads, for rows read once; see RowNT.)
 template <int N, bool NT = false>
 __device__ __forceinline__ void load_row_slots(float2 (&v)[Cfg<N>::E], const float2* row, int l, unsigned mask,
                                                unsigned any) {
-  constexpr int L = Cfg<N>::L, E = Cfg<N>::E;
-  const float2* p = row + l;
+  constexpr int E = Cfg<N>::E, W = RowSteps<N>::W;
+  // (both slots of a pair are loaded if one is needed)
+  const unsigned got = W == 2 ? any | ((any & 0x555555u) << 1) | ((any & 0xaaaaaau) >> 1) : any;
+  const float2* p = row + W * l;
 #pragma unroll
-  for (int a = 0; a < E; ++a) {
-    v[a] = make_float2(0.f, 0.f);
-    if ((any >> a) & 1u) {
-      if constexpr (RowNT<N, NT>::on)
-        v[a] = make_float2(__builtin_nontemporal_load(&p[L * a].x), __builtin_nontemporal_load(&p[L * a].y));
-      else v[a] = p[L * a];
-    }
+  for (int c = 0; c < RowSteps<N>::COUNT; ++c) {
+    float2 t[W];
+#pragma unroll
+    for (int k = 0; k < W; ++k) t[k] = make_float2(0.f, 0.f);
+    if ((got >> (W * c)) & 1u) load_step<N, NT>(t, p, Cfg<N>::L * c);
+#pragma unroll
+    for (int k = 0; k < W; ++k) v[W * c + k] = t[k];
   }
-  const unsigned part = any & ~mask;
+  const unsigned part = got & ~mask;
 #pragma unroll
   for (int a = 0; a < E; ++a)
     if ((part >> a) & 1u) v[a] = make_float2(0.f, 0.f);
 }
 
-// Row-pass store of the slots set in `any` (wave-uniform): every lane of a
-// live slot stores, also a lane whose column is dead, since no consumer reads
-// dead columns.
+// Row-pass store of the steps with a slot set in `any` (wave-uniform): every
+// lane stores, also one whose column is dead, since no consumer reads dead
+// columns, so lines are written whole (against exact stores 1.070 -> 1.046 ms per
+// adjoint launch at N = 256, 8 modes, 512 positions).
 template <int N>
 __device__ __forceinline__ void store_row_slots(const float2 (&v)[Cfg<N>::E], float2* row, int l, unsigned any) {
-  constexpr int L = Cfg<N>::L, E = Cfg<N>::E;
-  float2* p = row + l;
+  constexpr int L = Cfg<N>::L, W = RowSteps<N>::W;
+  float2* p = row + W * l;
 #pragma unroll
-  for (int a = 0; a < E; ++a)
-    if ((any >> a) & 1u) p[L * a] = v[a];
+  for (int c = 0; c < RowSteps<N>::COUNT; ++c)
+    if ((any >> (W * c)) & RowSteps<N>::BITS) {
+      if constexpr (row_pairs<N>()) {
+        const f32x4 t = {v[2 * c].x, v[2 * c].y, v[2 * c + 1].x, v[2 * c + 1].y};
+        reinterpret_cast<f32x4*>(p)[L * c] = t;
+      } else {
+        p[L * c] = v[c];
+      }
+    }
 }
 
 // byte offset of element (y, x) of an N x N tile, or kOff when the lane is masked off
@@ -359,7 +387,7 @@ __global__ __launch_bounds__(kThreads) void k_row_adj(const Item* __restrict__ i
   if (!it.valid || i < 0) return;
   load_twiddles<N>(tw, twg);
   __syncthreads();
-  const int l = threadIdx.x % L, line = threadIdx.x / L;
+  const int l0 = threadIdx.x % L, l = l0, line = threadIdx.x / L;
   const int y = blockIdx.x * LINES + line;
   float2* sx = xch + line * Xch<N>::ROW_STRIDE;
   using CT = typename Ck<HALF>::T;
@@ -378,13 +406,8 @@ __global__ __launch_bounds__(kThreads) void k_row_adj(const Item* __restrict__ i
   const unsigned gmask = (r.live && i < r.S - 1) ? live : ~0u;
   const unsigned cmask = (r.live && i >= 1) ? live : ~0u;
   // the output of slices i >= 1 feeds only the adjoint propagation column
-  // pass, which reads the live columns alone (slice 0 feeds the final one).
-  // Where a slot is a whole line (N = 256) every lane of a slot with a live
-  // column stores, as in the forward row pass: whole-line writes beat partial
-  // ones at the band edges (1.070 -> 1.046 ms per launch at 8 modes, 512
-  // positions); at 8 lanes per line only the live lanes store.
-  const unsigned omask = cmask;
-  const unsigned any_o = WholeLines<N>::on ? wave_slots<N>(omask) : omask;
+  // pass, which reads the live columns alone (slice 0 feeds the final one)
+  const unsigned any_o = wave_slots<N>(cmask), any_g = wave_slots<N>(gmask);
   float2 acc[E];
   const size_t orow = ((size_t)i * r.H + it.ny + y) * r.W + it.nx;
   // ePIE: object step divided by max sum_m |psi_i|^2, wave step by max |O_i|^2
@@ -415,12 +438,21 @@ __global__ __launch_bounds__(kThreads) void k_row_adj(const Item* __restrict__ i
   float2* out_row = nullptr;
   auto flush = [&]() {
     if (!out_row) return;
+    if constexpr (row_pairs<N>()) {
+      store_row_slots<N>(hout, out_row, l, any_o);
+    } else {
 #pragma unroll
-    for (int a = 0; a < E; ++a)
-      if ((any_o >> a) & 1u) out_row[l + L * a] = hout[a];
+      for (int a = 0; a < E; ++a)
+        if ((any_o >> a) & 1u) out_row[l + L * a] = hout[a];
+    }
     out_row = nullptr;
   };
   for (int m = 0; m < r.M; ++m) {
+    // where the 16-byte accesses are used the lane index is opaque in each mode: else the
+    // twiddles of all three transforms are held in registers across the modes, and with the
+    // accesses' register quads N = 192 needs 282 registers (one wave per SIMD) instead of 241
+    int l = l0;
+    if constexpr (row_pairs<N>()) asm volatile("" : "+v"(l));
     float2* trow = ws + ((size_t)(it.tile0 + m) * N + y) * N;
     const CT* prow;
     if (psi.from_seg) prow = static_cast<const CT*>(psi.seg) + (((size_t)(it.tile0 + m) * psi.seg_len + (i - psi.seg_base)) * N + y) * N;
@@ -429,10 +461,15 @@ __global__ __launch_bounds__(kThreads) void k_row_adj(const Item* __restrict__ i
     // would otherwise hold the second request back by a whole memory latency)
     float2 v[E];
     float2 ps[SPEC ? E : 1];
-    load_row_masked<N>(v, trow, l, gmask);
     // the checkpoint row is read once: non-temporal, so that the gradient
     // tiles the adjoint column pass reads next stay in the caches
-    if constexpr (SPEC) load_row_masked<N, true>(ps, reinterpret_cast<const float2*>(prow), l, cmask);
+    if constexpr (row_pairs<N>()) {
+      load_row_slots<N>(v, trow, l, gmask, any_g);
+      if constexpr (SPEC) load_row_slots<N, true>(ps, reinterpret_cast<const float2*>(prow), l, cmask, any_o);
+    } else {
+      load_row_masked<N>(v, trow, l, gmask);
+      if constexpr (SPEC) load_row_masked<N, true>(ps, reinterpret_cast<const float2*>(prow), l, cmask);
+    }
     flush();
     line_fft<N, true>(v, l, tw, sx, WaveSync{});
     if constexpr (SPEC) line_fft<N, true>(ps, l, tw, sx, WaveSync{});
@@ -592,7 +629,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col(const Item* __restr
     }
   }
   const int c = ColMap<N>::col(), l = ColMap<N>::lane(), t = threadIdx.x;
-  const int ux = cb * CB + c;
+  const int mx = cb * CB + c, ux = mem_column<N>(mx);   // position in a tile row, column
   float2* sx = xch + c * ColMap<N>::STRIDE;
   float2* tile = ws + (size_t)(it.tile0 + m) * N * N;
   // a forward propagation whose output is a stored checkpoint runs in place
@@ -618,7 +655,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col(const Item* __restr
   if constexpr (OP != COL_SHIFT) {
     const TileBuf tb(tile, N * N * 8);
 #pragma unroll
-    for (int a = 0; a < E; ++a) v[a] = tb.ld(tile_off<N>(live_col, l + L * a, ux));
+    for (int a = 0; a < E; ++a) v[a] = tb.ld(tile_off<N>(live_col, l + L * a, mx));
   }
   if (t < N) {
     tw[t] = tw_t;
@@ -715,7 +752,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col(const Item* __restr
   // block is dead there), and only the live columns are stored.
   const bool st_col = (PROP && WholeLines<N>::on) ? true : live_col;
 #pragma unroll
-  for (int a = 0; a < E; ++a) out.st(tile_off<N>(st_col, l + L * a, ux), v[a]);
+  for (int a = 0; a < E; ++a) out.st(tile_off<N>(st_col, l + L * a, mx), v[a]);
 }
 
 // Plain column DFT of M probe-sized tiles (in place): tile = scale * DFT_y(tile).
@@ -764,7 +801,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS, N == 256 ? 4 : 1) void k_far_l
   const ReqDev& r = reqs.r[it.req];
   if (step != r.S - 1) return;
   const int c = ColMap<N>::col(), l = ColMap<N>::lane();
-  const int ux = blockIdx.x * CB + c;
+  const int mx = blockIdx.x * CB + c, ux = mem_column<N>(mx);   // position in a tile row, column
   if (!it.valid) {
     if (r.I_out) {
       float* Io = r.I_out + (size_t)(b - r.item0) * N * N;
@@ -785,7 +822,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS, N == 256 ? 4 : 1) void k_far_l
     float2* tile = ws + (size_t)(it.tile0 + m) * N * N;
     float2 v[E];
 #pragma unroll
-    for (int a = 0; a < E; ++a) v[a] = tile[(size_t)(l + L * a) * N + ux];
+    for (int a = 0; a < E; ++a) v[a] = tile[(size_t)(l + L * a) * N + mx];
     line_fft<N, false>(v, l, tw, sx, typename ColMap<N>::Sync{});
 #pragma unroll
     for (int a = 0; a < E; ++a) {
@@ -836,13 +873,13 @@ __global__ __launch_bounds__(ColPass<N>::THREADS, N == 256 ? 4 : 1) void k_far_l
       float2* tile = ws + (size_t)(it.tile0 + m) * N * N;
       float2 v[E];
 #pragma unroll
-      for (int a = 0; a < E; ++a) v[a] = tile[(size_t)(l + L * a) * N + ux];
+      for (int a = 0; a < E; ++a) v[a] = tile[(size_t)(l + L * a) * N + mx];
       line_fft<N, false>(v, l, tw, sx, typename ColMap<N>::Sync{});
 #pragma unroll
       for (int a = 0; a < E; ++a) v[a] = cscale(cscale(v[a], inv), wgt[a] * inv);
       line_fft<N, true>(v, l, tw, sx, typename ColMap<N>::Sync{});
 #pragma unroll
-      for (int a = 0; a < E; ++a) tile[(size_t)(l + L * a) * N + ux] = v[a];
+      for (int a = 0; a < E; ++a) tile[(size_t)(l + L * a) * N + mx] = v[a];
     }
   }
 }
@@ -2039,7 +2076,7 @@ __global__ __launch_bounds__(Res<N>::THREADS) void k_res_fwd(const Item* __restr
       if (i == r.S - 1) {
         float2* trow = ws + ((size_t)(it.tile0 + m) * N + y) * N;
 #pragma unroll
-        for (int a = 0; a < E; ++a) trow[l + L * a] = v[a];
+        for (int a = 0; a < E; ++a) trow[mem_position<N>(l + L * a)] = v[a];
       } else {
         res_store_row<N>(v, tile, y, l);
       }
@@ -2081,7 +2118,7 @@ __global__ __launch_bounds__(Res<N>::THREADS) void k_res_adj(const Item* __restr
       float2 v[E];
       if (i == r.S - 1) {
 #pragma unroll
-        for (int a = 0; a < E; ++a) v[a] = wtile[(size_t)y * N + l + L * a];
+        for (int a = 0; a < E; ++a) v[a] = wtile[(size_t)y * N + mem_position<N>(l + L * a)];
       } else {
         res_load_row<N>(v, tile, y, l);
       }
@@ -2103,7 +2140,7 @@ __global__ __launch_bounds__(Res<N>::THREADS) void k_res_adj(const Item* __restr
       res_line_fft<N, false, L + 1, 1>(v, l, tw, tile + y * Res<N>::P);
       if (i == 0) {
 #pragma unroll
-        for (int a = 0; a < E; ++a) wtile[(size_t)y * N + l + L * a] = v[a];
+        for (int a = 0; a < E; ++a) wtile[(size_t)y * N + mem_position<N>(l + L * a)] = v[a];
       } else {
         res_store_row<N>(v, tile, y, l);
       }
