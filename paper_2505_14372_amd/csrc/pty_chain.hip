@@ -560,16 +560,19 @@ __global__ __launch_bounds__(256) void k_chain_far(const Item* __restrict__ item
   }
 }
 
-// dst = scale F^-1(src) of the probe-sized tiles (src transposed), added to dst if accumulate.
+// dst = scale F^-1(src) of probe-sized tiles (src transposed), added to dst if
+// accumulate; the probes of every request of a step in one launch.
 template <int N>
-__global__ __launch_bounds__(Ch<N>::T) void k_chain_plain(const float2* __restrict__ src, float2* __restrict__ dst,
-                                                          const float2* __restrict__ tab, float scale, int accumulate) {
+__global__ __launch_bounds__(Ch<N>::T) void k_chain_plain(const PlainTable t, const float2* __restrict__ tab,
+                                                          float scale, int accumulate) {
   __shared__ typename Ch<N>::Elem lds[Ch<N>::SIZE];
+  int q = 0, tile = blockIdx.x;
+  while (tile >= t.n[q]) tile -= t.n[q++];
   const Fft2<N> fft(lds, tab);
   float2 v[Ch<N>::EL];
-  fft.load_spec(v, src + (size_t)blockIdx.x * N * N);
+  fft.load_spec(v, t.src[q] + (size_t)tile * N * N);
   fft.inverse(v);
-  float2* out = dst + (size_t)blockIdx.x * N * N;
+  float2* out = t.dst[q] + (size_t)tile * N * N;
 #pragma unroll
   for (int e = 0; e < Ch<N>::EL; ++e) v[e] = cscale(v[e], scale);
   if (accumulate) {
@@ -633,8 +636,10 @@ struct Chain {
       run_as<kAdjoint>(L, p);
     }
   }
-  static void plain_inv(hipStream_t s, const float2* tw, const float2* src, float2* dst, int n, float scale, bool acc) {
-    hipLaunchKernelGGL((k_chain_plain<N>), dim3(n), dim3(Ch<N>::T), 0, s, src, dst, tw + N, scale, acc ? 1 : 0);
+  static void plain_inv(hipStream_t s, const float2* tw, const PlainTable& t, float scale, bool acc) {
+    int n = 0;
+    for (int k = 0; k < t.count; ++k) n += t.n[k];
+    if (n) hipLaunchKernelGGL((k_chain_plain<N>), dim3(n), dim3(Ch<N>::T), 0, s, t, tw + N, scale, acc ? 1 : 0);
   }
 };
 
@@ -650,9 +655,8 @@ bool chain_size(int N) { return N == 64 || N == 128; }
 
 void launch_chain_begin(const LaunchCtx& L, int N) { CHAIN_DISPATCH(N, begin(L)); }
 void launch_chain(const LaunchCtx& L, int N, const ChainRun& p) { CHAIN_DISPATCH(N, run(L, p)); }
-void launch_chain_plain_inv(int N, hipStream_t s, const float2* tw, const float2* src, float2* dst, int n, float scale,
-                            bool acc) {
-  CHAIN_DISPATCH(N, plain_inv(s, tw, src, dst, n, scale, acc));
+void launch_chain_plain_inv(int N, hipStream_t s, const float2* tw, const PlainTable& t, float scale, bool acc) {
+  CHAIN_DISPATCH(N, plain_inv(s, tw, t, scale, acc));
 }
 
 }  // namespace pty

@@ -123,6 +123,87 @@ __device__ __forceinline__ bool object_sum(const Item* __restrict__ items, int i
   return true;
 }
 
+// One real component of an update.
+//   SGD:  th -= lr g
+//   Adam: m = b1 m + (1 - b1) g ; v = b2 v + (1 - b2) g^2 ;
+//         th -= step_size m / (sqrt(v) inv_sqrt_bc2 + eps), step_size = lr / (1 - b1^t)
+// The complements c1 = 1 - b1 and c2 = 1 - b2 are formed in double: 1 - 0.999f in
+// float would be off by 1.3e-5 relative.
+struct OptCoef {
+  float lr, step_size, inv_sqrt_bc2, b1, c1, b2, c2, eps;
+};
+__device__ __forceinline__ void opt_element(int kind, const OptCoef& k, float& th, float g, float& mo, float& ve) {
+  if (kind == OPT_SGD) {
+    th -= k.lr * g;
+    return;
+  }
+  const float m = k.b1 * mo + k.c1 * g;
+  const float v = k.b2 * ve + k.c2 * g * g;
+  mo = m;
+  ve = v;
+  th -= k.step_size * m / (sqrtf(v) * k.inv_sqrt_bc2 + k.eps);
+}
+
+__device__ __forceinline__ OptCoef opt_coef(const OptSeg& s, const OptPar& p) {
+  if (s.kind != OPT_ADAM) return OptCoef{(float)s.lr, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  AdamFactors f = s.f;
+  if (p.t_dev) f = adam_factors(s.lr, p.b1, p.b2, *p.t_dev + 1);
+  return OptCoef{0.f, f.step_size, f.inv_sqrt_bc2, (float)p.b1, (float)(1.0 - p.b1), (float)p.b2, (float)(1.0 - p.b2),
+                 p.eps};
+}
+
+// Updates a segment: thread `start` of `step`, 4 consecutive elements at a time.
+__device__ __forceinline__ void opt_update(const OptSeg& s, const OptPar& p, long long start, long long step) {
+  const OptCoef k = opt_coef(s, p);
+  const long long hi = s.n;
+  for (long long i = 4 * start; i < hi; i += 4 * step) {
+    if (s.wide && i + 4 <= hi) {
+      float4 th = *reinterpret_cast<float4*>(s.th + i), mo{}, ve{};
+      const float4 g = *reinterpret_cast<const float4*>(s.g + i);
+      if (s.kind == OPT_ADAM) {
+        mo = *reinterpret_cast<float4*>(s.m + i);
+        ve = *reinterpret_cast<float4*>(s.v + i);
+      }
+      opt_element(s.kind, k, th.x, g.x, mo.x, ve.x);
+      opt_element(s.kind, k, th.y, g.y, mo.y, ve.y);
+      opt_element(s.kind, k, th.z, g.z, mo.z, ve.z);
+      opt_element(s.kind, k, th.w, g.w, mo.w, ve.w);
+      if (s.kind == OPT_ADAM) {
+        *reinterpret_cast<float4*>(s.m + i) = mo;
+        *reinterpret_cast<float4*>(s.v + i) = ve;
+      }
+      *reinterpret_cast<float4*>(s.th + i) = th;
+    } else {
+      for (long long j = i; j < hi && j < i + 4; ++j) {
+        float mo = 0.f, ve = 0.f;
+        if (s.kind == OPT_ADAM) {
+          mo = s.m[j];
+          ve = s.v[j];
+        }
+        opt_element(s.kind, k, s.th[j], s.g[j], mo, ve);
+        if (s.kind == OPT_ADAM) {
+          s.m[j] = mo;
+          s.v[j] = ve;
+        }
+      }
+    }
+  }
+}
+
+// Segment and parameters of this workgroup.
+__device__ __forceinline__ int opt_segment(const OptTable& t, int& par) {
+  int q = -1;
+  unsigned at = 0;
+#pragma unroll
+  for (int k = 0; k < kMaxOpt; ++k) {
+    const bool in = t.at[k] <= blockIdx.x * kMaxReqs + (kMaxReqs - 1);
+    q += in ? 1 : 0;
+    at = in ? t.at[k] : at;
+  }
+  par = (int)(at % kMaxReqs);
+  return q;
+}
+
 // Descriptor of batch entry b, written by nt threads (t: this one's index):
 // its request, integer window offset and
 // subpixel remainder (in double, so n = floor(X + 0.5) is exact for float32

@@ -184,14 +184,60 @@ void launch_loss_reduce(const LaunchCtx& L, int N);
 void launch_plain2d(int N, hipStream_t s, const float2* tw, const float2* src, float2* dst, int n_tiles,
                     bool inverse, float scale, bool accumulate);
 void launch_fill(hipStream_t s, float* p, size_t n, float v);
-void launch_sgd(hipStream_t s, float* th, const float* g, size_t n, float lr);
-void launch_adam(hipStream_t s, float* th, const float* g, float* m, float* v, size_t n, float step_size,
-                 float inv_sqrt_bc2, double b1, double b2, float eps);
-// Adam with the step count read on the device: t = *step_dev + 1
-void launch_adam_dev(hipStream_t s, float* th, const float* g, float* m, float* v, size_t n, double lr,
-                     const int64_t* step_dev, double b1, double b2, float eps);
 void launch_step_advance(hipStream_t s, int64_t* step_dev);
 int col_blocks(int N);
+
+// Optimiser updates of one launch: one segment per variable, an element's
+// update by the formulas in opt_element.
+constexpr int kMaxOpt = 3 * kMaxReqs;
+enum OptKind { OPT_SGD = 1, OPT_ADAM = 2 };
+struct OptSeg {
+  float *th, *m, *v;
+  const float* g;
+  long long n;              // floats
+  union {
+    double lr;              // SGD, and Adam with the count on the device
+    AdamFactors f;          // Adam with the step's factors from the host
+  };
+  unsigned block0;          // first workgroup (set by the launcher)
+  short kind;               // OptKind
+  short wide;               // every pointer a multiple of 16 bytes (set by the launcher)
+};
+struct OptPar {
+  double b1, b2;
+  const int64_t* t_dev;     // Adam: the step is *t_dev + 1; null: see OptSeg::f
+  float eps;
+};
+struct OptTable {
+  // first workgroup * kMaxReqs + index into par of each segment, all bits set
+  // past the last: side by side, read in one access
+  unsigned at[kMaxOpt];
+  OptSeg s[kMaxOpt];
+  OptPar par[kMaxReqs];
+  signed char par_of[kMaxOpt];   // the segments' indices into par
+  int n_segs, n_pars;
+};
+static_assert(sizeof(OptTable) <= 4096 - 64, "the table is a kernel argument");
+// workgroups of T threads for n elements, 4 a thread at a time
+__host__ __device__ inline unsigned opt_blocks(long long n, int T) {
+  const long long b = (n + 4 * T - 1) / (4 * T);
+  return b > 65536 ? 65536u : (unsigned)b;
+}
+// Places the segments on workgroups of T threads; returns how many.
+inline unsigned opt_layout(OptTable& t, int T) {
+  unsigned blocks = 0;
+  for (int k = t.n_segs; k < kMaxOpt; ++k) t.at[k] = ~0u;
+  for (int k = 0; k < t.n_segs; ++k) {
+    OptSeg& s = t.s[k];
+    s.block0 = blocks;
+    t.at[k] = blocks * kMaxReqs + (unsigned)t.par_of[k];
+    const uintptr_t at = (uintptr_t)s.th | (uintptr_t)s.g | (s.kind == OPT_ADAM ? (uintptr_t)s.m | (uintptr_t)s.v : 0);
+    s.wide = at % 16 == 0;
+    blocks += opt_blocks(s.n, T);
+  }
+  return blocks;
+}
+void launch_opt(hipStream_t s, OptTable t);
 
 enum ColOp { COL_SHIFT = 0, COL_PROP = 1, COL_PROP_ADJ = 2, COL_FINAL = 3 };
 
@@ -266,8 +312,14 @@ struct ChainRun {
 bool chain_size(int N);
 void launch_chain_begin(const LaunchCtx& L, int N);
 void launch_chain(const LaunchCtx& L, int N, const ChainRun& p);
-void launch_chain_plain_inv(int N, hipStream_t s, const float2* tw, const float2* src, float2* dst, int n, float scale,
-                            bool acc);
+// dst[k] = scale F^-1(src[k]) (+ dst[k] if accumulate) of the n[k] N x N tiles of each entry
+struct PlainTable {
+  const float2* src[kMaxReqs];
+  float2* dst[kMaxReqs];
+  int n[kMaxReqs];
+  int count;
+};
+void launch_chain_plain_inv(int N, hipStream_t s, const float2* tw, const PlainTable& t, float scale, bool acc);
 
 // LDS-resident forward / adjoint chains (N = 64, 128; every slice checkpointed)
 bool resident_supported(int N);
