@@ -236,12 +236,28 @@ constexpr int pad_to(int x, int mod, int rem) { return x + ((rem - x % mod) % mo
 // to consecutive columns) float2 apart. Both strides are padded so that the
 // 64 lanes of a wave spread over all 64 four-byte LDS banks: a float2
 // access then takes the minimum of two bank cycles per wave.
+// Where the scratch limits the workgroups on a CU (24 values a lane at N = 192:
+// 61 KB for rows, 57 KB for columns, two workgroups; rows at N = 128: 44 KB) the
+// real and imaginary parts go through it in turn, in half the space (35, 29 and
+// 26 KB): column passes and forward row passes then run three waves per SIMD
+// instead of two at N = 192, and the rows of a wave need no barrier between the
+// halves. A step of 192 x 192, 6 modes, 20 slices, 256 positions 14.1 -> 13.3 ms,
+// the forward of 100 positions, 3 modes, 12 slices 897 -> 801 us; an ePIE step at
+// 128 x 128, 3 modes, 4 slices 709 -> 700 us.
+// Strides: a wave's 64 accesses of 4 bytes fall on 64 different banks.
+template <bool SPLIT> struct XchElem { using T = float2; };
+template <> struct XchElem<true> { using T = float; };
 template <int N> struct Xch {
   static constexpr int L = Cfg<N>::L, E = Cfg<N>::E;
   static constexpr int XP = L + 1;
   static constexpr int SIZE = E * XP;
-  static constexpr int ROW_STRIDE = (L == 16) ? pad_to(SIZE, 32, 16) : pad_to(SIZE, 32, 8);
-  static constexpr int COL_STRIDE = (L == 16) ? pad_to(SIZE, 32, 4) : pad_to(SIZE, 2, 1);
+  static constexpr bool ROW_SPLIT = N == 192 || N == 128, COL_SPLIT = N == 192;
+  using RowElem = typename XchElem<ROW_SPLIT>::T;
+  using ColElem = typename XchElem<COL_SPLIT>::T;
+  static constexpr int ROW_STRIDE = ROW_SPLIT ? pad_to(SIZE, 64, 8)
+                                    : (L == 16) ? pad_to(SIZE, 32, 16) : pad_to(SIZE, 32, 8);
+  static constexpr int COL_STRIDE = COL_SPLIT ? pad_to(SIZE, 4, 2)
+                                    : (L == 16) ? pad_to(SIZE, 32, 4) : pad_to(SIZE, 2, 1);
 };
 
 // Line FFT of v (layout above), in two stages around the LDS exchange.
@@ -265,6 +281,16 @@ __host__ __device__ __forceinline__ void line_fft_stage1(float2 (&v)[Cfg<N>::E],
 }
 
 template <int N, bool INV>
+__host__ __device__ __forceinline__ void line_fft_last(float2 (&u)[Cfg<N>::E], float2 (&v)[Cfg<N>::E]) {
+  constexpr int L = Cfg<N>::L, C = Cfg<N>::E / L;
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    Dft<L, INV>::run(&u[c * L]);
+#pragma unroll
+    for (int k2 = 0; k2 < L; ++k2) v[c + C * k2] = u[c * L + k2];
+  }
+}
+template <int N, bool INV>
 __host__ __device__ __forceinline__ void line_fft_stage2(float2 (&v)[Cfg<N>::E], int l, const float2* xch) {
   constexpr int L = Cfg<N>::L, E = Cfg<N>::E, C = E / L, XP = Xch<N>::XP;
   float2 u[E];
@@ -273,22 +299,17 @@ __host__ __device__ __forceinline__ void line_fft_stage2(float2 (&v)[Cfg<N>::E],
 #pragma unroll
     for (int ll = 0; ll < L; ++ll) u[c * L + ll] = xch[(l + L * c) * XP + ll];
   }
-#pragma unroll
-  for (int c = 0; c < C; ++c) {
-    Dft<L, INV>::run(&u[c * L]);
-#pragma unroll
-    for (int k2 = 0; k2 < L; ++k2) v[c + C * k2] = u[c * L + k2];
-  }
+  line_fft_last<N, INV>(u, v);
 }
 
 // Whole line FFT. SYNC orders the lanes' LDS accesses: it runs before the
 // exchange writes (so the scratch may be reused line after line) and
-// between the writes and the reads.
-template <int N, bool INV, typename SYNC>
-__device__ __forceinline__ void line_fft(float2 (&v)[Cfg<N>::E], int l, const float2* tw, float2* xch,
-                                         SYNC sync) {
+// between the writes and the reads. With a scratch of floats the real and
+// imaginary parts go through it one after the other, in half the space.
+template <int N, bool INV, typename X, typename SYNC>
+__device__ __forceinline__ void line_fft(float2 (&v)[Cfg<N>::E], int l, const float2* tw, X* xch, SYNC sync) {
   Dft<Cfg<N>::E, INV>::run(v);
-  constexpr int L = Cfg<N>::L, E = Cfg<N>::E, XP = Xch<N>::XP;
+  constexpr int L = Cfg<N>::L, E = Cfg<N>::E, C = E / L, XP = Xch<N>::XP;
 #pragma unroll
   for (int k1 = 1; k1 < E; ++k1) {
     float2 w = tw[l * k1];
@@ -296,11 +317,30 @@ __device__ __forceinline__ void line_fft(float2 (&v)[Cfg<N>::E], int l, const fl
     v[k1] = cmul(v[k1], w);
   }
   sync();
+  if constexpr (sizeof(X) == sizeof(float)) {
+    float2 u[E];
 #pragma unroll
-  for (int k1 = 0; k1 < E; ++k1) xch[k1 * XP + l] = v[k1];
-  sync();
-  line_fft_stage2<N, INV>(v, l, xch);
-  (void)L;
+    for (int k1 = 0; k1 < E; ++k1) xch[k1 * XP + l] = v[k1].x;
+    sync();
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int ll = 0; ll < L; ++ll) u[c * L + ll].x = xch[(l + L * c) * XP + ll];
+    sync();
+#pragma unroll
+    for (int k1 = 0; k1 < E; ++k1) xch[k1 * XP + l] = v[k1].y;
+    sync();
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int ll = 0; ll < L; ++ll) u[c * L + ll].y = xch[(l + L * c) * XP + ll];
+    line_fft_last<N, INV>(u, v);
+  } else {
+#pragma unroll
+    for (int k1 = 0; k1 < E; ++k1) xch[k1 * XP + l] = v[k1];
+    sync();
+    line_fft_stage2<N, INV>(v, l, xch);
+  }
 }
 
 // ---------------------------------------------------------------- LDS-resident tiles

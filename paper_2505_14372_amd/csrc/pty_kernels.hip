@@ -235,7 +235,7 @@ __global__ void k_items(const ReqTable reqs, int n_reqs, Item* __restrict__ item
 // max-accumulated into r.emax[item][i] (non-negative floats order like their
 // bit patterns, so an unsigned atomic max is exact).
 template <int N, bool FROM_REAL, bool HALF, bool EMAX = false>
-__global__ __launch_bounds__(kThreads) void k_row_fwd(const Item* __restrict__ items,
+__global__ __launch_bounds__(kThreads, N == 192 && !EMAX ? 3 : 1) void k_row_fwd(const Item* __restrict__ items,
                                                       const ReqTable reqs,
                                                       float2* __restrict__ ws, void* __restrict__ ck_,
                                                       const float2* __restrict__ twg, int step,
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(kThreads) void k_row_fwd(const Item* __restrict__ i
   const int by = gridDim.y - 1 - blockIdx.y;
   constexpr int L = Pass<N>::L, E = Pass<N>::E, LINES = Pass<N>::LINES;
   __shared__ float2 tw[N];
-  __shared__ float2 xch[LINES * Xch<N>::ROW_STRIDE];
+  __shared__ typename Xch<N>::RowElem xch[LINES * Xch<N>::ROW_STRIDE];
   const Item it = items[item_off + by];
   const ReqDev& r = reqs.r[it.req];
   const int i = step;
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(kThreads) void k_row_fwd(const Item* __restrict__ i
   CT* ck = static_cast<CT*>(ck_);
   const int l = threadIdx.x % L, line = threadIdx.x / L;
   const int y = blockIdx.x * LINES + line;
-  float2* sx = xch + line * Xch<N>::ROW_STRIDE;
+  typename Xch<N>::RowElem* sx = xch + line * Xch<N>::ROW_STRIDE;
   // the row spectrum of slice i >= 1 was written by a propagation column pass,
   // which leaves the columns outside the propagator's support unwritten (zero)
   unsigned live = ~0u;
@@ -281,9 +281,10 @@ __global__ __launch_bounds__(kThreads) void k_row_fwd(const Item* __restrict__ i
   }
   // Each mode's output row is stored as soon as it is transformed: with the
   // masked loads and stores in load_row_slots / store_row_slots the pass
-  // holds few enough registers for three waves per SIMD at N = 256, which
-  // hides the memory latency better than deferring the stores behind the
-  // next mode's requests at two waves.
+  // holds few enough registers for three waves per SIMD at N = 256 (and, with 8
+  // spilled, at N = 192: forward of 100 positions 847 -> 801 us), which hides the
+  // memory latency better than deferring the stores behind the next mode's
+  // requests at two waves. (Four waves, 4 spilled, measured slower at N = 256.)
   for (int m = 0; m < r.M; ++m) {
     float2* trow = ws + ((size_t)(it.tile0 + m) * N + y) * N;
     float2 v[E];
@@ -380,7 +381,7 @@ __global__ __launch_bounds__(kThreads) void k_row_adj(const Item* __restrict__ i
   const int by = gridDim.y - 1 - blockIdx.y;
   constexpr int L = Pass<N>::L, E = Pass<N>::E, LINES = Pass<N>::LINES;
   __shared__ float2 tw[N];
-  __shared__ float2 xch[LINES * Xch<N>::ROW_STRIDE];
+  __shared__ typename Xch<N>::RowElem xch[LINES * Xch<N>::ROW_STRIDE];
   const Item it = items[item_off + by];
   const ReqDev& r = reqs.r[it.req];
   const int i = r.S - 1 - step;
@@ -389,7 +390,7 @@ __global__ __launch_bounds__(kThreads) void k_row_adj(const Item* __restrict__ i
   __syncthreads();
   const int l0 = threadIdx.x % L, l = l0, line = threadIdx.x / L;
   const int y = blockIdx.x * LINES + line;
-  float2* sx = xch + line * Xch<N>::ROW_STRIDE;
+  typename Xch<N>::RowElem* sx = xch + line * Xch<N>::ROW_STRIDE;
   using CT = typename Ck<HALF>::T;
   const CT* ck = static_cast<const CT*>(ck_);
   // columns outside the propagator's support: zero in g for i < S - 1 (it came
@@ -527,7 +528,7 @@ __global__ __launch_bounds__(kThreads) void k_row_plain(const float2* __restrict
                                                         int accumulate) {
   constexpr int L = Pass<N>::L, E = Pass<N>::E, LINES = Pass<N>::LINES;
   __shared__ float2 tw[N];
-  __shared__ float2 xch[LINES * Xch<N>::ROW_STRIDE];
+  __shared__ typename Xch<N>::RowElem xch[LINES * Xch<N>::ROW_STRIDE];
   load_twiddles<N>(tw, twg);
   __syncthreads();
   const int l = threadIdx.x % L, line = threadIdx.x / L;
@@ -601,7 +602,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col(const Item* __restr
   const int cb = (int)((colmap >> (8 * blockIdx.x)) & 0xffu);
   __shared__ float2 tw[N];
   __shared__ float4 hy[PROP ? N : 1];
-  __shared__ float2 xch[CB * ColMap<N>::STRIDE];
+  __shared__ typename Xch<N>::ColElem xch[CB * ColMap<N>::STRIDE];
   __shared__ float red[2][T / 64];
   // grid (column blocks, modes, items): dispatched item by item, in item order
   const int b = item_off + blockIdx.z, m = blockIdx.y;
@@ -630,7 +631,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col(const Item* __restr
   }
   const int c = ColMap<N>::col(), l = ColMap<N>::lane(), t = threadIdx.x;
   const int mx = cb * CB + c, ux = mem_column<N>(mx);   // position in a tile row, column
-  float2* sx = xch + c * ColMap<N>::STRIDE;
+  typename Xch<N>::ColElem* sx = xch + c * ColMap<N>::STRIDE;
   float2* tile = ws + (size_t)(it.tile0 + m) * N * N;
   // a forward propagation whose output is a stored checkpoint runs in place
   // in that slot, where the forward row pass left its input
@@ -761,7 +762,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col_plain(float2* __res
                                                         float scale) {
   constexpr int L = ColPass<N>::L, E = ColPass<N>::E, CB = ColPass<N>::CB;
   __shared__ float2 tw[N];
-  __shared__ float2 xch[CB * ColMap<N>::STRIDE];
+  __shared__ typename Xch<N>::ColElem xch[CB * ColMap<N>::STRIDE];
   load_twiddles<N>(tw, twg);
   __syncthreads();
   const int c = ColMap<N>::col(), l = ColMap<N>::lane();
@@ -794,7 +795,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS, N == 256 ? 4 : 1) void k_far_l
                                                        int item_off) {
   constexpr int L = ColPass<N>::L, E = ColPass<N>::E, CB = ColPass<N>::CB;
   __shared__ float2 tw[N];
-  __shared__ float2 xch[CB * ColMap<N>::STRIDE];
+  __shared__ typename Xch<N>::ColElem xch[CB * ColMap<N>::STRIDE];
   __shared__ float red[ColPass<N>::THREADS / 64];
   const int b = item_off + blockIdx.y;
   const Item it = items[b];
@@ -813,7 +814,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS, N == 256 ? 4 : 1) void k_far_l
   }
   load_twiddles<N>(tw, twg);
   __syncthreads();
-  float2* sx = xch + c * ColMap<N>::STRIDE;
+  typename Xch<N>::ColElem* sx = xch + c * ColMap<N>::STRIDE;
   const float inv = 1.f / (float)N;
   float I[E];
 #pragma unroll
@@ -960,7 +961,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col_final_chain(const I
   static_assert(T >= N, "the twiddle table takes one entry per thread");
   const int cb = (int)((colmap >> (8 * blockIdx.x)) & 0xffu);
   __shared__ float2 tw[N];
-  __shared__ float2 xch[CB * ColMap<N>::STRIDE];
+  __shared__ typename Xch<N>::ColElem xch[CB * ColMap<N>::STRIDE];
   __shared__ float red[2][T / 64];
   const int rq = blockIdx.z / kProbeSplit, q = blockIdx.z % kProbeSplit, m = blockIdx.y;
   const ReqDev& r = reqs.r[rq];
@@ -970,7 +971,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col_final_chain(const I
   __syncthreads();
   const int c = ColMap<N>::col(), l = ColMap<N>::lane();
   const int ux = cb * CB + c;
-  float2* sx = xch + c * ColMap<N>::STRIDE;
+  typename Xch<N>::ColElem* sx = xch + c * ColMap<N>::STRIDE;
   const float2* ph = r.phat + (size_t)m * N * N;
   const float inv = 1.f / (float)N;
   const float fx = (float)((ux < (N + 1) / 2) ? ux : ux - N) / (float)N;
