@@ -239,7 +239,7 @@ __global__ __launch_bounds__(kThreads, N == 192 && !EMAX ? 3 : 1) void k_row_fwd
                                                       const ReqTable reqs,
                                                       float2* __restrict__ ws, void* __restrict__ ck_,
                                                       const float2* __restrict__ twg, int step,
-                                                      PsiStore store, int item_off) {
+                                                      PsiStore store, int item_off, int split) {
   // items in reverse order (the column passes run them forward; see Launch::col)
   const int by = gridDim.y - 1 - blockIdx.y;
   constexpr int L = Pass<N>::L, E = Pass<N>::E, LINES = Pass<N>::LINES;
@@ -248,7 +248,8 @@ __global__ __launch_bounds__(kThreads, N == 192 && !EMAX ? 3 : 1) void k_row_fwd
   const Item it = items[item_off + by];
   const ReqDev& r = reqs.r[it.req];
   const int i = step;
-  if (!it.valid || i >= r.S) return;
+  const int m_lo = split ? blockIdx.z : 0, m_hi = split ? m_lo + 1 : r.M;
+  if (!it.valid || i >= r.S || m_lo >= r.M) return;
   load_twiddles<N>(tw, twg);
   __syncthreads();
   using CT = typename Ck<HALF>::T;
@@ -285,7 +286,7 @@ __global__ __launch_bounds__(kThreads, N == 192 && !EMAX ? 3 : 1) void k_row_fwd
   // spilled, at N = 192: forward of 100 positions 847 -> 801 us), which hides the
   // memory latency better than deferring the stores behind the next mode's
   // requests at two waves. (Four waves, 4 spilled, measured slower at N = 256.)
-  for (int m = 0; m < r.M; ++m) {
+  for (int m = m_lo; m < m_hi; ++m) {
     float2* trow = ws + ((size_t)(it.tile0 + m) * N + y) * N;
     float2 v[E];
     if constexpr (FROM_REAL) {
@@ -1066,13 +1067,20 @@ template <int N>
 struct Launch {
   template <bool HALF>
   static void rows_fwd_t(const LaunchCtx& L, int step, PsiStore st, bool from_real) {
-    dim3 g(Pass<N>::NBLK, L.n_items);
+    // One mode a workgroup where a launch of whole items leaves CUs idle or with one
+    // workgroup; the object row is then read once more per mode, from cache. Loss and
+    // gradients of 3 modes, 6 slices at 192 x 192: 526 -> 461 us at 8 positions (48
+    // workgroups of whole items), 625 -> 584 at 32 (192); forward: 299 -> 282 at 48
+    // (288), against 470 -> 477 at 100 (600). At 256 x 256, 4 modes, 6 slices: 245 ->
+    // 229 at 16 (256), against 761 -> 770 at 100 (1600).
+    const int split = !L.emax && L.max_modes > 1 && (int)Pass<N>::NBLK * L.n_items <= 320;
+    dim3 g(Pass<N>::NBLK, L.n_items, split ? L.max_modes : 1);
     if (from_real)
-      hipLaunchKernelGGL((k_row_fwd<N, true, HALF>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, st, L.item_off);
+      hipLaunchKernelGGL((k_row_fwd<N, true, HALF>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, st, L.item_off, split);
     else if (L.emax)
-      hipLaunchKernelGGL((k_row_fwd<N, false, HALF, true>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, st, L.item_off);
+      hipLaunchKernelGGL((k_row_fwd<N, false, HALF, true>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, st, L.item_off, split);
     else
-      hipLaunchKernelGGL((k_row_fwd<N, false, HALF>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, st, L.item_off);
+      hipLaunchKernelGGL((k_row_fwd<N, false, HALF>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, st, L.item_off, split);
   }
   static void rows_fwd(const LaunchCtx& L, int step, PsiStore st, bool from_real) {
     if (L.ck_half) rows_fwd_t<true>(L, step, st, from_real);
