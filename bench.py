@@ -128,6 +128,8 @@ def kernel_bytes_per_launch(name, N, M, B, S, ck_half=False, engine="adam", spec
         return int(B * 2 * M * Tl)
     if name == "far_loss":     # tiles read twice (the far field is recomputed, not stored), seed written; pattern read
         return B * (3 * M * T + T // 2)
+    if name == "chain":        # every slice: store the entry waves, read them back, store the contributions; seeds; patches
+        return int(B * (M * (3 * S + 4) * T + 2 * S * T + T // 2))
     if name == "col_shift":    # write every tile (the probe spectrum stays in cache)
         return B * M * T
     if name == "col_final":    # read + write every tile, or read every tile and write the chain sums
@@ -153,14 +155,15 @@ def method_flops_per_launch(name, N, M, B, S=1):
     transform): each slice step is a 2D DFT and an inverse 2D DFT per mode,
     whose row halves run in the row passes and column halves in the column
     passes; an LDS-resident chain runs every slice in one launch (row halves of
-    all S slices, column halves of the S - 1 propagations). Work a kernel does
-    beyond that (the adjoint row pass recovering the entry wave from its
+    all S slices, column halves of the S - 1 propagations); the chain kernels
+    (every slice stored) take the whole step's. Work a kernel does beyond that (the adjoint row pass recovering the entry wave from its
     spectral checkpoint, the far-field pass recomputing the far field) is
     design overhead and not counted."""
     per_line = 5 * N * np.log2(N)
     lines = B * M * N
     n_fft = {"row_fwd": 2, "row_adj": 2, "col_prop": 2, "col_prop_adj": 2, "far_loss": 2,
-             "col_shift": 1, "col_final": 1, "res_fwd": 4 * S - 2, "res_adj": 4 * S - 2}.get(name, 0)
+             "col_shift": 1, "col_final": 1, "res_fwd": 4 * S - 2, "res_adj": 4 * S - 2,
+             "chain": 8 * S}.get(name, 0)
     return n_fft * lines * per_line
 
 
@@ -188,17 +191,18 @@ def method_bytes_per_launch(name, N, B, S=1):
     """The method's own HBM bytes in one launch: the object patch of the slice
     (read in the forward and again in the adjoint), the object-gradient
     read-modify-write in the adjoint and the pattern read by the loss; tiles
-    are taken to stay on chip (an LDS-resident chain covers all S slices)."""
+    are taken to stay on chip (an LDS-resident chain covers all S slices, the
+    chain kernels the whole step)."""
     T = 8 * N * N
     return {"row_fwd": B * T, "row_adj": 3 * B * T, "far_loss": B * 4 * N * N,
-            "res_fwd": S * B * T, "res_adj": 3 * S * B * T}.get(name, 0)
+            "res_fwd": S * B * T, "res_adj": 3 * S * B * T, "chain": B * (4 * N * N + 4 * S * T)}.get(name, 0)
 
 
-# Object-gradient reduction measured faster per workload on one MI355X: the
-# ordered sum pays one extra pass over the group's contributions and wins
-# where atomics contend (a whole dense scan in one group, 128^2) or where the
-# adjoint row pass runs one wave per SIMD (192^2); the served stream also
-# becomes bit-identical to its one-at-a-time run.
+# Object-gradient reduction per workload. The default mode adds with atomics only
+# in large groups of many modes at N = 256, where that measured faster (83.8
+# against 84.2 ms per group of 512), and sums stored contributions in batch order
+# elsewhere, as the ordered mode does everywhere; the served stream is then
+# bit-identical to its one-at-a-time run.
 FASTER_REDUCTION = {"ms256_m8_s30": "atomic", "ms192_m6_s20": "ordered", "ms128_m4_s8": "ordered",
                     "spoa64": "atomic", "serving": "ordered"}
 
@@ -472,7 +476,7 @@ def kernel_source_hash():
     import hashlib
     import re
     h = hashlib.sha256()
-    for p in ("pty_kernels.hip", "pty_fft.hpp", "pty_internal.h"):
+    for p in ("pty_kernels.hip", "pty_device.hpp", "pty_fft.hpp", "pty_internal.h"):
         with open(os.path.join(ROOT, "paper_2505_14372_amd", "csrc", p)) as f:
             text = f.read()
         text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)
