@@ -101,33 +101,12 @@ struct WholeLines {
   static constexpr bool on = Cfg<N>::L * sizeof(float2) >= 128;
 };
 
-// Row-pass accesses of a row spectrum. A step is one access of a lane: register
-// a (16 lanes, 8 bytes each) or, where the columns are stored in pairs (see
-// row_pairs), registers 2 c and 2 c + 1 (8 lanes, 16 bytes each); either way the
-// lanes of a row cover a whole 128-byte line, which a non-temporal load (NT, for
-// rows read once) needs: of a line read in two halves it would not keep the
-// second one.
+// Row-pass accesses of a row spectrum: a lane moves register a (16 lanes, 8 bytes
+// each) or, where the columns are stored in pairs (see row_pairs), registers 2 c
+// and 2 c + 1 (8 lanes, 16 bytes each); either way the lanes of a row cover a
+// whole 128-byte line, which a non-temporal load (NT, for rows read once) needs:
+// of a line read in two halves it would not keep the second one.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-template <int N> struct RowSteps {
-  static constexpr int W = row_pairs<N>() ? 2 : 1;        // registers of a step
-  static constexpr int COUNT = Cfg<N>::E / W;
-  static constexpr unsigned BITS = W == 2 ? 3u : 1u;      // their bits in a slot mask
-};
-// the values of one step, index i of the row counted in steps (i = l: the first)
-template <int N, bool NT>
-__device__ __forceinline__ void load_step(float2 (&t)[RowSteps<N>::W], const float2* row, int i) {
-  if constexpr (row_pairs<N>()) {
-    const f32x4* p = reinterpret_cast<const f32x4*>(row) + i;
-    const f32x4 q = NT ? __builtin_nontemporal_load(p) : *p;
-    t[0] = make_float2(q.x, q.y);
-    t[1] = make_float2(q.z, q.w);
-  } else if constexpr (NT) {
-    const float2* p = row + i;
-    t[0] = make_float2(__builtin_nontemporal_load(&p->x), __builtin_nontemporal_load(&p->y));
-  } else {
-    t[0] = row[i];
-  }
-}
 
 // Row-pass load of the register slots a set in `mask`, zero in the others, of the
 // adjoint row pass at N = 256. A masked slot loads the lane's slot-0 element of
@@ -161,8 +140,8 @@ __device__ __forceinline__ unsigned wave_slots(unsigned mask) {
 }
 
 // Row-pass load of the register slots a set in `mask`, zero in the others. `any`
-// (wave_slots(mask)) is uniform, so a step no lane of the wave needs is skipped
-// by a scalar branch and costs no request; the other steps are read by every
+// (wave_slots(mask)) is uniform, so a slot or pair no lane of the wave needs is skipped
+// by a scalar branch and costs no request; the others are read by every
 // lane from one base address with immediate offsets (no per-slot address
 // registers), and the lanes whose slot is dead take zero.
 // A dead column of a tile holds whatever was last written there (stale data,
@@ -171,18 +150,30 @@ __device__ __forceinline__ unsigned wave_slots(unsigned mask) {
 template <int N, bool NT = false>
 __device__ __forceinline__ void load_row_slots(float2 (&v)[Cfg<N>::E], const float2* row, int l, unsigned mask,
                                                unsigned any) {
-  constexpr int E = Cfg<N>::E, W = RowSteps<N>::W;
-  // (both slots of a pair are loaded if one is needed)
-  const unsigned got = W == 2 ? any | ((any & 0x555555u) << 1) | ((any & 0xaaaaaau) >> 1) : any;
-  const float2* p = row + W * l;
+  constexpr int L = Cfg<N>::L, E = Cfg<N>::E;
+  unsigned got = any;
+  if constexpr (row_pairs<N>()) {
+    // (both slots of a pair are loaded if one is needed)
+    got = any | ((any & 0x555555u) << 1) | ((any & 0xaaaaaau) >> 1);
+    const f32x4* p = reinterpret_cast<const f32x4*>(row) + l;
 #pragma unroll
-  for (int c = 0; c < RowSteps<N>::COUNT; ++c) {
-    float2 t[W];
+    for (int a = 0; a < E; a += 2) {
+      f32x4 t = {0.f, 0.f, 0.f, 0.f};
+      if ((got >> a) & 1u) t = NT ? __builtin_nontemporal_load(p + L * (a / 2)) : p[L * (a / 2)];
+      v[a] = make_float2(t.x, t.y);
+      v[a + 1] = make_float2(t.z, t.w);
+    }
+  } else {
+    const float2* p = row + l;
 #pragma unroll
-    for (int k = 0; k < W; ++k) t[k] = make_float2(0.f, 0.f);
-    if ((got >> (W * c)) & 1u) load_step<N, NT>(t, p, Cfg<N>::L * c);
-#pragma unroll
-    for (int k = 0; k < W; ++k) v[W * c + k] = t[k];
+    for (int a = 0; a < E; ++a) {
+      v[a] = make_float2(0.f, 0.f);
+      if ((got >> a) & 1u) {
+        if constexpr (NT)
+          v[a] = make_float2(__builtin_nontemporal_load(&p[L * a].x), __builtin_nontemporal_load(&p[L * a].y));
+        else v[a] = p[L * a];
+      }
+    }
   }
   const unsigned part = got & ~mask;
 #pragma unroll
@@ -190,24 +181,24 @@ __device__ __forceinline__ void load_row_slots(float2 (&v)[Cfg<N>::E], const flo
     if ((part >> a) & 1u) v[a] = make_float2(0.f, 0.f);
 }
 
-// Row-pass store of the steps with a slot set in `any` (wave-uniform): every
+// Row-pass store of the slots (or pairs) set in `any` (wave-uniform): every
 // lane stores, also one whose column is dead, since no consumer reads dead
 // columns, so lines are written whole (against exact stores 1.070 -> 1.046 ms per
 // adjoint launch at N = 256, 8 modes, 512 positions).
 template <int N>
 __device__ __forceinline__ void store_row_slots(const float2 (&v)[Cfg<N>::E], float2* row, int l, unsigned any) {
-  constexpr int L = Cfg<N>::L, W = RowSteps<N>::W;
-  float2* p = row + W * l;
+  constexpr int L = Cfg<N>::L, E = Cfg<N>::E;
+  if constexpr (row_pairs<N>()) {
+    f32x4* p = reinterpret_cast<f32x4*>(row) + l;
 #pragma unroll
-  for (int c = 0; c < RowSteps<N>::COUNT; ++c)
-    if ((any >> (W * c)) & RowSteps<N>::BITS) {
-      if constexpr (row_pairs<N>()) {
-        const f32x4 t = {v[2 * c].x, v[2 * c].y, v[2 * c + 1].x, v[2 * c + 1].y};
-        reinterpret_cast<f32x4*>(p)[L * c] = t;
-      } else {
-        p[L * c] = v[c];
-      }
-    }
+    for (int a = 0; a < E; a += 2)
+      if ((any >> a) & 3u) p[L * (a / 2)] = f32x4{v[a].x, v[a].y, v[a + 1].x, v[a + 1].y};
+  } else {
+    float2* p = row + l;
+#pragma unroll
+    for (int a = 0; a < E; ++a)
+      if ((any >> a) & 1u) p[L * a] = v[a];
+  }
 }
 
 // byte offset of element (y, x) of an N x N tile, or kOff when the lane is masked off
@@ -409,7 +400,7 @@ __global__ __launch_bounds__(kThreads) void k_row_adj(const Item* __restrict__ i
   const unsigned cmask = (r.live && i >= 1) ? live : ~0u;
   // the output of slices i >= 1 feeds only the adjoint propagation column
   // pass, which reads the live columns alone (slice 0 feeds the final one)
-  const unsigned any_o = wave_slots<N>(cmask), any_g = wave_slots<N>(gmask);
+  const unsigned any_o = wave_slots<N>(cmask), any_g = row_pairs<N>() ? wave_slots<N>(gmask) : 0u;
   float2 acc[E];
   const size_t orow = ((size_t)i * r.H + it.ny + y) * r.W + it.nx;
   // ePIE: object step divided by max sum_m |psi_i|^2, wave step by max |O_i|^2
