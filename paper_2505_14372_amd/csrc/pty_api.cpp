@@ -1594,7 +1594,10 @@ pty_status pty_group_reconstruct_step(pty_group* G, void* stream, const pty_grou
   const bool resident = !ordered && use_resident(items[0].ctx->strategy, N, 1);
   // The requests whose contexts run the chain kernels share one set of
   // launches, the others another, one after the other in the same workspace,
-  // so each request takes the path (and has the bits) of its steps alone.
+  // so each request takes the path (and has the bits) of its steps alone. The
+  // gradients of both sets wait in the contexts: every one is taken before the
+  // first update, since requests may share a state.
+  const auto on_chain = [&](const pty_group_item& it) { return use_chain(it.ctx) && !resident; };
   for (int chain = 1; chain >= 0; --chain) {
     LaunchCtx L{};
     L.stream = s;
@@ -1613,11 +1616,11 @@ pty_status pty_group_reconstruct_step(pty_group* G, void* stream, const pty_grou
     int item0 = 0, tile0 = 0, S_max = 0, M_max = 0, nq = 0;
     long long ck0 = 0;
     bool all_live = false;
-    std::vector<int> last_steps, mine;
+    std::vector<int> last_steps;
     for (int q = 0; q < n; ++q) {
       const pty_group_item& it = items[q];
       pty_ctx* c = it.ctx;
-      if ((use_chain(c) && !resident) != (chain == 1)) continue;
+      if (on_chain(it) != (chain == 1)) continue;
       const int M = c->g.n_modes, S = c->g.n_slices;
       ReqDev r = base_req(c);
       r.probe = (const float2*)it.state->probe;
@@ -1640,7 +1643,6 @@ pty_status pty_group_reconstruct_step(pty_group* G, void* stream, const pty_grou
       S_max = std::max(S_max, S);
       M_max = std::max(M_max, M);
       last_steps.push_back(S - 1);
-      mine.push_back(q);
       // a column block runs when any request has a live column in it
       all_live |= c->live_blocks == 0;
       L.col_live_blocks |= c->live_blocks;
@@ -1659,27 +1661,27 @@ pty_status pty_group_reconstruct_step(pty_group* G, void* stream, const pty_grou
     set_chain_final(L, N, true);
     run_chunk(L, N, S_max, last_steps, 1.f, 1, nullptr, nullptr);
     run_finish_backward(L, N, S_max, 1, 1.f);
-    // One optimiser launch for the requests without regularizers; one with them
-    // sees the state that the requests before it left, as one after the other.
-    OptBatch opt(N, s, G->tw);
-    for (int q : mine) {
-      pty_ctx* c = items[q].ctx;
-      const bool in_opt = chain && !c->reg_on;
-      if (c->reg_on) opt.flush();
-      if (!in_opt) probe_from_spectrum(N, chain, s, G->tw, c->gphat, c->gprobe, c->g.n_modes, false);
-      if (apply_cost_regularizers(c, s, items[q].state, items[q].loss, chain != 0) != PTY_OK) {
-        opt.flush();
-        G->err = c->err;
-        return PTY_EHIP;
-      }
-      opt.add(c, items[q].state, items[q].opt, in_opt);
-      if (c->con_on) {
-        opt.flush();
-        apply_constraints(c, s, items[q].state);
-      }
-    }
-    opt.flush();
   }
+  // One optimiser launch for the requests without regularizers; one with them
+  // sees the state that the requests before it left, as one after the other.
+  OptBatch opt(N, s, G->tw);
+  for (int q = 0; q < n; ++q) {
+    pty_ctx* c = items[q].ctx;
+    const bool chain = on_chain(items[q]), in_opt = chain && !c->reg_on;
+    if (c->reg_on) opt.flush();
+    if (!in_opt) probe_from_spectrum(N, chain, s, G->tw, c->gphat, c->gprobe, c->g.n_modes, false);
+    if (apply_cost_regularizers(c, s, items[q].state, items[q].loss, chain) != PTY_OK) {
+      opt.flush();
+      G->err = c->err;
+      return PTY_EHIP;
+    }
+    opt.add(c, items[q].state, items[q].opt, in_opt);
+    if (c->con_on) {
+      opt.flush();
+      apply_constraints(c, s, items[q].state);
+    }
+  }
+  opt.flush();
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) { G->err = hipGetErrorString(e); return PTY_EHIP; }
   return PTY_OK;

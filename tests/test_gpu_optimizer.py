@@ -123,3 +123,33 @@ def test_grouped_requests_that_share_a_state_update_it_in_turn(N):
         assert np.all(np.abs(after[var][0] - x[var][0]) <= 4 * tol[var][0]), var
         for k in (1, 2):
             assert np.all(np.abs(after[var][k] - x[var][k]) <= 2 * tol[var][k]), (var, k)
+
+
+@pytest.mark.parametrize("N,paths", [(64, ("auto", "two_pass")), (128, ("two_pass", "auto"))])
+def test_grouped_requests_of_other_paths_that_share_a_state(N, paths):
+    """The same when the requests of one state run on different kernels, in
+    either order: losses and gradients are those of the state before the step."""
+    c = _case(N)
+    d = c.device()
+    probs = [c.problem(), c.problem()]
+    for p, path in zip(probs, paths):
+        p.set_strategy(path)
+    batches = [d["batch"][:4].contiguous(), d["batch"][4:].contiguous()]
+    opt = api.Optimizer(kind="sgd", lr_object=1e-3, lr_probe=1e-3, lr_pos=1e-3)
+    st = api.ReconState(d["probe"].clone(), d["obj"].clone(), d["pos"].clone(), adam=False)
+    before = {v: _real(getattr(st, v)) for v, _ in VARS}
+    losses = [torch.zeros(1, dtype=torch.float64, device="cuda") for _ in probs]
+    grads = [p.loss_and_grad(st.probe, st.object, st.positions, d["pats"], b, dense_pos=True)
+             for p, b in zip(probs, batches)]
+    grp = api.Group(N, 9, 18, 36)
+    grp.step([(p, st, d["pats"], b, opt, loss) for p, b, loss in zip(probs, batches, losses)])
+    torch.cuda.synchronize()
+    for loss, g in zip(losses, grads):
+        assert loss.item() == g[0].item()
+    for k, (var, lr_name) in enumerate(VARS, 1):
+        lr, x, size = getattr(opt, lr_name), before[var], 0.0
+        for g in (_real(g[k]) for g in grads):
+            x, size = x - lr * g, size + np.abs(lr * g)
+        # a product and a difference are rounded for each request
+        tol = 2 * U * (np.abs(before[var]) + 2 * size)
+        assert np.all(np.abs(_real(getattr(st, var)) - x) <= tol), var
