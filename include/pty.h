@@ -435,7 +435,11 @@ void pty_destroy(pty_ctx* ctx);
  * S, object size, loss) in shared kernel launches. Entry waves are stored for
  * every slice (no recompute) in the group's workspace. A grouped step uses
  * the ordered object-gradient reduction when every context in it is set to
- * PTY_REDUCE_ORDERED, else that of PTY_REDUCE_ATOMIC. */
+ * PTY_REDUCE_ORDERED, else that of PTY_REDUCE_ATOMIC. Every gradient is taken
+ * before the first update; the updates follow in the order of the items.
+ * Items should not share a context: those that do add their object and
+ * position gradients up (with atomics), and each one's update takes the
+ * total; which item's probe gradient they all take is not defined. */
 typedef struct pty_group pty_group;
 
 typedef struct {

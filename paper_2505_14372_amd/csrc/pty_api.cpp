@@ -1595,10 +1595,20 @@ pty_status pty_group_reconstruct_step(pty_group* G, void* stream, const pty_grou
   // The requests whose contexts run the chain kernels share one set of
   // launches, the others another, one after the other in the same workspace,
   // so each request takes the path (and has the bits) of its steps alone. The
-  // gradients of both sets wait in the contexts: every one is taken before the
+  // gradients of every set wait in the contexts: every one is taken before the
   // first update, since requests may share a state.
-  const auto on_chain = [&](const pty_group_item& it) { return use_chain(it.ctx) && !resident; };
-  for (int chain = 1; chain >= 0; --chain) {
+  enum { kOnChain, kTwoPass, kShared, kSets };
+  int set[kMaxReqs];
+  for (int q = 0; q < n; ++q) {
+    set[q] = use_chain(items[q].ctx) && !resident ? kOnChain : kTwoPass;
+    // A context listed twice has one set of gradients for both entries: they are
+    // added up with atomics (a stored sum is written whole, so one entry's would
+    // be lost), and each entry's update takes the total.
+    for (int p = 0; p < n; ++p)
+      if (p != q && items[p].ctx == items[q].ctx && !resident) set[q] = kShared;
+  }
+  for (int k = 0; k < kSets; ++k) {
+    const int chain = k == kOnChain;
     LaunchCtx L{};
     L.stream = s;
     L.items = G->items;
@@ -1620,7 +1630,7 @@ pty_status pty_group_reconstruct_step(pty_group* G, void* stream, const pty_grou
     for (int q = 0; q < n; ++q) {
       const pty_group_item& it = items[q];
       pty_ctx* c = it.ctx;
-      if (on_chain(it) != (chain == 1)) continue;
+      if (set[q] != k) continue;
       const int M = c->g.n_modes, S = c->g.n_slices;
       ReqDev r = base_req(c);
       r.probe = (const float2*)it.state->probe;
@@ -1652,7 +1662,7 @@ pty_status pty_group_reconstruct_step(pty_group* G, void* stream, const pty_grou
     L.n_reqs = nq;
     L.n_items = item0;
     L.max_modes = M_max;
-    L.defer = !chain && !resident && store_contributions(ordered, N, M_max, item0);
+    L.defer = k == kTwoPass && !resident && store_contributions(ordered, N, M_max, item0);
     clear_grads(L, true);
     std::sort(last_steps.begin(), last_steps.end());
     last_steps.erase(std::unique(last_steps.begin(), last_steps.end()), last_steps.end());
@@ -1667,7 +1677,7 @@ pty_status pty_group_reconstruct_step(pty_group* G, void* stream, const pty_grou
   OptBatch opt(N, s, G->tw);
   for (int q = 0; q < n; ++q) {
     pty_ctx* c = items[q].ctx;
-    const bool chain = on_chain(items[q]), in_opt = chain && !c->reg_on;
+    const bool chain = set[q] == kOnChain, in_opt = chain && !c->reg_on;
     if (c->reg_on) opt.flush();
     if (!in_opt) probe_from_spectrum(N, chain, s, G->tw, c->gphat, c->gprobe, c->g.n_modes, false);
     if (apply_cost_regularizers(c, s, items[q].state, items[q].loss, chain) != PTY_OK) {

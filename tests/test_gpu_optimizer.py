@@ -153,3 +153,37 @@ def test_grouped_requests_of_other_paths_that_share_a_state(N, paths):
         # a product and a difference are rounded for each request
         tol = 2 * U * (np.abs(before[var]) + 2 * size)
         assert np.all(np.abs(_real(getattr(st, var)) - x) <= tol), var
+
+
+@pytest.mark.parametrize("N,strategy,reduction", [(64, "auto", "atomic"), (64, "auto", "ordered"),
+                                                  (128, "two_pass", "ordered"), (192, "auto", "atomic")])
+def test_grouped_entries_of_one_context_add_their_gradients(N, strategy, reduction):
+    """Two batches of one reconstruction through one context, beside another
+    reconstruction: object and position gradients are the sum over both, and each
+    entry's update takes it; the other one is not touched by it."""
+    c, other = _case(N), _case(N, seed=9)
+    d, e = c.device(), other.device()
+    prob, prob2 = c.problem(), other.problem()
+    for p in (prob, prob2):
+        p.set_strategy(strategy)
+        p.set_reduction(reduction)
+    opt = api.Optimizer(kind="sgd", lr_object=1e-3, lr_probe=0.0, lr_pos=1e-3)
+    make = lambda x: api.ReconState(x["probe"].clone(), x["obj"].clone(), x["pos"].clone(), adam=False)  # noqa: E731
+    st, alone, beside = make(d), make(e), make(e)
+    want = {v: _real(getattr(st, v)) for v in ("object", "positions")}
+    _, gO, _, gX = prob.loss_and_grad(st.probe, st.object, st.positions, d["pats"], d["batch"], dense_pos=True)
+    step = {"object": 2e-3 * _real(gO), "positions": 2e-3 * _real(gX)}
+    loss = lambda: torch.zeros(1, dtype=torch.float64, device="cuda")  # noqa: E731
+    prob2.reconstruct_step(alone, e["pats"], e["batch"], opt)
+    grp = api.Group(N, 18, 36, 72)
+    grp.step([(prob, st, d["pats"], d["batch"][:4].contiguous(), opt, loss()),
+              (prob2, beside, e["pats"], e["batch"], opt, loss()),
+              (prob, st, d["pats"], d["batch"][4:].contiguous(), opt, loss())])
+    torch.cuda.synchronize()
+    for v, delta in step.items():
+        got = _real(getattr(st, v)) - want[v]
+        # the parity bound of a gradient, and the rounding of the two updates
+        assert np.linalg.norm(got + delta) <= 1e-3 * np.linalg.norm(delta) + 4 * U * np.linalg.norm(want[v]), v
+    for v, _ in VARS:
+        a, b = _real(getattr(alone, v)), _real(getattr(beside, v))
+        assert np.array_equal(a, b), v
