@@ -531,7 +531,7 @@ void run_backward_chunk(const LaunchCtx& L, int N, int S_max, const std::vector<
       g.seg = sg;
       g.seg_len = k - 1;
       g.seg_base = i0 + 1;
-      { ProfScope q(P_OBJ_GATHER, L.stream); launch_finish(L, N, g, true, false, scale); }
+      { ProfScope q(P_OBJ_GATHER, L.stream); launch_finish(L, N, g, false, scale); }
       i1 = i0 - 1;
     }
     return;
@@ -639,7 +639,7 @@ void run_finish_backward(const LaunchCtx& L, int N, int S_max, int k, float scal
   FinishRun p{};
   p.slices = gather ? S_max : 0;
   ProfScope q(gather ? P_OBJ_GATHER : P_PROBE_GRAD, L.stream);
-  launch_finish(L, N, p, gather, true, scale);
+  launch_finish(L, N, p, true, scale);
 }
 
 pty_status check_call(pty_ctx* c, const void* probe, const void* object, const void* positions,
@@ -1404,6 +1404,7 @@ extern "C" pty_status pty_reconstruct_step(pty_ctx* c, void* stream, pty_state* 
     launch_fill(s, c->emax, (size_t)B * S * 2, 0.f);
   }
   run_fused(c, L, 1.f);
+  HIPCHECK(c, hipGetLastError());   // a refused launch leaves the state as it was
   // (a regularizer adds to the probe gradient before the update)
   const bool in_opt = L.chain && !c->reg_on;
   OptBatch opt(N, s, c->tw);
@@ -1477,6 +1478,7 @@ extern "C" pty_status pty_lsqml_step(pty_ctx* c, void* stream, pty_state* st, co
   }
   // the chain accumulates minus the summed directions: gobj = -D, gphat -> gprobe = -dP
   run_fused(c, L, 1.f);
+  HIPCHECK(c, hipGetLastError());   // a refused launch leaves the state as it was
   probe_from_spectrum(N, false, s, c->tw, c->gphat, c->gprobe, M, false);
   {
     ProfScope p(P_OPTIM, s);
@@ -1672,6 +1674,8 @@ pty_status pty_group_reconstruct_step(pty_group* G, void* stream, const pty_grou
     run_chunk(L, N, S_max, last_steps, 1.f, 1, nullptr, nullptr);
     run_finish_backward(L, N, S_max, 1, 1.f);
   }
+  hipError_t e = hipGetLastError();   // a refused launch leaves the states as they were
+  if (e != hipSuccess) { G->err = hipGetErrorString(e); return PTY_EHIP; }
   // One optimiser launch for the requests without regularizers; one with them
   // sees the state that the requests before it left, as one after the other.
   OptBatch opt(N, s, G->tw);
@@ -1692,7 +1696,7 @@ pty_status pty_group_reconstruct_step(pty_group* G, void* stream, const pty_grou
     }
   }
   opt.flush();
-  hipError_t e = hipGetLastError();
+  e = hipGetLastError();
   if (e != hipSuccess) { G->err = hipGetErrorString(e); return PTY_EHIP; }
   return PTY_OK;
 }

@@ -604,9 +604,13 @@ struct Chain {
   }
   template <int WHAT>
   static void run_as(const LaunchCtx& L, const ChainRun& p) {
-    hipLaunchKernelGGL((k_chain<N, WHAT>), dim3(8 * ((L.n_items + 7) / 8) * L.max_modes), dim3(Ch<N>::T), 0, L.stream,
-                       L.items, L.reqs, L.ws, static_cast<float2*>(L.ck), L.ramps, tab(L), L.loss_part, L.pos_part,
-                       L.flags, L.item_off, L.n_items, L.max_modes, p);
+    const int most = chain_items(L.max_modes, Ch<N>::T);
+    for (int at = 0; at < L.n_items; at += most) {
+      const int n = std::min(L.n_items - at, most);
+      hipLaunchKernelGGL((k_chain<N, WHAT>), dim3(8 * ((n + 7) / 8) * L.max_modes), dim3(Ch<N>::T), 0, L.stream,
+                         L.items, L.reqs, L.ws, static_cast<float2*>(L.ck), L.ramps, tab(L), L.loss_part, L.pos_part,
+                         L.flags, L.item_off + at, n, L.max_modes, p);
+    }
   }
   static void run(const LaunchCtx& L, ChainRun p) {
     bool far = false;   // a far-field launch between the chains

@@ -10,11 +10,12 @@
 
 namespace pty {
 
-constexpr int kTY = 4;            // rows of an object-gradient tile
+constexpr int kTY = kFinishTY;    // rows of an object-gradient tile
 constexpr int kProbeSplit = 16;   // interleaved sums of the probe-spectrum gradient
 
-// The work is split over workgroup ranges; every sum has a fixed order, so
-// repeated calls give the same bits.
+// The work is split over workgroup ranges, each request's by its own sizes (by
+// the largest of a group's the product of all the maxima can exceed what a launch
+// takes); every sum has a fixed order, so repeated calls give the same bits.
 //   - object gradient (stored contributions): one workgroup per 4 x 64 tile and
 //     slice (object_sum). The chain kernels leave one contribution per mode, the
 //     two-pass kernels one per position (already scaled). With one list of
@@ -32,19 +33,49 @@ template <int N, bool CHAIN>
 __global__ __launch_bounds__(512) void k_finish(const Item* __restrict__ items, const ReqTable reqs,
                                                 const float2* __restrict__ ws, const float2* __restrict__ ck,
                                                 const float2* __restrict__ ramps, const float* __restrict__ loss_part,
-                                                const float* __restrict__ pos_part, int n_items, int max_modes,
-                                                float scale, FinishRun p) {
+                                                const float* __restrict__ pos_part, int n_items, float scale,
+                                                FinishRun p) {
   constexpr int NBLK = N / 32;
   __shared__ float2 part[7 * kTY * 64];
   static_assert(7 * kTY * 64 >= 512, "one value per thread");
   const int t = threadIdx.x;
-  int g = blockIdx.x;
-  const int n_gather = p.n_reqs * p.slices * p.ty * p.tx;
-  if (g < n_gather) {
-    const int tx = g % p.tx, ty = (g / p.tx) % p.ty, s = (g / (p.tx * p.ty)) % p.slices, q = g / (p.tx * p.ty * p.slices);
-    const ReqDev& r = reqs.r[q];
-    const int i = p.lo + s, x0 = tx * 64, y0 = ty * kTY, x = x0 + (t & 63);
-    if (i >= r.S || !r.gobj || x0 >= r.W || y0 >= r.H) return;
+  unsigned g = blockIdx.x + p.first;
+  const int q = finish_request(p, g);
+  g -= p.at[q];
+  if (q == p.n_reqs) {
+    // per item: dL/dX = 2 pi scale times the sum over modes (and column blocks) of
+    // the partials; to g_pos[local] and / or added to a dense [J][2] gradient
+    const int b = (int)g * 512 + t;
+    if (b >= n_items) return;
+    const Item it = items[b];
+    const ReqDev& r = reqs.r[it.req];
+    float g0 = 0.f, g1 = 0.f;
+    if (it.valid)
+      for (int m = 0; m < r.M; ++m)
+        for (int k = 0; k < (CHAIN ? 1 : NBLK); ++k) {
+          const float* pp = pos_part + ((size_t)(it.tile0 + m) * NBLK + k) * 2;
+          g0 += pp[0];
+          g1 += pp[1];
+        }
+    const float f = 6.283185307179586f * adj_scale(r, scale);
+    g0 *= f;
+    g1 *= f;
+    const int local = b - r.item0;
+    if (r.gpos) {
+      if (r.accumulate) { r.gpos[2 * local] += g0; r.gpos[2 * local + 1] += g1; }
+      else { r.gpos[2 * local] = g0; r.gpos[2 * local + 1] = g1; }
+    }
+    if (r.gpos_dense && it.valid) {
+      atomicAdd(r.gpos_dense + 2 * it.j, g0);
+      atomicAdd(r.gpos_dense + 2 * it.j + 1, g1);
+    }
+    return;
+  }
+  const ReqDev& r = reqs.r[q];
+  const FinishParts parts = finish_parts(p, r, N);
+  if (g < parts.gather) {
+    const int i = p.lo + (int)(g / (parts.tx * parts.ty)), x0 = (int)(g % parts.tx) * 64;
+    const int y0 = (int)((g / parts.tx) % parts.ty) * kTY, x = x0 + (t & 63);
     const bool sg = p.seg && i % r.ck_every != 0;
     const float2* src = sg ? p.seg + (size_t)(i - p.seg_base) * N * N
                            : ck + (size_t)(i / r.ck_every) * r.n_items * r.M * N * N;
@@ -67,13 +98,10 @@ __global__ __launch_bounds__(512) void k_finish(const Item* __restrict__ items, 
     }
     return;
   }
-  g -= n_gather;
-  const int n_probe = p.n_reqs * max_modes * (N * N / 32);
-  if (g < n_probe) {
-    const ReqDev& r = reqs.r[g / (max_modes * (N * N / 32))];
-    const int m = (g / (N * N / 32)) % max_modes;
-    if (m >= r.M || !r.gphat) return;
-    const int px = (g % (N * N / 32)) * 32 + (t & 31), s = t >> 5;
+  g -= parts.gather;
+  if (g < parts.probe) {
+    const int m = (int)(g / (N * N / kFinishPX));
+    const int px = (int)(g % (N * N / kFinishPX)) * kFinishPX + (t & 31), s = t >> 5;
     const int ux = CHAIN ? px / N : mem_column<N>(px % N), uy = CHAIN ? px % N : px / N;
     float2 acc = make_float2(0.f, 0.f);
     if (!CHAIN && r.chain_final) {
@@ -97,81 +125,40 @@ __global__ __launch_bounds__(512) void k_finish(const Item* __restrict__ items, 
     }
     return;
   }
-  g -= n_probe;
-  if (g < p.n_reqs) {
-    const ReqDev& r = reqs.r[g];
-    if (!r.loss_out) return;
-    double* red = reinterpret_cast<double*>(part);
-    double acc = 0.0;
-    const float* lp = loss_part + (size_t)r.item0 * NBLK;
-    for (int e = t; e < r.n_items * NBLK; e += 512) acc += (double)lp[e];
-    red[t] = acc;
+  // the loss
+  double* red = reinterpret_cast<double*>(part);
+  double acc = 0.0;
+  const float* lp = loss_part + (size_t)r.item0 * NBLK;
+  for (int e = t; e < r.n_items * NBLK; e += 512) acc += (double)lp[e];
+  red[t] = acc;
+  __syncthreads();
+  for (int s = 256; s > 0; s >>= 1) {
+    if (t < s) red[t] += red[t + s];
     __syncthreads();
-    for (int s = 256; s > 0; s >>= 1) {
-      if (t < s) red[t] += red[t + s];
-      __syncthreads();
-    }
-    if (t == 0) *r.loss_out = red[0];
-    return;
   }
-  // per item: dL/dX = 2 pi scale times the sum over modes (and column blocks) of
-  // the partials; to g_pos[local] and / or added to a dense [J][2] gradient
-  g -= p.n_reqs;
-  const int b = g * 512 + t;
-  if (b >= n_items) return;
-  const Item it = items[b];
-  const ReqDev& r = reqs.r[it.req];
-  float g0 = 0.f, g1 = 0.f;
-  if (it.valid)
-    for (int m = 0; m < r.M; ++m)
-      for (int k = 0; k < (CHAIN ? 1 : NBLK); ++k) {
-        const float* pp = pos_part + ((size_t)(it.tile0 + m) * NBLK + k) * 2;
-        g0 += pp[0];
-        g1 += pp[1];
-      }
-  const float f = 6.283185307179586f * adj_scale(r, scale);
-  g0 *= f;
-  g1 *= f;
-  const int local = b - r.item0;
-  if (r.gpos) {
-    if (r.accumulate) { r.gpos[2 * local] += g0; r.gpos[2 * local + 1] += g1; }
-    else { r.gpos[2 * local] = g0; r.gpos[2 * local + 1] = g1; }
-  }
-  if (r.gpos_dense && it.valid) {
-    atomicAdd(r.gpos_dense + 2 * it.j, g0);
-    atomicAdd(r.gpos_dense + 2 * it.j + 1, g1);
-  }
+  if (t == 0) *r.loss_out = red[0];
 }
 
 template <int N, bool CHAIN>
-static void finish(const LaunchCtx& L, FinishRun p, bool gather, bool rest, float scale) {
-  p.n_reqs = L.n_reqs;
-  p.tx = p.ty = 0;
-  if (gather)
-    for (int q = 0; q < L.n_reqs; ++q) {
-      if (!L.reqs.r[q].gobj) continue;
-      p.tx = std::max(p.tx, (L.reqs.r[q].W + 63) / 64);
-      p.ty = std::max(p.ty, (L.reqs.r[q].H + kTY - 1) / kTY);
-    }
-  size_t blocks = (size_t)p.n_reqs * p.slices * p.ty * p.tx;
-  if (rest) blocks += (size_t)p.n_reqs * L.max_modes * (N * N / 32) + p.n_reqs + (L.n_items + 511) / 512;
-  if (blocks == 0) return;
-  hipLaunchKernelGGL((k_finish<N, CHAIN>), dim3((unsigned)blocks), dim3(512), 0, L.stream, L.items, L.reqs, L.ws,
-                     static_cast<const float2*>(L.ck), L.ramps, L.loss_part, L.pos_part, L.n_items, L.max_modes, scale,
-                     p);
+static void finish(const LaunchCtx& L, FinishRun p, bool rest, float scale) {
+  const unsigned blocks = finish_layout(p, L.reqs, L.n_reqs, L.n_items, N, rest);
+  for (p.first = 0; p.first < blocks; p.first += kFinishBlocks)
+    hipLaunchKernelGGL((k_finish<N, CHAIN>), dim3(std::min(blocks - p.first, kFinishBlocks)), dim3(512), 0, L.stream,
+                       L.items, L.reqs, L.ws, static_cast<const float2*>(L.ck), L.ramps, L.loss_part, L.pos_part,
+                       L.n_items, scale, p);
 }
 
-void launch_finish(const LaunchCtx& L, int N, const FinishRun& p, bool gather, bool rest, float scale) {
+void launch_finish(const LaunchCtx& L, int N, FinishRun p, bool rest, float scale) {
   if (L.chain) {
-    if (N == 64) finish<64, true>(L, p, gather, rest, scale);
-    else finish<128, true>(L, p, gather, rest, scale);
+    if (N == 64) finish<64, true>(L, p, rest, scale);
+    else finish<128, true>(L, p, rest, scale);
     return;
   }
   switch (N) {
-    case 64: finish<64, false>(L, p, gather, rest, scale); break;
-    case 128: finish<128, false>(L, p, gather, rest, scale); break;
-    case 192: finish<192, false>(L, p, gather, rest, scale); break;
-    default: finish<256, false>(L, p, gather, rest, scale); break;
+    case 64: finish<64, false>(L, p, rest, scale); break;
+    case 128: finish<128, false>(L, p, rest, scale); break;
+    case 192: finish<192, false>(L, p, rest, scale); break;
+    default: finish<256, false>(L, p, rest, scale); break;
   }
 }
 

@@ -292,12 +292,59 @@ void launch_lsq_probe(hipStream_t s, float2* P, const float2* g, const float* wp
 // Last sums of the adjoint (pty_finish.hip): gather: the object gradient of slices lo ..
 // lo + slices - 1 from stored contributions; rest: probe spectrum, loss, positions.
 struct FinishRun {
-  int lo, slices;           // slices of the object-gradient sum
+  int lo, slices;           // slices of the object-gradient sum (0: none)
   const float2* seg;        // as in ChainRun
   int seg_len, seg_base;
-  int n_reqs, tx, ty;       // (set by the launcher)
+  // (set by finish_layout)
+  int rest, n_reqs;
+  unsigned at[kMaxReqs + 1];   // first workgroup of each request, then of the positions
+  unsigned first;              // first workgroup of this launch
 };
-void launch_finish(const LaunchCtx& L, int N, const FinishRun& p, bool gather, bool rest, float scale);
+constexpr int kFinishTY = 4;      // rows of an object-gradient tile
+constexpr int kFinishPX = 32;     // probe pixels of a workgroup
+// HIP takes fewer than 2^32 threads in a grid dimension: workgroups of 512 in one launch
+constexpr unsigned kFinishBlocks = (1u << 23) - 1;
+
+// Workgroups of a request: object-gradient tiles (tx x ty of each slice), probe
+// pixels, loss.
+struct FinishParts {
+  unsigned tx, ty, gather, probe, loss;
+};
+__host__ __device__ inline FinishParts finish_parts(const FinishRun& p, const ReqDev& r, int N) {
+  FinishParts f{};
+  f.tx = (unsigned)(r.W + 63) / 64;
+  f.ty = (unsigned)(r.H + kFinishTY - 1) / kFinishTY;
+  const int slices = r.S - p.lo < p.slices ? r.S - p.lo : p.slices;
+  if (r.gobj && slices > 0) f.gather = (unsigned)slices * f.ty * f.tx;
+  if (p.rest && r.gphat) f.probe = (unsigned)r.M * (unsigned)(N * N / kFinishPX);
+  if (p.rest && r.loss_out) f.loss = 1;
+  return f;
+}
+// Gives each request workgroups for its own sizes, and the position gradients
+// theirs; returns how many there are.
+inline unsigned finish_layout(FinishRun& p, const ReqTable& reqs, int n_reqs, int n_items, int N, bool rest) {
+  unsigned g = 0;
+  p.rest = rest ? 1 : 0;
+  p.n_reqs = n_reqs;
+  for (int q = 0; q <= kMaxReqs; ++q) p.at[q] = ~0u;
+  for (int q = 0; q < n_reqs; ++q) {
+    p.at[q] = g;
+    const FinishParts f = finish_parts(p, reqs.r[q], N);
+    g += f.gather + f.probe + f.loss;
+  }
+  p.at[n_reqs] = g;
+  return rest ? g + (unsigned)(n_items + 511) / 512 : g;
+}
+// Request of workgroup g (n_reqs: the positions).
+__host__ __device__ inline int finish_request(const FinishRun& p, unsigned g) {
+  int q = -1;
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+#endif
+  for (int k = 0; k <= kMaxReqs; ++k) q += p.at[k] <= g ? 1 : 0;
+  return q;
+}
+void launch_finish(const LaunchCtx& L, int N, FinishRun p, bool rest, float scale);
 
 // Chain kernels (pty_chain.hip): every slice of a tile in one launch.
 enum { kForward = 1, kRecompute = 2, kFar = 4, kSeed = 8, kAdjoint = 16, kFirst = 32 };   // see k_chain
@@ -310,6 +357,12 @@ struct ChainRun {
   int seg_len, seg_base;    // slice i at slot i - seg_base of [tiles][seg_len][N][N]
 };
 bool chain_size(int N);
+// Items of one launch of T threads a tile, eights of them times the most modes of
+// any request: HIP takes fewer than 2^32 threads in a grid dimension.
+inline int chain_items(int max_modes, int T) {
+  const long long n = ((1ll << 32) - 1) / T / max_modes / 8 * 8;
+  return n < 8 ? 8 : n > kMaxItems + 1 ? kMaxItems + 1 : (int)n;
+}
 void launch_chain_begin(const LaunchCtx& L, int N);
 void launch_chain(const LaunchCtx& L, int N, const ChainRun& p);
 // dst[k] = scale F^-1(src[k]) (+ dst[k] if accumulate) of the n[k] N x N tiles of each entry

@@ -1,0 +1,96 @@
+// Workgroups of the launches whose grids grow with the requests of a group
+// (finish_layout, chain_items), taken through every workgroup on the host: each
+// request gets those of its own sizes, every launch stays under the threads a
+// grid dimension takes, and together they cover the work once.
+#include <cstdio>
+#include <vector>
+
+#include "pty_internal.h"
+
+using namespace pty;
+
+static int bad = 0;
+static void need(bool ok, const char* what) {
+  if (!ok) { std::printf("%s\n", what); ++bad; }
+}
+
+static ReqDev request(int M, int S, int H, int W, int n_items) {
+  static float2 some;
+  static double loss;
+  ReqDev r{};
+  r.M = M;
+  r.S = S;
+  r.H = H;
+  r.W = W;
+  r.n_items = n_items;
+  r.gobj = r.gphat = &some;
+  r.loss_out = &loss;
+  return r;
+}
+
+// Walks the launches; returns how many there were.
+static int walk(const std::vector<ReqDev>& rs, int N, int lo, int slices, bool rest, unsigned long long want) {
+  ReqTable t{};
+  int n_items = 0;
+  for (size_t q = 0; q < rs.size(); ++q) {
+    t.r[q] = rs[q];
+    t.r[q].item0 = n_items;
+    n_items += rs[q].n_items;
+  }
+  FinishRun p{};
+  p.lo = lo;
+  p.slices = slices;
+  const unsigned blocks = finish_layout(p, t, (int)rs.size(), n_items, N, rest);
+  need(blocks == want, "workgroups of the request sizes");
+  int launches = 0;
+  unsigned next = 0;
+  for (p.first = 0; p.first < blocks; p.first += kFinishBlocks, ++launches) {
+    const unsigned n = blocks - p.first < kFinishBlocks ? blocks - p.first : kFinishBlocks;
+    need((unsigned long long)n * 512 < (1ull << 32), "threads of a launch");
+    for (unsigned g = p.first; g < p.first + n; ++g) {
+      const int q = finish_request(p, g);
+      if (q < 0 || q > (int)rs.size()) { need(false, "a workgroup of no request"); return launches; }
+      need(g == next++, "workgroups in turn");
+      const unsigned own = g - p.at[q];
+      if (q == (int)rs.size()) {
+        need(rest && (int)own * 512 < n_items, "positions");
+        continue;
+      }
+      const FinishParts f = finish_parts(p, t.r[q], N);
+      if (own >= f.gather + f.probe + f.loss) { need(false, "past the request's work"); return launches; }
+    }
+  }
+  need(next == blocks, "the last workgroup");
+  return launches;
+}
+
+int main() {
+  auto tiles = [](unsigned long long S, unsigned long long H, unsigned long long W) { return S * ((H + 3) / 4) * ((W + 63) / 64); };
+  // sixteen requests, one with a large object: by the largest of each size they
+  // would need 16 * 30 * 529 * 34 = 8633280 workgroups for the object alone
+  std::vector<ReqDev> group{request(1, 30, 2116, 2116, 9)};
+  unsigned long long want = tiles(30, 2116, 2116) + 128 + 1;
+  for (int q = 1; q < 16; ++q) {
+    group.push_back(request(q % 3 + 1, 1 + q % 2, 64 + q, 70, 4 + q));
+    want += tiles(1 + q % 2, 64 + q, 70) + 128 * (q % 3 + 1) + 1;
+  }
+  need(walk(group, 64, 0, 30, true, want + 1) == 1, "one launch for the group");
+  need(walk(group, 64, 0, 30, false, want - 16 - 128 * (1 + 30)) == 1, "the object alone");
+  // an object of 2^31 values
+  need(walk({request(1, 2, 32768, 32768, 100)}, 64, 0, 2, true, tiles(2, 32768, 32768) + 128 + 1 + 1) == 2, "two launches");
+  // a segment of slices, past the end of a shallower request; nothing to sum
+  need(walk({request(2, 7, 200, 300, 5)}, 128, 6, 3, false, tiles(1, 200, 300)) == 1, "the last segment");
+  need(walk({request(2, 7, 200, 300, 5)}, 128, 0, 0, true, 2 * 512 + 1 + 1) == 1, "no object gradient");
+  ReqDev no = request(1, 3, 100, 100, 600);
+  no.gobj = no.gphat = nullptr;
+  no.loss_out = nullptr;
+  need(walk({no}, 64, 0, 3, true, 2) == 1, "positions alone");
+  for (int T : {256, 512})
+    for (int M : {1, 3, 8, 127, 128, 300, 65535}) {
+      const int n = chain_items(M, T);
+      need(n >= 8 && n % 8 == 0 && (unsigned long long)n * M * T < (1ull << 32), "threads of a chain launch");
+      need(n > kMaxItems || (unsigned long long)(n + 8) * M * T >= (1ull << 32), "no more chain launches than needed");
+    }
+  if (!bad) std::printf("ok\n");
+  return bad ? 1 : 0;
+}

@@ -128,3 +128,34 @@ def test_grouped_step_of_mixed_paths_gives_the_single_step_bits():
         assert alone.item() == loss.item()
         for f in ("object", "probe", "positions"):
             assert torch.equal(getattr(st[0], f), getattr(st[1], f)), f
+
+
+@pytest.mark.parametrize("strategy", ["auto", "two_pass"])
+def test_sixteen_requests_with_one_large_object(strategy):
+    """One object of 30 slices of 2116 x 2116 beside fifteen small ones: each
+    request takes workgroups for its own sizes (for sixteen of the largest a
+    launch would need more threads than it can have), and each has the bits of
+    its step alone."""
+    from paper_2505_14372_amd import api
+    opt = api.Optimizer(kind="sgd", lr_object=1e-3, lr_probe=1e-3, lr_pos=1e-3)
+    big = _case(64, 1, 30, 4)
+    big.H = big.W = 2116
+    d = big.device()
+    d["obj"] = torch.polar(torch.ones((30, 2116, 2116), device="cuda"), 0.1 * torch.rand((30, 2116, 2116), device="cuda"))
+    d["pos"] += torch.tensor([2000.0, 1900.0], device="cuda")
+    pairs = [(big, d)] + [(c, c.device()) for c in (_case(64, 1, 1, 4, seed=40 + q) for q in range(15))]
+    entries, alone = [], []
+    for c, d in pairs:
+        prob = c.problem()
+        prob.set_strategy(strategy)
+        prob.set_reduction("ordered")
+        one, many = (api.ReconState(d["probe"].clone(), d["obj"].clone(), d["pos"].clone(), adam=False) for _ in range(2))
+        alone.append((one, prob.reconstruct_step(one, d["pats"], d["batch"], opt)))
+        entries.append((prob, many, d["pats"], d["batch"], opt, torch.zeros(1, dtype=torch.float64, device="cuda")))
+    assert not torch.equal(alone[0][0].object, pairs[0][1]["obj"])
+    api.Group(64, 64, 64, 15 * 4 + 30 * 4).step(entries)
+    torch.cuda.synchronize()
+    for (one, loss), entry in zip(alone, entries):
+        assert loss.item() == entry[5].item()
+        for f in ("object", "probe", "positions"):
+            assert torch.equal(getattr(one, f), getattr(entry[1], f)), f
