@@ -289,6 +289,27 @@ void launch_lsq_object(hipStream_t s, float2* O, const float2* g, const float* w
 void launch_lsq_probe(hipStream_t s, float2* P, const float2* g, const float* wp, float* cur, const float* prev,
                       int M, int N2, float delta, double gamma, float beta, double* alpha);
 
+// Is an object gradient summed strip by strip (k_object_strips), where `items`
+// windows with `parts` contributions each lie on an H x W object and `slices` of it
+// are summed? A workgroup per tile (object_sum) costs about 3 ns of a launch however
+// little lies on its 4 x 64 values; a wave per strip less, but it adds the strip's
+// contributions alone. So strips are taken where there are enough to fill the GPU,
+// and few contributions over a value for their number. Over 300 calls (64, 128 and
+// 256 wide windows, 1 - 6 modes, 1 and 6 slices, 8 - 512 positions on objects of 128 to
+// 2000 rows) this line is within 0.3% of the better one on average; loss and
+// gradients of one mode, 64 x 64, 16 positions on 2048 x 2048, tiles against strips:
+// 8 slices 541 -> 179 us, one 95 -> 58; 128 positions of two modes, 6 slices, 128 x 128 on
+// 800 x 800 (6.6 contributions over a value, 3900 strips), kept on tiles: 498 against 522;
+// 128 half-stored positions, 6 slices summed one by one, 64 x 64 on 1536 x 1536 (2304 strips),
+// kept on tiles: 396 against 431.
+// A value's sum is the same bits either way.
+constexpr int kStripRows = 16;
+__host__ __device__ inline bool sum_in_strips(int N, long long items, int parts, int H, int W, int slices) {
+  const long long strips = (long long)slices * ((H + kStripRows - 1) / kStripRows) * ((W + 63) / 64);
+  const long long over = items * parts * N * N, values = (long long)H * W;   // contributions over a value: over / values
+  return strips >= 3000 && over < 16 * values && over * 700 / strips < values;
+}
+
 // Last sums of the adjoint (pty_finish.hip): gather: the object gradient of slices lo ..
 // lo + slices - 1 from stored contributions; rest: probe spectrum, loss, positions.
 struct FinishRun {
@@ -297,6 +318,7 @@ struct FinishRun {
   int seg_len, seg_base;
   // (set by finish_layout)
   int rest, n_reqs;
+  unsigned strips;             // requests (bits) whose object gradient is summed in strips
   unsigned at[kMaxReqs + 1];   // first workgroup of each request, then of the positions
   unsigned first;              // first workgroup of this launch
 };
@@ -305,31 +327,36 @@ constexpr int kFinishPX = 32;     // probe pixels of a workgroup
 // HIP takes fewer than 2^32 threads in a grid dimension: workgroups of 512 in one launch
 constexpr unsigned kFinishBlocks = (1u << 23) - 1;
 
-// Workgroups of a request: object-gradient tiles (tx x ty of each slice), probe
-// pixels, loss.
+// Workgroups of a request: object-gradient tiles (tx x ty of each slice; none where
+// the sum is taken in strips), probe pixels, loss.
 struct FinishParts {
   unsigned tx, ty, gather, probe, loss;
 };
-__host__ __device__ inline FinishParts finish_parts(const FinishRun& p, const ReqDev& r, int N) {
+__host__ __device__ inline FinishParts finish_parts(const FinishRun& p, const ReqDev& r, int q, int N) {
   FinishParts f{};
   f.tx = (unsigned)(r.W + 63) / 64;
   f.ty = (unsigned)(r.H + kFinishTY - 1) / kFinishTY;
   const int slices = r.S - p.lo < p.slices ? r.S - p.lo : p.slices;
-  if (r.gobj && slices > 0) f.gather = (unsigned)slices * f.ty * f.tx;
+  if (r.gobj && slices > 0 && !((p.strips >> q) & 1u)) f.gather = (unsigned)slices * f.ty * f.tx;
   if (p.rest && r.gphat) f.probe = (unsigned)r.M * (unsigned)(N * N / kFinishPX);
   if (p.rest && r.loss_out) f.loss = 1;
   return f;
 }
 // Gives each request workgroups for its own sizes, and the position gradients
-// theirs; returns how many there are.
-inline unsigned finish_layout(FinishRun& p, const ReqTable& reqs, int n_reqs, int n_items, int N, bool rest) {
+// theirs; returns how many there are. chain: one contribution per mode.
+inline unsigned finish_layout(FinishRun& p, const ReqTable& reqs, int n_reqs, int n_items, int N, bool chain,
+                              bool rest) {
   unsigned g = 0;
   p.rest = rest ? 1 : 0;
   p.n_reqs = n_reqs;
+  p.strips = 0;
   for (int q = 0; q <= kMaxReqs; ++q) p.at[q] = ~0u;
   for (int q = 0; q < n_reqs; ++q) {
+    const ReqDev& r = reqs.r[q];
+    const int slices = r.S - p.lo < p.slices ? r.S - p.lo : p.slices;
+    if (r.gobj && slices > 0 && sum_in_strips(N, r.n_items, chain ? r.M : 1, r.H, r.W, slices)) p.strips |= 1u << q;
     p.at[q] = g;
-    const FinishParts f = finish_parts(p, reqs.r[q], N);
+    const FinishParts f = finish_parts(p, r, q, N);
     g += f.gather + f.probe + f.loss;
   }
   p.at[n_reqs] = g;
@@ -345,6 +372,23 @@ __host__ __device__ inline int finish_request(const FinishRun& p, unsigned g) {
   return q;
 }
 void launch_finish(const LaunchCtx& L, int N, FinishRun p, bool rest, float scale);
+
+// Object gradient of one request from stored contributions, strip by strip.
+struct StripRun {
+  const float2* src;        // contribution `part` of item b in slice i: tile index + part * step, index:
+  const float* wsrc;        // LSQML illuminations, stored alike, or null
+  int scratch;              // 1: b (src is the scratch area of one slice), 0: the item's
+                            // checkpoint or segment tile (as in k_finish)
+  const float2* seg;
+  int seg_len, seg_base;
+  int parts;                // contributions of an item
+  int lo, slices;           // slices lo .. lo + slices - 1
+  int item_lo, item_hi;     // items of the launch
+  int add;                  // add to the gradient instead of writing it
+  int scaled;               // times the adjoint scale (two-pass contributions have it)
+  float scale;
+};
+void launch_object_strips(hipStream_t s, int N, const Item* items, const ReqDev& r, StripRun p);
 
 // Chain kernels (pty_chain.hip): every slice of a tile in one launch.
 enum { kForward = 1, kRecompute = 2, kFar = 4, kSeed = 8, kAdjoint = 16, kFirst = 32 };   // see k_chain

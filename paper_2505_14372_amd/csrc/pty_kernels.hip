@@ -29,6 +29,7 @@
 
 #include <hip/hip_fp16.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "pty_device.hpp"
@@ -898,8 +899,8 @@ __global__ void k_loss_reduce(const ReqTable reqs, const float* __restrict__ los
 
 // Ordered object-gradient reduction for slice i = S - 1 - step of every
 // request, where the contributions of a slice wait in the scratch area (half
-// checkpoints, recomputed segments, LSQML): one workgroup per 4 x 64 tile of the
-// slice adds their sum (object_sum) to the gradient, and with WS that of the
+// checkpoints, recomputed segments, LSQML) and sum_in_strips does not hold: one
+// workgroup per 4 x 64 tile of the slice adds their sum (object_sum) to the gradient, and with WS that of the
 // stored illuminations (wscr) to r.wsum.
 constexpr int kGatherTY = 4;
 template <int N, bool WS>
@@ -1129,6 +1130,20 @@ struct Launch {
     }
   }
   static void obj_gather(const LaunchCtx& L, int step, int max_h, int max_w) {
+    if (L.n_reqs == 1 && sum_in_strips(N, L.n_items, 1, max_h, max_w, 1)) {
+      const ReqDev& r = L.reqs.r[0];
+      const int i = r.S - 1 - step;
+      if (i < 0 || !r.gobj) return;
+      StripRun o{};
+      o.src = L.cscr;
+      o.wsrc = L.wsum ? L.wscr : nullptr;
+      o.scratch = o.parts = o.slices = o.add = 1;
+      o.lo = i;
+      o.item_lo = std::max(r.item0, L.item_off);
+      o.item_hi = std::min(r.item0 + r.n_items, L.item_off + L.n_items);
+      launch_object_strips(L.stream, N, L.items, r, o);
+      return;
+    }
     dim3 g((max_w + 63) / 64, (max_h + kGatherTY - 1) / kGatherTY, L.n_reqs);
     if (L.wsum && L.wscr)
       hipLaunchKernelGGL((k_obj_gather<N, true>), g, dim3(512), 0, L.stream, L.items, L.reqs, L.cscr,

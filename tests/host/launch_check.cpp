@@ -40,7 +40,7 @@ static int walk(const std::vector<ReqDev>& rs, int N, int lo, int slices, bool r
   FinishRun p{};
   p.lo = lo;
   p.slices = slices;
-  const unsigned blocks = finish_layout(p, t, (int)rs.size(), n_items, N, rest);
+  const unsigned blocks = finish_layout(p, t, (int)rs.size(), n_items, N, true, rest);
   need(blocks == want, "workgroups of the request sizes");
   int launches = 0;
   unsigned next = 0;
@@ -56,7 +56,7 @@ static int walk(const std::vector<ReqDev>& rs, int N, int lo, int slices, bool r
         need(rest && (int)own * 512 < n_items, "positions");
         continue;
       }
-      const FinishParts f = finish_parts(p, t.r[q], N);
+      const FinishParts f = finish_parts(p, t.r[q], q, N);
       if (own >= f.gather + f.probe + f.loss) { need(false, "past the request's work"); return launches; }
     }
   }
@@ -69,15 +69,27 @@ int main() {
   // sixteen requests, one with a large object: by the largest of each size they
   // would need 16 * 30 * 529 * 34 = 8633280 workgroups for the object alone
   std::vector<ReqDev> group{request(1, 30, 2116, 2116, 9)};
-  unsigned long long want = tiles(30, 2116, 2116) + 128 + 1;
+  need(sum_in_strips(64, 9, 1, 2116, 2116, 30), "few windows on a large object");
+  unsigned long long want = 128 + 1;   // (its sum is taken in strips)
   for (int q = 1; q < 16; ++q) {
     group.push_back(request(q % 3 + 1, 1 + q % 2, 64 + q, 70, 4 + q));
     want += tiles(1 + q % 2, 64 + q, 70) + 128 * (q % 3 + 1) + 1;
   }
   need(walk(group, 64, 0, 30, true, want + 1) == 1, "one launch for the group");
-  need(walk(group, 64, 0, 30, false, want - 16 - 128 * (1 + 30)) == 1, "the object alone");
-  // an object of 2^31 values
-  need(walk({request(1, 2, 32768, 32768, 100)}, 64, 0, 2, true, tiles(2, 32768, 32768) + 128 + 1 + 1) == 2, "two launches");
+  need(walk(group, 64, 0, 30, false, want - 16 - 128 * (1 + 30)) == 1, "the objects alone");
+  // the same object under many windows, and 3 x 10^9 values
+  group[0].n_items = 20000;
+  want += tiles(30, 2116, 2116);
+  need(walk(group, 64, 0, 30, true, want + (20000 + 15 * 11 + 511) / 512) == 1, "one launch for the group");
+  need(walk({request(5, 3, 32000, 32000, 65535)}, 256, 0, 3, true, tiles(3, 32000, 32000) + 5 * 2048 + 1 + 128) == 2,
+       "two launches");
+  // the line between tiles and strips: enough strips; contributions over a value
+  const int H = 3000 * 16, values = H * 64;
+  need(!sum_in_strips(64, 8, 1, H - 16, 64, 1) && sum_in_strips(64, 8, 1, H, 64, 1), "3000 strips");
+  need(sum_in_strips(64, values / 4096 * 4, 1, H, 64, 1) && !sum_in_strips(64, values / 4096 * 5, 1, H, 64, 1) &&
+           !sum_in_strips(64, values / 4096, 5, H, 64, 1),
+       "3000 / 700 contributions over a value");
+  need(sum_in_strips(256, 65535, 1, 17000, 17000, 2) && !sum_in_strips(256, 65535, 1, 16000, 16000, 2), "sixteen");
   // a segment of slices, past the end of a shallower request; nothing to sum
   need(walk({request(2, 7, 200, 300, 5)}, 128, 6, 3, false, tiles(1, 200, 300)) == 1, "the last segment");
   need(walk({request(2, 7, 200, 300, 5)}, 128, 0, 0, true, 2 * 512 + 1 + 1) == 1, "no object gradient");
