@@ -24,7 +24,7 @@ constexpr int kProbeSplit = 16;   // interleaved sums of the probe-spectrum grad
 //     modes, 8 slices (35; 118 MB of contributions) and 1.15 ms at 128 x 128, 4
 //     modes, 8 slices, 1024 positions (1.07; 4.3 GB, read at 4.0 TB/s);
 //   - probe-spectrum gradient: gphat_m(u) = scale sum_b h_hat_{b,m}(u) conj(R_b(u)),
-//     32 pixels x 16 interleaved sums over the items, added in order; for the
+//     16 interleaved sums over the items, added in order (finish_pixels); for the
 //     requests whose final pass kept these sums (chain_final), the 16 tiles it
 //     left are added the same way;
 //   - loss; position gradients.
@@ -100,29 +100,52 @@ __global__ __launch_bounds__(512) void k_finish(const Item* __restrict__ items, 
   }
   g -= parts.gather;
   if (g < parts.probe) {
-    const int m = (int)(g / (N * N / kFinishPX));
-    const int px = (int)(g % (N * N / kFinishPX)) * kFinishPX + (t & 31), s = t >> 5;
+    const int per = N * N / finish_pixels(p.wide), m = (int)g / per;
+    const int px = p.wide ? (int)g % per * 512 + t : (int)g % per * 32 + (t & 31), s = t >> 5;
     const int ux = CHAIN ? px / N : mem_column<N>(px % N), uy = CHAIN ? px % N : px / N;
-    float2 acc = make_float2(0.f, 0.f);
-    if (!CHAIN && r.chain_final) {
-      if (s < r.n_items) acc = ws[(size_t)(items[r.item0 + s].tile0 + m) * N * N + px];
-    } else {
-#pragma unroll 4
-      for (int b = r.item0 + s; b < r.item0 + r.n_items; b += kProbeSplit) {
-        const Item it = items[b];
-        const float2 R = xmul(ramps[(size_t)b * 2 * N + uy], ramps[(size_t)b * 2 * N + N + ux]);
-        const float2 h = ws[(size_t)(it.tile0 + m) * N * N + px];
-        if (it.valid) acc = cadd(acc, xmul(h, cconj(R)));
+    const bool sums = !CHAIN && r.chain_final;
+    auto term = [&](int b) {
+      const Item it = items[b];
+      const float2 R = xmul(ramps[(size_t)b * 2 * N + uy], ramps[(size_t)b * 2 * N + N + ux]);
+      const float2 h = ws[(size_t)(it.tile0 + m) * N * N + px];
+      return it.valid ? xmul(h, cconj(R)) : make_float2(0.f, 0.f);
+    };
+    float2 z = make_float2(0.f, 0.f);
+    if (p.wide) {
+      for (int s0 = 0; s0 < kProbeSplit; s0 += 4) {
+        float2 a[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) a[k] = make_float2(0.f, 0.f);
+        if (sums) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            if (s0 + k < r.n_items) a[k] = ws[(size_t)(items[r.item0 + s0 + k].tile0 + m) * N * N + px];
+        } else {
+          for (int b = s0; b < r.n_items; b += kProbeSplit) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+              if (b + k < r.n_items) a[k] = cadd(a[k], term(r.item0 + b + k));
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) z = s0 + k == 0 ? a[0] : cadd(z, a[k]);
       }
-    }
-    part[t] = acc;
-    __syncthreads();
-    if (s == 0) {
-      float2 z = part[t];
+    } else {
+      float2 acc = make_float2(0.f, 0.f);
+      if (sums) {
+        if (s < r.n_items) acc = ws[(size_t)(items[r.item0 + s].tile0 + m) * N * N + px];
+      } else {
+#pragma unroll 4
+        for (int b = r.item0 + s; b < r.item0 + r.n_items; b += kProbeSplit) acc = cadd(acc, term(b));
+      }
+      part[t] = acc;
+      __syncthreads();
+      if (s > 0) return;
+      z = part[t];
 #pragma unroll
       for (int k = 1; k < kProbeSplit; ++k) z = cadd(z, part[32 * k + t]);
-      r.gphat[(size_t)m * N * N + (CHAIN ? px : uy * N + ux)] = cscale(z, adj_scale(r, scale));
     }
+    r.gphat[(size_t)m * N * N + (CHAIN ? px : uy * N + ux)] = cscale(z, adj_scale(r, scale));
     return;
   }
   // the loss

@@ -317,13 +317,24 @@ struct FinishRun {
   const float2* seg;        // as in ChainRun
   int seg_len, seg_base;
   // (set by finish_layout)
-  int rest, n_reqs;
+  int rest, n_reqs, wide;
   unsigned strips;             // requests (bits) whose object gradient is summed in strips
   unsigned at[kMaxReqs + 1];   // first workgroup of each request, then of the positions
   unsigned first;              // first workgroup of this launch
 };
 constexpr int kFinishTY = 4;      // rows of an object-gradient tile
-constexpr int kFinishPX = 32;     // probe pixels of a workgroup
+// Probe pixels of a workgroup: 32, the 16 interleaved sums of each side by side, or
+// (wide) 512, a thread taking the 16 of one pixel in turn: a workgroup costs about 3 ns
+// of the launch, the sums in turn the latency of every fourth item. Loss and
+// gradients of one slice, 32 against 512: 256 x 256, 8 modes (524288 pixels), 4
+// positions 227 -> 193 us, 256 positions 2485 -> 2449; 192 x 192, 8 modes, 64 positions 491 -> 463;
+// 128 x 128, 4 modes (65536), 16 positions 127 -> 126; kept at 32: the same with 64
+// positions 150 against 166, 256 x 256, 2 modes, 64 positions 238 against 243. The same bits
+// either way.
+__host__ __device__ inline int finish_pixels(int wide) { return wide ? 512 : 32; }
+inline bool finish_wide(long long pixels, long long most_items) {
+  return pixels >= 262144 || (pixels >= 32768 && pixels >= 4096 * most_items);
+}
 // HIP takes fewer than 2^32 threads in a grid dimension: workgroups of 512 in one launch
 constexpr unsigned kFinishBlocks = (1u << 23) - 1;
 
@@ -338,7 +349,7 @@ __host__ __device__ inline FinishParts finish_parts(const FinishRun& p, const Re
   f.ty = (unsigned)(r.H + kFinishTY - 1) / kFinishTY;
   const int slices = r.S - p.lo < p.slices ? r.S - p.lo : p.slices;
   if (r.gobj && slices > 0 && !((p.strips >> q) & 1u)) f.gather = (unsigned)slices * f.ty * f.tx;
-  if (p.rest && r.gphat) f.probe = (unsigned)r.M * (unsigned)(N * N / kFinishPX);
+  if (p.rest && r.gphat) f.probe = (unsigned)r.M * (unsigned)(N * N / finish_pixels(p.wide));
   if (p.rest && r.loss_out) f.loss = 1;
   return f;
 }
@@ -349,6 +360,12 @@ inline unsigned finish_layout(FinishRun& p, const ReqTable& reqs, int n_reqs, in
   unsigned g = 0;
   p.rest = rest ? 1 : 0;
   p.n_reqs = n_reqs;
+  long long pixels = 0, most = 0;
+  for (int q = 0; q < n_reqs; ++q) {
+    pixels += reqs.r[q].gphat ? (long long)reqs.r[q].M * N * N : 0;
+    most = most > reqs.r[q].n_items ? most : reqs.r[q].n_items;
+  }
+  p.wide = finish_wide(pixels, most) ? 1 : 0;
   p.strips = 0;
   for (int q = 0; q <= kMaxReqs; ++q) p.at[q] = ~0u;
   for (int q = 0; q < n_reqs; ++q) {

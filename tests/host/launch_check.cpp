@@ -69,20 +69,24 @@ int main() {
   // sixteen requests, one with a large object: by the largest of each size they
   // would need 16 * 30 * 529 * 34 = 8633280 workgroups for the object alone
   std::vector<ReqDev> group{request(1, 30, 2116, 2116, 9)};
-  need(sum_in_strips(64, 9, 1, 2116, 2116, 30), "few windows on a large object");
-  unsigned long long want = 128 + 1;   // (its sum is taken in strips)
+  unsigned long long small = 0, modes = 1;
   for (int q = 1; q < 16; ++q) {
     group.push_back(request(q % 3 + 1, 1 + q % 2, 64 + q, 70, 4 + q));
-    want += tiles(1 + q % 2, 64 + q, 70) + 128 * (q % 3 + 1) + 1;
+    small += tiles(1 + q % 2, 64 + q, 70);
+    modes += q % 3 + 1;
   }
-  need(walk(group, 64, 0, 30, true, want + 1) == 1, "one launch for the group");
-  need(walk(group, 64, 0, 30, false, want - 16 - 128 * (1 + 30)) == 1, "the objects alone");
+  need(sum_in_strips(64, 9, 1, 2116, 2116, 30), "few windows on a large object");
+  // (its sum is taken in strips; 31 modes of 64 x 64 pixels, at most 19 items: 512 pixels a workgroup)
+  need(walk(group, 64, 0, 30, true, small + 8 * modes + 16 + 1) == 1, "one launch for the group");
+  need(walk(group, 64, 0, 30, false, small) == 1, "the objects alone");
   // the same object under many windows, and 3 x 10^9 values
   group[0].n_items = 20000;
-  want += tiles(30, 2116, 2116);
-  need(walk(group, 64, 0, 30, true, want + (20000 + 15 * 11 + 511) / 512) == 1, "one launch for the group");
-  need(walk({request(5, 3, 32000, 32000, 65535)}, 256, 0, 3, true, tiles(3, 32000, 32000) + 5 * 2048 + 1 + 128) == 2,
+  need(walk(group, 64, 0, 30, true, tiles(30, 2116, 2116) + small + 128 * modes + 16 + (20000 + 15 * 12 + 511) / 512) == 1,
+       "one launch for the group");
+  need(walk({request(5, 3, 32000, 32000, 65535)}, 256, 0, 3, true, tiles(3, 32000, 32000) + 5 * 128 + 1 + 128) == 2,
        "two launches");
+  // the line between 32 and 512 probe pixels
+  need(!finish_wide(32767, 1) && finish_wide(32768, 8) && !finish_wide(32768, 9) && finish_wide(262144, 65535), "probe pixels");
   // the line between tiles and strips: enough strips; contributions over a value
   const int H = 3000 * 16, values = H * 64;
   need(!sum_in_strips(64, 8, 1, H - 16, 64, 1) && sum_in_strips(64, 8, 1, H, 64, 1), "3000 strips");
@@ -92,7 +96,7 @@ int main() {
   need(sum_in_strips(256, 65535, 1, 17000, 17000, 2) && !sum_in_strips(256, 65535, 1, 16000, 16000, 2), "sixteen");
   // a segment of slices, past the end of a shallower request; nothing to sum
   need(walk({request(2, 7, 200, 300, 5)}, 128, 6, 3, false, tiles(1, 200, 300)) == 1, "the last segment");
-  need(walk({request(2, 7, 200, 300, 5)}, 128, 0, 0, true, 2 * 512 + 1 + 1) == 1, "no object gradient");
+  need(walk({request(2, 7, 200, 300, 5)}, 128, 0, 0, true, 2 * 32 + 1 + 1) == 1, "no object gradient");
   ReqDev no = request(1, 3, 100, 100, 600);
   no.gobj = no.gphat = nullptr;
   no.loss_out = nullptr;
