@@ -307,14 +307,48 @@ bool use_resident(int strategy, int N, int ck_every) {
 // separates (any circular limit or centred mask; other masks are read from the
 // N x N table, which the chains' lane order would read one line per lane). A
 // window's rows are addressed with 32-bit offsets, hence the limit on obj_w.
-// Measured against two-pass (group step or gradients): 64 x 64, 2 modes, 8
-// slices, 225 positions 611 -> 218 us; 128 x 128, 2 modes, 5 slices, 77
-// positions 500 -> 327 us; 4 modes, 8 slices, 1024 positions 7.17 -> 6.05 ms.
-// The rule looks at the context alone, so a reconstruction takes the same
-// path, and has the same bits, alone and in a grouped step.
-bool use_chain(const pty_ctx* c) {
+bool can_chain(const pty_ctx* c) {
   return c->strategy == PTY_STRATEGY_AUTO && chain_size(c->g.N) && !c->ck_half && c->g.obj_w <= (1 << 20) &&
          (c->g.n_slices == 1 || c->prop_y);
+}
+
+// Where the two passes measured faster than the chains, for B positions in flight.
+// Loss and gradients, two-pass against chain, us (measured for 1 - 32 modes, 1 - 20
+// slices, 4 - 1024 positions; forward calls gain and lose along the same lines by less).
+// few: a workgroup takes a tile through all its transforms in turn, so few tiles
+// leave CUs idle, where the two passes spread a tile over several workgroups, but
+// take the modes of a position in turn. At 64 x 64 the chains win all the same.
+//   128 x 128, 1 slice, 1 mode, 16 positions 71, 98; 256: 168, 159; 512: 300, 257
+//              1 slice, 4 modes, 16 positions 120, 126; 32: 134, 130
+//              2 slices, 2 modes, 8 positions 119, 138; 32: 147, 154
+//              8 slices, 1 mode, 16 positions 312, 369; 64: 382, 385; 256: 772, 584
+//              8 slices, 2 modes, 8 positions (left to the chains) 348, 374; 32: 401, 388
+bool chain_few(int N, int M, int S, int B) {
+  if (N == 64) return false;
+  const long long tiles = (long long)B * M;
+  if (S == 1) return M == 1 ? B < 512 : M < 8 && tiles < 128;
+  return M <= (S == 2 ? 2 : 1) && tiles < 64;
+}
+// many: a chain leaves a contribution of every mode in memory, which with one slice
+// and many modes is more traffic than it saves.
+//   128 x 128, 1 slice, 8 modes, 16 positions 170, 138; 128: 360, 418
+//   64 x 64, 1 slice, 8 modes, 128 positions 127, 117; 256: 210, 242
+bool chain_many(int N, int M, int S, int B) {
+  return S == 1 && M >= 8 && (N == 64 ? B >= 256 : (long long)B * M > 512);
+}
+
+// Does a call with B positions run the chain kernels? Under the ordered reduction
+// few positions run them too: there a reconstruction has the same bits alone
+// and in a grouped step, and a grouped step shares the chains among its requests,
+// where few positions of each win (two-pass against chain, 16 requests of 4 positions,
+// 1 mode, 128 x 128: 1 slice 359, 134; 10 slices 801, 567).
+bool use_chain(const pty_ctx* c, int B) {
+  const int N = c->g.N, M = c->g.n_modes, S = c->g.n_slices;
+  if (!can_chain(c)) return false;
+  if (c->reduce == PTY_REDUCE_ORDERED) return !chain_many(N, M, S, B);
+  // (of a chunked schedule; recomputing chains take the whole group at once)
+  if (c->chunk > 0 && c->ck_every == 1) B = (int)std::min<long long>(B, (long long)c->chunk * c->n_streams);
+  return !chain_many(N, M, S, B) && !chain_few(N, M, S, B);
 }
 
 ReqDev base_req(pty_ctx* c) {
@@ -381,7 +415,7 @@ LaunchCtx ctx_launch(pty_ctx* c, hipStream_t s, const ReqDev& r, int B) {
   L.loss_part = c->loss_part;
   L.pos_part = c->pos_part;
   L.flags = c->flags;
-  L.chain = use_chain(c) ? 1 : 0;
+  L.chain = use_chain(c, B) ? 1 : 0;
   L.resident = (use_resident(c->strategy, c->g.N, c->ck_every) && c->reduce != PTY_REDUCE_ORDERED) ? 1 : 0;
   set_sum(c, L);
   // float checkpoints: the column passes write the stored entry waves' row
@@ -1594,15 +1628,20 @@ pty_status pty_group_reconstruct_step(pty_group* G, void* stream, const pty_grou
   bool ordered = true;
   for (int q = 0; q < n; ++q) ordered &= items[q].ctx->reduce == PTY_REDUCE_ORDERED;
   const bool resident = !ordered && use_resident(items[0].ctx->strategy, N, 1);
-  // The requests whose contexts run the chain kernels share one set of
+  // The requests that run the chain kernels share one set of
   // launches, the others another, one after the other in the same workspace,
   // so each request takes the path (and has the bits) of its steps alone. The
   // gradients of every set wait in the contexts: every one is taken before the
   // first update, since requests may share a state.
   enum { kOnChain, kTwoPass, kShared, kSets };
-  int set[kMaxReqs];
+  int set[kMaxReqs], able = 0;
+  for (int q = 0; q < n; ++q) able += can_chain(items[q].ctx) ? 1 : 0;
   for (int q = 0; q < n; ++q) {
-    set[q] = use_chain(items[q].ctx) && !resident ? kOnChain : kTwoPass;
+    // (two requests and more share the chains, so few positions of each win)
+    const pty_ctx* c = items[q].ctx;
+    const int B = items[q].batch;
+    const bool chain = able > 1 ? can_chain(c) && !chain_many(N, c->g.n_modes, c->g.n_slices, B) : use_chain(c, B);
+    set[q] = chain && !resident ? kOnChain : kTwoPass;
     // A context listed twice has one set of gradients for both entries: they are
     // added up with atomics (a stored sum is written whole, so one entry's would
     // be lost), and each entry's update takes the total.

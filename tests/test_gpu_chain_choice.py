@@ -1,0 +1,86 @@
+"""Which kernels the default strategy takes at 64 x 64 and 128 x 128, on both sides of
+its lines: the bits are those of the two-pass kernels, or of the chain kernels,
+which the ordered reduction takes for few positions too, and either agrees with the
+other within the parity bounds. Grouped, few positions run the chains."""
+import numpy as np
+import pytest
+
+from paper_2505_14372_amd import api, synth
+
+from _cases import Case, rel_l2
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _case(N, M, S, B, seed=8):
+    scan = int(np.ceil(np.sqrt(B)))
+    return Case(synth.make_small(N=N, M=M, S=S, scan=scan, step=2, seed=seed, loss="poisson", eps=0.8, amp_noise=0.2),
+                batch=np.arange(B))
+
+
+def _grad(c, d, strategy="auto", reduction="atomic", chunk=0, streams=1):
+    p = c.problem()
+    p.set_strategy(strategy)
+    p.set_reduction(reduction)
+    p.set_chunk(chunk)
+    p.set_streams(streams)
+    out = p.loss_and_grad(d["probe"], d["obj"], d["pos"], d["pats"], d["batch"])
+    loss, _ = p.forward_save(d["probe"], d["obj"], d["pos"], d["pats"], d["batch"])
+    assert loss.item() == out[0].item()
+    fwd, loss = p.forward(d["probe"], d["obj"], d["pos"], d["batch"], patterns=d["pats"])
+    assert loss.item() == out[0].item()
+    p.check()
+    return out + (fwd,)
+
+
+@pytest.mark.parametrize("N,M,S,B,chain", [
+    (64, 1, 1, 1, True), (64, 8, 1, 255, True), (64, 8, 1, 256, False), (64, 7, 1, 256, True), (64, 8, 2, 256, True),
+    (128, 1, 1, 511, False), (128, 1, 1, 512, True), (128, 2, 1, 63, False), (128, 2, 1, 64, True),
+    (128, 7, 1, 18, False), (128, 8, 1, 1, True), (128, 8, 1, 64, True), (128, 8, 1, 65, False),
+    (128, 1, 2, 63, False), (128, 1, 2, 64, True), (128, 2, 2, 31, False), (128, 2, 2, 32, True),
+    (128, 3, 2, 1, True), (128, 1, 3, 63, False), (128, 1, 3, 64, True), (128, 2, 3, 1, True)])
+def test_default_takes_the_faster_kernels(N, M, S, B, chain):
+    c = _case(N, M, S, B)
+    d = c.device()
+    got, two = _grad(c, d), _grad(c, d, "two_pass")
+    many = S == 1 and M >= 8 and not chain
+    ordered = _grad(c, d, reduction="ordered")
+    for a, b in zip(got, ordered if chain else two):
+        assert torch.equal(a, b)
+    for a, b in zip(ordered, two):
+        assert rel_l2(a.cpu().numpy(), b.cpu().numpy()) < 1e-3
+    assert torch.equal(ordered[1], two[1]) == many
+
+
+@pytest.mark.parametrize("chunk,streams,chain", [(15, 4, False), (16, 4, True), (63, 1, False), (64, 1, True)])
+def test_positions_in_flight_count(chunk, streams, chain):
+    c = _case(128, 1, 3, 130)
+    d = c.device()
+    got = _grad(c, d, chunk=chunk, streams=streams)
+    want = _grad(c, d, "auto" if chain else "two_pass")
+    for a, b in zip(got[1:], want[1:]):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("N,M,S,n,chain", [(128, 1, 1, 1, False), (128, 1, 1, 2, True), (128, 2, 2, 3, True),
+                                           (64, 1, 1, 1, True)])
+def test_grouped_requests_share_the_chains(N, M, S, n, chain):
+    opt = api.Optimizer(kind="sgd", lr_object=1e-4, lr_probe=1e-4, lr_pos=1e-4)
+    entries, want = [], []
+    for q in range(n):
+        c = _case(N, M, S, 5 + q, seed=70 + q)
+        d = c.device()
+        ref, prob = c.problem(), c.problem()
+        ref.set_strategy("auto" if chain else "two_pass")
+        ref.set_reduction("ordered")
+        one, many = (api.ReconState(d["probe"].clone(), d["obj"].clone(), d["pos"].clone(), adam=False) for _ in range(2))
+        want.append((one, ref.reconstruct_step(one, d["pats"], d["batch"], opt)))
+        entries.append((prob, many, d["pats"], d["batch"], opt, torch.zeros(1, dtype=torch.float64, device="cuda")))
+    tiles = sum(M * (5 + q) for q in range(n))
+    api.Group(N, tiles, tiles, tiles * S).step(entries)
+    torch.cuda.synchronize()
+    for (one, loss), e in zip(want, entries):
+        assert loss.item() == e[5].item()
+        for f in ("object", "probe", "positions"):
+            assert torch.equal(getattr(one, f), getattr(e[1], f)), f
