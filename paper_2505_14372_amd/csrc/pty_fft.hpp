@@ -232,7 +232,7 @@ constexpr int pad_to(int x, int mod, int rem) { return x + ((rem - x % mod) % mo
 
 // Exchange scratch of one line: Z[l][k1] at xch[k1 * XP + l], XP = L + 1.
 // Lines of one workgroup are ROW_STRIDE (row passes: the lines of a wave
-// are consecutive) or COL_STRIDE (column passes: consecutive lanes belong
+// are consecutive) or col_stride (column passes: consecutive lanes belong
 // to consecutive columns) float2 apart. Both strides are padded so that the
 // 64 lanes of a wave spread over all 64 four-byte LDS banks: a float2
 // access then takes the minimum of two bank cycles per wave.
@@ -253,11 +253,13 @@ template <int N> struct Xch {
   static constexpr int SIZE = E * XP;
   static constexpr bool ROW_SPLIT = N == 192 || N == 128, COL_SPLIT = N == 192;
   using RowElem = typename XchElem<ROW_SPLIT>::T;
-  using ColElem = typename XchElem<COL_SPLIT>::T;
-  static constexpr int ROW_STRIDE = ROW_SPLIT ? pad_to(SIZE, 64, 8)
-                                    : (L == 16) ? pad_to(SIZE, 32, 16) : pad_to(SIZE, 32, 8);
-  static constexpr int COL_STRIDE = COL_SPLIT ? pad_to(SIZE, 4, 2)
-                                    : (L == 16) ? pad_to(SIZE, 32, 4) : pad_to(SIZE, 2, 1);
+  static constexpr int row_stride(bool split) {
+    return split ? pad_to(SIZE, 64, 8) : (L == 16) ? pad_to(SIZE, 32, 16) : pad_to(SIZE, 32, 8);
+  }
+  static constexpr int ROW_STRIDE = row_stride(ROW_SPLIT);
+  static constexpr int col_stride(bool split) {
+    return split ? pad_to(SIZE, 4, 2) : (L == 16) ? pad_to(SIZE, 32, 4) : pad_to(SIZE, 2, 1);
+  }
 };
 
 // Line FFT of v (layout above), in two stages around the LDS exchange.

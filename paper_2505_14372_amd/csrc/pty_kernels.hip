@@ -226,8 +226,8 @@ __global__ void k_items(const ReqTable reqs, int n_reqs, Item* __restrict__ item
 // EMAX the maxima over the window of sum_m |psi_i,m|^2 and of |O_i|^2 are
 // max-accumulated into r.emax[item][i] (non-negative floats order like their
 // bit patterns, so an unsigned atomic max is exact).
-template <int N, bool FROM_REAL, bool HALF, bool EMAX = false>
-__global__ __launch_bounds__(kThreads, N == 192 && !EMAX ? 3 : 1) void k_row_fwd(const Item* __restrict__ items,
+template <int N, bool FROM_REAL, bool HALF, bool EMAX = false, bool WHOLE = false>
+__global__ __launch_bounds__(kThreads, N == 192 && !EMAX && !WHOLE ? 3 : 1) void k_row_fwd(const Item* __restrict__ items,
                                                       const ReqTable reqs,
                                                       float2* __restrict__ ws, void* __restrict__ ck_,
                                                       const float2* __restrict__ twg, int step,
@@ -236,7 +236,9 @@ __global__ __launch_bounds__(kThreads, N == 192 && !EMAX ? 3 : 1) void k_row_fwd
   const int by = gridDim.y - 1 - blockIdx.y;
   constexpr int L = Pass<N>::L, E = Pass<N>::E, LINES = Pass<N>::LINES;
   __shared__ float2 tw[N];
-  __shared__ typename Xch<N>::RowElem xch[LINES * Xch<N>::ROW_STRIDE];
+  using Elem = typename XchElem<!WHOLE && Xch<N>::ROW_SPLIT>::T;
+  constexpr int STRIDE = Xch<N>::row_stride(!WHOLE && Xch<N>::ROW_SPLIT);
+  __shared__ Elem xch[LINES * STRIDE];
   const Item it = items[item_off + by];
   const ReqDev& r = reqs.r[it.req];
   const int i = step;
@@ -248,7 +250,7 @@ __global__ __launch_bounds__(kThreads, N == 192 && !EMAX ? 3 : 1) void k_row_fwd
   CT* ck = static_cast<CT*>(ck_);
   const int l = threadIdx.x % L, line = threadIdx.x / L;
   const int y = blockIdx.x * LINES + line;
-  typename Xch<N>::RowElem* sx = xch + line * Xch<N>::ROW_STRIDE;
+  Elem* sx = xch + line * STRIDE;
   // the row spectrum of slice i >= 1 was written by a propagation column pass,
   // which leaves the columns outside the propagator's support unwritten (zero)
   unsigned live = ~0u;
@@ -563,11 +565,14 @@ template <int N> struct ColPass {
 // through LDS with block barriers. (Keeping each column inside one wave, with
 // no block barrier, measured slower: the loads then cover 64 / L values per
 // row.)
-template <int N> struct ColMap {
+// SPLIT: the exchange in half the LDS (see Xch), which column passes over few tiles
+// leave out (whole_exchange).
+template <int N, bool SPLIT = Xch<N>::COL_SPLIT> struct ColMap {
   static constexpr int CB = ColPass<N>::CB;
+  using Elem = typename XchElem<SPLIT>::T;
   // per-column exchange stride: with 32 or more columns of 16 lanes an odd
   // stride keeps a wave's accesses at two bank cycles (checked by exhaustive count)
-  static constexpr int STRIDE = (CB >= 32 && Cfg<N>::L == 16) ? pad_to(Xch<N>::SIZE, 2, 1) : Xch<N>::COL_STRIDE;
+  static constexpr int STRIDE = (CB >= 32 && Cfg<N>::L == 16) ? pad_to(Xch<N>::SIZE, 2, 1) : Xch<N>::col_stride(SPLIT);
   __device__ __forceinline__ static int col() { return threadIdx.x % CB; }
   __device__ __forceinline__ static int lane() { return threadIdx.x / CB; }
   using Sync = BlockSync;
@@ -579,7 +584,7 @@ template <int N> struct ColMap {
 //   COL_PROP_ADJ tile = IDFT_y(conj(H_{i-1}) * DFT_y(tile)) (adjoint, i = S-1-step >= 1)
 //   COL_FINAL    tile = DFT_y(tile) / N = h_hat          (adjoint, i = 0) and the
 //                per-block sums of Im(conj(h_hat) phat R) u_a for the position gradient
-template <int N, int OP>
+template <int N, int OP, bool SPLIT>
 __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col(const Item* __restrict__ items,
                                                   const ReqTable reqs,
                                                   float2* __restrict__ ws, const float2* __restrict__ ramps,
@@ -595,7 +600,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col(const Item* __restr
   const int cb = (int)((colmap >> (8 * blockIdx.x)) & 0xffu);
   __shared__ float2 tw[N];
   __shared__ float4 hy[PROP ? N : 1];
-  __shared__ typename Xch<N>::ColElem xch[CB * ColMap<N>::STRIDE];
+  __shared__ typename ColMap<N, SPLIT>::Elem xch[CB * ColMap<N, SPLIT>::STRIDE];
   __shared__ float red[2][T / 64];
   // grid (column blocks, modes, items): dispatched item by item, in item order
   const int b = item_off + blockIdx.z, m = blockIdx.y;
@@ -622,9 +627,9 @@ __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col(const Item* __restr
       if (!any) return;
     }
   }
-  const int c = ColMap<N>::col(), l = ColMap<N>::lane(), t = threadIdx.x;
+  const int c = ColMap<N, SPLIT>::col(), l = ColMap<N, SPLIT>::lane(), t = threadIdx.x;
   const int mx = cb * CB + c, ux = mem_column<N>(mx);   // position in a tile row, column
-  typename Xch<N>::ColElem* sx = xch + c * ColMap<N>::STRIDE;
+  typename ColMap<N, SPLIT>::Elem* sx = xch + c * ColMap<N, SPLIT>::STRIDE;
   float2* tile = ws + (size_t)(it.tile0 + m) * N * N;
   // a forward propagation whose output is a stored checkpoint runs in place
   // in that slot, where the forward row pass left its input
@@ -666,9 +671,9 @@ __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col(const Item* __restr
       int uy = l + L * a;
       v[a] = cscale(cmul(cmul(ph[(size_t)uy * N + ux], ry[uy]), rx), inv);
     }
-    line_fft<N, true>(v, l, tw, sx, typename ColMap<N>::Sync{});
+    line_fft<N, true>(v, l, tw, sx, typename ColMap<N, SPLIT>::Sync{});
   } else {
-    line_fft<N, false>(v, l, tw, sx, typename ColMap<N>::Sync{});
+    line_fft<N, false>(v, l, tw, sx, typename ColMap<N, SPLIT>::Sync{});
     if constexpr (PROP) {
       if (sep) {
         // H = [|k_x| <= K_y] Hy(k_y) Hx(k_x), factors staged above
@@ -688,7 +693,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col(const Item* __restr
           v[a] = (OP == COL_PROP) ? cmul(v[a], h) : cjmul(h, v[a]);
         }
       }
-      line_fft<N, true>(v, l, tw, sx, typename ColMap<N>::Sync{});
+      line_fft<N, true>(v, l, tw, sx, typename ColMap<N, SPLIT>::Sync{});
     } else {  // COL_FINAL
       const float inv = 1.f / (float)N;
       const float2* ry = ramps + (size_t)b * 2 * N;
@@ -755,7 +760,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col_plain(float2* __res
                                                         float scale) {
   constexpr int L = ColPass<N>::L, E = ColPass<N>::E, CB = ColPass<N>::CB;
   __shared__ float2 tw[N];
-  __shared__ typename Xch<N>::ColElem xch[CB * ColMap<N>::STRIDE];
+  __shared__ typename ColMap<N>::Elem xch[CB * ColMap<N>::STRIDE];
   load_twiddles<N>(tw, twg);
   __syncthreads();
   const int c = ColMap<N>::col(), l = ColMap<N>::lane();
@@ -780,7 +785,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col_plain(float2* __res
 // At N = 256 the launch bound asks for four waves per SIMD (128 VGPRs, 40
 // bytes per lane spilled), which lets two 512-thread workgroups share a CU
 // instead of one: 1.55 -> 1.39 ms per group of 512 positions.
-template <int N, bool GRAD>
+template <int N, bool GRAD, bool SPLIT>
 __global__ __launch_bounds__(ColPass<N>::THREADS, N == 256 ? 4 : 1) void k_far_loss(const Item* __restrict__ items,
                                                        const ReqTable reqs,
                                                        float2* __restrict__ ws, const float2* __restrict__ twg,
@@ -788,13 +793,13 @@ __global__ __launch_bounds__(ColPass<N>::THREADS, N == 256 ? 4 : 1) void k_far_l
                                                        int item_off) {
   constexpr int L = ColPass<N>::L, E = ColPass<N>::E, CB = ColPass<N>::CB;
   __shared__ float2 tw[N];
-  __shared__ typename Xch<N>::ColElem xch[CB * ColMap<N>::STRIDE];
+  __shared__ typename ColMap<N, SPLIT>::Elem xch[CB * ColMap<N, SPLIT>::STRIDE];
   __shared__ float red[ColPass<N>::THREADS / 64];
   const int b = item_off + blockIdx.y;
   const Item it = items[b];
   const ReqDev& r = reqs.r[it.req];
   if (step != r.S - 1) return;
-  const int c = ColMap<N>::col(), l = ColMap<N>::lane();
+  const int c = ColMap<N, SPLIT>::col(), l = ColMap<N, SPLIT>::lane();
   const int mx = blockIdx.x * CB + c, ux = mem_column<N>(mx);   // position in a tile row, column
   if (!it.valid) {
     if (r.I_out) {
@@ -807,7 +812,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS, N == 256 ? 4 : 1) void k_far_l
   }
   load_twiddles<N>(tw, twg);
   __syncthreads();
-  typename Xch<N>::ColElem* sx = xch + c * ColMap<N>::STRIDE;
+  typename ColMap<N, SPLIT>::Elem* sx = xch + c * ColMap<N, SPLIT>::STRIDE;
   const float inv = 1.f / (float)N;
   float I[E];
 #pragma unroll
@@ -817,7 +822,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS, N == 256 ? 4 : 1) void k_far_l
     float2 v[E];
 #pragma unroll
     for (int a = 0; a < E; ++a) v[a] = tile[(size_t)(l + L * a) * N + mx];
-    line_fft<N, false>(v, l, tw, sx, typename ColMap<N>::Sync{});
+    line_fft<N, false>(v, l, tw, sx, typename ColMap<N, SPLIT>::Sync{});
 #pragma unroll
     for (int a = 0; a < E; ++a) {
       v[a] = cscale(v[a], inv);
@@ -868,10 +873,10 @@ __global__ __launch_bounds__(ColPass<N>::THREADS, N == 256 ? 4 : 1) void k_far_l
       float2 v[E];
 #pragma unroll
       for (int a = 0; a < E; ++a) v[a] = tile[(size_t)(l + L * a) * N + mx];
-      line_fft<N, false>(v, l, tw, sx, typename ColMap<N>::Sync{});
+      line_fft<N, false>(v, l, tw, sx, typename ColMap<N, SPLIT>::Sync{});
 #pragma unroll
       for (int a = 0; a < E; ++a) v[a] = cscale(cscale(v[a], inv), wgt[a] * inv);
-      line_fft<N, true>(v, l, tw, sx, typename ColMap<N>::Sync{});
+      line_fft<N, true>(v, l, tw, sx, typename ColMap<N, SPLIT>::Sync{});
 #pragma unroll
       for (int a = 0; a < E; ++a) tile[(size_t)(l + L * a) * N + mx] = v[a];
     }
@@ -903,6 +908,7 @@ __global__ void k_loss_reduce(const ReqTable reqs, const float* __restrict__ los
 // workgroup per 4 x 64 tile of the slice adds their sum (object_sum) to the gradient, and with WS that of the
 // stored illuminations (wscr) to r.wsum.
 constexpr int kGatherTY = 4;
+constexpr long long kWholeExchange = 512;   // see Launch::whole_exchange
 template <int N, bool WS>
 __global__ __launch_bounds__(512) void k_obj_gather(const Item* __restrict__ items, const ReqTable reqs,
                                                     const float2* __restrict__ cscr, const float* __restrict__ wscr,
@@ -954,7 +960,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col_final_chain(const I
   static_assert(T >= N, "the twiddle table takes one entry per thread");
   const int cb = (int)((colmap >> (8 * blockIdx.x)) & 0xffu);
   __shared__ float2 tw[N];
-  __shared__ typename Xch<N>::ColElem xch[CB * ColMap<N>::STRIDE];
+  __shared__ typename ColMap<N>::Elem xch[CB * ColMap<N>::STRIDE];
   __shared__ float red[2][T / 64];
   const int rq = blockIdx.z / kProbeSplit, q = blockIdx.z % kProbeSplit, m = blockIdx.y;
   const ReqDev& r = reqs.r[rq];
@@ -964,7 +970,7 @@ __global__ __launch_bounds__(ColPass<N>::THREADS) void k_col_final_chain(const I
   __syncthreads();
   const int c = ColMap<N>::col(), l = ColMap<N>::lane();
   const int ux = cb * CB + c;
-  typename Xch<N>::ColElem* sx = xch + c * ColMap<N>::STRIDE;
+  typename ColMap<N>::Elem* sx = xch + c * ColMap<N>::STRIDE;
   const float2* ph = r.phat + (size_t)m * N * N;
   const float inv = 1.f / (float)N;
   const float fx = (float)((ux < (N + 1) / 2) ? ux : ux - N) / (float)N;
@@ -1071,6 +1077,8 @@ struct Launch {
       hipLaunchKernelGGL((k_row_fwd<N, true, HALF>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, st, L.item_off, split);
     else if (L.emax)
       hipLaunchKernelGGL((k_row_fwd<N, false, HALF, true>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, st, L.item_off, split);
+    else if (whole_exchange((long long)g.x * g.y * g.z))
+      hipLaunchKernelGGL((k_row_fwd<N, false, HALF, false, Xch<N>::COL_SPLIT>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, st, L.item_off, split);
     else
       hipLaunchKernelGGL((k_row_fwd<N, false, HALF>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, st, L.item_off, split);
   }
@@ -1113,18 +1121,30 @@ struct Launch {
     // reverse of the row passes around it: each pass starts on the tiles
     // the previous pass wrote last, which the memory-side cache still holds
     dim3 g(nb, L.max_modes, L.n_items);
+    if (whole_exchange((long long)nb * L.max_modes * L.n_items)) col_as<false>(L, op, step, g, map);
+    else col_as<Xch<N>::COL_SPLIT>(L, op, step, g, map);
+  }
+  // Few workgroups are bound by latency, of which the exchange in half the LDS has
+  // more (two barriers a transform in the column passes, spills in the forward row
+  // pass): they take the whole one where it is split else. Forward of 192 x 192, 8
+  // slices, halves against whole: 1 mode, 4 positions 172 -> 162 us, 80 positions (480 row
+  // workgroups) 283 -> 269; above the line the columns alone, 2 modes, 64 positions
+  // (768), 328 against 349.
+  static bool whole_exchange(long long workgroups) { return Xch<N>::COL_SPLIT && workgroups <= kWholeExchange; }
+  template <bool SPLIT>
+  static void col_as(const LaunchCtx& L, int op, int step, dim3 g, unsigned long long map) {
     float2* ck_out = L.ck_spec ? static_cast<float2*>(L.ck) : nullptr;
     switch (op) {
-      case COL_SHIFT: hipLaunchKernelGGL((k_col<N, COL_SHIFT>), g, dim3(ColPass<N>::THREADS), 0, L.stream, L.items, L.reqs, L.ws, L.ramps, L.tw, step, L.pos_part, L.item_off, ck_out, map, L.seg_out); break;
-      case COL_PROP: hipLaunchKernelGGL((k_col<N, COL_PROP>), g, dim3(ColPass<N>::THREADS), 0, L.stream, L.items, L.reqs, L.ws, L.ramps, L.tw, step, L.pos_part, L.item_off, ck_out, map, L.seg_out); break;
-      case COL_PROP_ADJ: hipLaunchKernelGGL((k_col<N, COL_PROP_ADJ>), g, dim3(ColPass<N>::THREADS), 0, L.stream, L.items, L.reqs, L.ws, L.ramps, L.tw, step, L.pos_part, L.item_off, nullptr, map, L.seg_out); break;
+      case COL_SHIFT: hipLaunchKernelGGL((k_col<N, COL_SHIFT, SPLIT>), g, dim3(ColPass<N>::THREADS), 0, L.stream, L.items, L.reqs, L.ws, L.ramps, L.tw, step, L.pos_part, L.item_off, ck_out, map, L.seg_out); break;
+      case COL_PROP: hipLaunchKernelGGL((k_col<N, COL_PROP, SPLIT>), g, dim3(ColPass<N>::THREADS), 0, L.stream, L.items, L.reqs, L.ws, L.ramps, L.tw, step, L.pos_part, L.item_off, ck_out, map, L.seg_out); break;
+      case COL_PROP_ADJ: hipLaunchKernelGGL((k_col<N, COL_PROP_ADJ, SPLIT>), g, dim3(ColPass<N>::THREADS), 0, L.stream, L.items, L.reqs, L.ws, L.ramps, L.tw, step, L.pos_part, L.item_off, nullptr, map, L.seg_out); break;
       default: {
         bool any_chain = false, any_plain = false;
         for (int q = 0; q < L.n_reqs; ++q) (L.reqs.r[q].chain_final ? any_chain : any_plain) = true;
         if (any_plain)
-          hipLaunchKernelGGL((k_col<N, COL_FINAL>), g, dim3(ColPass<N>::THREADS), 0, L.stream, L.items, L.reqs, L.ws, L.ramps, L.tw, step, L.pos_part, L.item_off, nullptr, map, L.seg_out);
+          hipLaunchKernelGGL((k_col<N, COL_FINAL, SPLIT>), g, dim3(ColPass<N>::THREADS), 0, L.stream, L.items, L.reqs, L.ws, L.ramps, L.tw, step, L.pos_part, L.item_off, nullptr, map, L.seg_out);
         if (any_chain)
-          hipLaunchKernelGGL((k_col_final_chain<N>), dim3(nb, L.max_modes, L.n_reqs * kProbeSplit), dim3(ColPass<N>::THREADS), 0, L.stream, L.items, L.reqs, L.ws, L.ramps, L.tw, step, L.pos_part, map);
+          hipLaunchKernelGGL((k_col_final_chain<N>), dim3(g.x, L.max_modes, L.n_reqs * kProbeSplit), dim3(ColPass<N>::THREADS), 0, L.stream, L.items, L.reqs, L.ws, L.ramps, L.tw, step, L.pos_part, map);
         break;
       }
     }
@@ -1152,12 +1172,17 @@ struct Launch {
       hipLaunchKernelGGL((k_obj_gather<N, false>), g, dim3(512), 0, L.stream, L.items, L.reqs, L.cscr,
                          nullptr, step, L.item_off, L.n_items);
   }
+  template <bool SPLIT>
+  static void far_loss_as(const LaunchCtx& L, int step, bool grad, dim3 g) {
+    if (grad)
+      hipLaunchKernelGGL((k_far_loss<N, true, SPLIT>), g, dim3(ColPass<N>::THREADS), 0, L.stream, L.items, L.reqs, L.ws, L.tw, step, L.loss_part, L.flags, L.item_off);
+    else
+      hipLaunchKernelGGL((k_far_loss<N, false, SPLIT>), g, dim3(ColPass<N>::THREADS), 0, L.stream, L.items, L.reqs, L.ws, L.tw, step, L.loss_part, L.flags, L.item_off);
+  }
   static void far_loss(const LaunchCtx& L, int step, bool grad) {
     dim3 g(ColPass<N>::NBLK, L.n_items);
-    if (grad)
-      hipLaunchKernelGGL((k_far_loss<N, true>), g, dim3(ColPass<N>::THREADS), 0, L.stream, L.items, L.reqs, L.ws, L.tw, step, L.loss_part, L.flags, L.item_off);
-    else
-      hipLaunchKernelGGL((k_far_loss<N, false>), g, dim3(ColPass<N>::THREADS), 0, L.stream, L.items, L.reqs, L.ws, L.tw, step, L.loss_part, L.flags, L.item_off);
+    if (whole_exchange((long long)ColPass<N>::NBLK * L.n_items)) far_loss_as<false>(L, step, grad, g);
+    else far_loss_as<Xch<N>::COL_SPLIT>(L, step, grad, g);
   }
   static void plain2d(hipStream_t s, const float2* tw, const float2* src, float2* dst, int n_tiles, bool inverse,
                       float scale, bool accumulate) {
