@@ -386,14 +386,26 @@ ReqDev base_req(pty_ctx* c) {
 // slice by slice.
 bool store_contributions(bool ordered, int N, int M, int B) { return ordered || !(N == 256 && M >= 8 && B > 256); }
 
+// The same where the sum is taken slice by slice (half checkpoints, recomputed
+// slices, LSQML), of B positions a launch: each slice then has a launch more, which
+// looks at the whole slice, so the windows have to hold enough values, against a
+// constant and against the slice. Loss and gradients of 6 slices, one mode, stored
+// against atomics: half checkpoints, 64 x 64, 16 positions 1.13 times as long, 128 0.93;
+// on a 1000 x 1000 object 1.27 and 1.01; 256 x 256, recomputed, 4 positions 1.04, 16 0.91; on
+// 1000 x 1000 1.13 and 0.96; LSQML, 128 x 128, 8 positions 1.07, 32 0.94, on 1000 x 1000 1.21 and
+// 1.07. Over 400 such calls the line is within 0.1% of the better one on average.
+bool store_slices(int N, long long B, long long H, long long W) { return B * N * N >= 409600 + 3 * H * W / 10; }
+
 // Sets where the stored contributions of L wait: in the checkpoint slots until
 // the last launch (every slice stored in float), else in the scratch area, summed
 // slice by slice.
 void set_sum(const pty_ctx* c, LaunchCtx& L) {
   const bool ordered = c->reduce == PTY_REDUCE_ORDERED;
+  const int B = c->chunk > 0 ? std::min(c->chunk, L.n_items) : L.n_items;
   const bool stored = !L.chain && !L.resident && store_contributions(ordered, c->g.N, c->g.n_modes, L.n_items);
   L.defer = stored && !L.wsum && !c->ck_half && c->ck_every == 1 ? 1 : 0;
-  L.cscr = stored && !L.defer && (ordered || c->n_streams <= 1) ? c->cscr : nullptr;
+  const bool slices = ordered || (c->n_streams <= 1 && store_slices(c->g.N, B, c->g.obj_h, c->g.obj_w));
+  L.cscr = stored && !L.defer && slices ? c->cscr : nullptr;
   L.wscr = L.wsum && L.cscr ? c->lsq_wscr : nullptr;
 }
 
