@@ -378,12 +378,17 @@ ReqDev base_req(pty_ctx* c) {
 // modes; stored contributions cost their own traffic. Measured (loss and
 // gradients, stored against atomics): 256 x 256, 1 mode, 8 slices, 300 positions
 // 2.7 against 4.2 - 4.9 ms; 3 modes, 10 slices, 128 positions 3.2 against 3.8 -
-// 4.0; 4 modes, 4 slices, 512 positions 6.7 against 7.0 - 7.4; 8 modes, 10 slices,
-// 128 positions 7.3 against 7.5 - 7.7; 8 modes, 30 slices, 512 positions 84.2
-// against 83.8. So under PTY_REDUCE_ATOMIC the atomics keep the large groups of
-// many modes at the largest window (a slice's contributions then exceed half the
-// memory-side cache), and chunks on concurrent streams where the sum is taken
-// slice by slice.
+// 4.0; 8 modes, 10 slices, 128 positions 7.3 against 7.5 - 7.7. With more of both the
+// two meet: 8 slices, positions 8 pixels apart (a 376 to 488 pixel object) and, in
+// brackets, at random on 1280 x 1280,
+//   4 modes, 256 positions  6.18, 6.48 (6.37, 7.00);  512 12.51, 12.71 (12.78, 13.67)
+//   6 modes, 256            8.98, 9.07 (9.18, 9.61);  512 18.60, 18.26 (18.39, 18.79)
+//   7 modes, 256           10.53, 10.47 (10.69, 10.95); 512 21.35, 21.34 (21.94, 21.90)
+//   8 modes, 256           12.13, 11.95 (12.15, 12.30); 512 24.79, 24.13 (24.35, 24.62)
+//  10 modes, 256           14.95, 14.84 (15.06, 15.20); 512 30.33, 30.11 (30.78, 30.41)
+// and 8 modes, 30 slices, 512 positions, 84.2 against 83.8. Under PTY_REDUCE_ATOMIC the
+// atomics keep the groups where neither is more than 1 - 3% ahead, and chunks
+// on concurrent streams where the sum is taken slice by slice.
 bool store_contributions(bool ordered, int N, int M, int B) { return ordered || !(N == 256 && M >= 8 && B > 256); }
 
 // The same where the sum is taken slice by slice (half checkpoints, recomputed
