@@ -39,9 +39,9 @@ __global__ __launch_bounds__(512) void k_finish(const Item* __restrict__ items, 
   __shared__ float2 part[7 * kTY * 64];
   static_assert(7 * kTY * 64 >= 512, "one value per thread");
   const int t = threadIdx.x;
-  unsigned g = blockIdx.x + p.first;
-  const int q = finish_request(p, g);
-  g -= p.at[q];
+  const FinishWork work = finish_work(p, blockIdx.x + p.first);
+  const int q = work.req;
+  const unsigned g = work.index;
   if (q == p.n_reqs) {
     // per item: dL/dX = 2 pi scale times the sum over modes (and column blocks) of
     // the partials; to g_pos[local] and / or added to a dense [J][2] gradient
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(512) void k_finish(const Item* __restrict__ items, 
   }
   const ReqDev& r = reqs.r[q];
   const FinishParts parts = finish_parts(p, r, q, N);
-  if (g < parts.gather) {
+  if (work.tile) {
     const int i = p.lo + (int)(g / (parts.tx * parts.ty)), x0 = (int)(g % parts.tx) * 64;
     const int y0 = (int)((g / parts.tx) % parts.ty) * kTY, x = x0 + (t & 63);
     const bool sg = p.seg && i % r.ck_every != 0;
@@ -98,7 +98,6 @@ __global__ __launch_bounds__(512) void k_finish(const Item* __restrict__ items, 
     }
     return;
   }
-  g -= parts.gather;
   if (g < parts.probe) {
     const int per = N * N / finish_pixels(p.wide), m = (int)g / per;
     const int px = p.wide ? (int)g % per * 512 + t : (int)g % per * 32 + (t & 31), s = t >> 5;

@@ -319,7 +319,9 @@ struct FinishRun {
   // (set by finish_layout)
   int rest, n_reqs, wide;
   unsigned strips;             // requests (bits) whose object gradient is summed in strips
-  unsigned at[kMaxReqs + 1];   // first workgroup of each request, then of the positions
+  // first workgroup of each request's object-gradient tiles, and of the rest of its work,
+  // which comes after the tiles of all (a tile takes longest); then that of the positions
+  unsigned tiles_at[kMaxReqs], rest_at[kMaxReqs + 1];
   unsigned first;              // first workgroup of this launch
 };
 constexpr int kFinishTY = 4;      // rows of an object-gradient tile
@@ -357,36 +359,51 @@ __host__ __device__ inline FinishParts finish_parts(const FinishRun& p, const Re
 // theirs; returns how many there are. chain: one contribution per mode.
 inline unsigned finish_layout(FinishRun& p, const ReqTable& reqs, int n_reqs, int n_items, int N, bool chain,
                               bool rest) {
-  unsigned g = 0;
   p.rest = rest ? 1 : 0;
   p.n_reqs = n_reqs;
   long long pixels = 0, most = 0;
-  for (int q = 0; q < n_reqs; ++q) {
-    pixels += reqs.r[q].gphat ? (long long)reqs.r[q].M * N * N : 0;
-    most = most > reqs.r[q].n_items ? most : reqs.r[q].n_items;
-  }
-  p.wide = finish_wide(pixels, most) ? 1 : 0;
   p.strips = 0;
-  for (int q = 0; q <= kMaxReqs; ++q) p.at[q] = ~0u;
   for (int q = 0; q < n_reqs; ++q) {
     const ReqDev& r = reqs.r[q];
     const int slices = r.S - p.lo < p.slices ? r.S - p.lo : p.slices;
     if (r.gobj && slices > 0 && sum_in_strips(N, r.n_items, chain ? r.M : 1, r.H, r.W, slices)) p.strips |= 1u << q;
-    p.at[q] = g;
-    const FinishParts f = finish_parts(p, r, q, N);
-    g += f.gather + f.probe + f.loss;
+    pixels += r.gphat ? (long long)r.M * N * N : 0;
+    most = most > r.n_items ? most : r.n_items;
   }
-  p.at[n_reqs] = g;
+  p.wide = finish_wide(pixels, most) ? 1 : 0;
+  unsigned g = 0;
+  for (int q = 0; q < kMaxReqs; ++q) {
+    p.tiles_at[q] = q < n_reqs ? g : ~0u;
+    if (q < n_reqs) g += finish_parts(p, reqs.r[q], q, N).gather;
+  }
+  for (int q = 0; q <= kMaxReqs; ++q) {
+    p.rest_at[q] = q <= n_reqs ? g : ~0u;
+    if (q >= n_reqs) continue;
+    const FinishParts f = finish_parts(p, reqs.r[q], q, N);
+    g += f.probe + f.loss;
+  }
   return rest ? g + (unsigned)(n_items + 511) / 512 : g;
 }
-// Request of workgroup g (n_reqs: the positions).
-__host__ __device__ inline int finish_request(const FinishRun& p, unsigned g) {
-  int q = -1;
+// Work of workgroup g: its request (n_reqs: the positions) and which of its tiles, or
+// which of the rest.
+struct FinishWork {
+  bool tile;
+  int req;
+  unsigned index;
+};
+__host__ __device__ inline FinishWork finish_work(const FinishRun& p, unsigned g) {
+  FinishWork w{g < p.rest_at[0], -1, 0};
 #if defined(__HIP_DEVICE_COMPILE__)
 #pragma unroll
 #endif
-  for (int k = 0; k <= kMaxReqs; ++k) q += p.at[k] <= g ? 1 : 0;
-  return q;
+  for (int k = 0; k <= kMaxReqs; ++k) {
+    const unsigned at = !w.tile ? p.rest_at[k] : k < kMaxReqs ? p.tiles_at[k] : ~0u;
+    if (at <= g) {
+      w.req = k;
+      w.index = g - at;
+    }
+  }
+  return w;
 }
 void launch_finish(const LaunchCtx& L, int N, FinishRun p, bool rest, float scale);
 

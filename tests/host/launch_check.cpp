@@ -44,21 +44,27 @@ static int walk(const std::vector<ReqDev>& rs, int N, int lo, int slices, bool r
   need(blocks == want, "workgroups of the request sizes");
   int launches = 0;
   unsigned next = 0;
+  std::vector<unsigned> tiles(rs.size()), others(rs.size());
   for (p.first = 0; p.first < blocks; p.first += kFinishBlocks, ++launches) {
     const unsigned n = blocks - p.first < kFinishBlocks ? blocks - p.first : kFinishBlocks;
     need((unsigned long long)n * 512 < (1ull << 32), "threads of a launch");
     for (unsigned g = p.first; g < p.first + n; ++g) {
-      const int q = finish_request(p, g);
+      const FinishWork w = finish_work(p, g);
+      const int q = w.req;
       if (q < 0 || q > (int)rs.size()) { need(false, "a workgroup of no request"); return launches; }
       need(g == next++, "workgroups in turn");
-      const unsigned own = g - p.at[q];
       if (q == (int)rs.size()) {
-        need(rest && (int)own * 512 < n_items, "positions");
+        need(rest && !w.tile && (int)w.index * 512 < n_items, "positions");
         continue;
       }
       const FinishParts f = finish_parts(p, t.r[q], q, N);
-      if (own >= f.gather + f.probe + f.loss) { need(false, "past the request's work"); return launches; }
+      if (w.index >= (w.tile ? f.gather : f.probe + f.loss)) { need(false, "past the request's work"); return launches; }
+      (w.tile ? tiles : others)[q] += 1;
     }
+  }
+  for (size_t q = 0; q < rs.size(); ++q) {
+    const FinishParts f = finish_parts(p, t.r[q], (int)q, N);
+    need(tiles[q] == f.gather && others[q] == f.probe + f.loss, "all of a request's work");
   }
   need(next == blocks, "the last workgroup");
   return launches;
