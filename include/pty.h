@@ -168,8 +168,8 @@ int32_t pty_checkpoint_every(const pty_ctx* ctx);
  * object gradient in batch order under either reduction; they need float
  * checkpoints, a propagator that separates into a k_y and a k_x factor (any
  * circular band limit, or a mask whose rows are centred intervals) and
- * obj_w <= 2^20. Two-pass where that is faster: with one slice and 8 modes or more
- * of many positions, and, except under PTY_REDUCE_ORDERED and in grouped steps of
+ * obj_w <= 2^20. Two-pass where that is faster: with one slice and several modes of
+ * many positions, and, except under PTY_REDUCE_ORDERED and in grouped steps of
  * several requests, with few positions at N = 128. Everything else under AUTO,
  * and the ePIE and LSQML engines, run TWO_PASS. */
 #define PTY_STRATEGY_AUTO 0

@@ -332,9 +332,11 @@ bool chain_few(int N, int M, int S, int B) {
 // many: a chain leaves a contribution of every mode in memory, which with one slice
 // and many modes is more traffic than it saves.
 //   128 x 128, 1 slice, 8 modes, 16 positions 170, 138; 128: 360, 418
+//              1 slice, 3 modes, 128 positions 183, 184; 512: 578, 645
 //   64 x 64, 1 slice, 8 modes, 128 positions 127, 117; 256: 210, 242
 bool chain_many(int N, int M, int S, int B) {
-  return S == 1 && M >= 8 && (N == 64 ? B >= 256 : (long long)B * M > 512);
+  if (S > 1) return false;
+  return N == 64 ? M >= 8 && B >= 256 : M > 1 && (long long)B * M >= (M >= 8 ? 520 : 768);
 }
 
 // Does a call with B positions run the chain kernels? Under the ordered reduction

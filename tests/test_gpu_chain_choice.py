@@ -37,14 +37,15 @@ def _grad(c, d, strategy="auto", reduction="atomic", chunk=0, streams=1):
 @pytest.mark.parametrize("N,M,S,B,chain", [
     (64, 1, 1, 1, True), (64, 8, 1, 255, True), (64, 8, 1, 256, False), (64, 7, 1, 256, True), (64, 8, 2, 256, True),
     (128, 1, 1, 511, False), (128, 1, 1, 512, True), (128, 2, 1, 63, False), (128, 2, 1, 64, True),
-    (128, 7, 1, 18, False), (128, 8, 1, 1, True), (128, 8, 1, 64, True), (128, 8, 1, 65, False),
+    (128, 7, 1, 18, False), (128, 8, 1, 1, True), (128, 8, 1, 64, True), (128, 8, 1, 65, False), (128, 2, 1, 383, True),
+    (128, 2, 1, 384, False), (128, 7, 1, 110, False), (128, 1, 1, 800, True),
     (128, 1, 2, 63, False), (128, 1, 2, 64, True), (128, 2, 2, 31, False), (128, 2, 2, 32, True),
     (128, 3, 2, 1, True), (128, 1, 3, 63, False), (128, 1, 3, 64, True), (128, 2, 3, 1, True)])
 def test_default_takes_the_faster_kernels(N, M, S, B, chain):
     c = _case(N, M, S, B)
     d = c.device()
     got, two = _grad(c, d), _grad(c, d, "two_pass")
-    many = S == 1 and M >= 8 and not chain
+    many = S == 1 and not chain and M * B > 128 and M > 1
     ordered = _grad(c, d, reduction="ordered")
     for a, b in zip(got, ordered if chain else two):
         assert torch.equal(a, b)
