@@ -476,7 +476,8 @@ def kernel_source_hash():
     import hashlib
     import re
     h = hashlib.sha256()
-    for p in ("pty_kernels.hip", "pty_device.hpp", "pty_fft.hpp", "pty_internal.h"):
+    for p in ("pty_kernels.hip", "pty_finish.hip", "pty_chain.hip", "pty_chain.hpp", "pty_device.hpp", "pty_fft.hpp",
+              "pty_internal.h"):
         with open(os.path.join(ROOT, "paper_2505_14372_amd", "csrc", p)) as f:
             text = f.read()
         text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)
