@@ -231,7 +231,7 @@ __global__ __launch_bounds__(kThreads, N == 192 && !EMAX && !WHOLE ? 3 : 1) void
                                                       const ReqTable reqs,
                                                       float2* __restrict__ ws, void* __restrict__ ck_,
                                                       const float2* __restrict__ twg, int step,
-                                                      PsiStore store, int item_off, int split) {
+                                                      PsiStore store, int item_off, int per) {
   // items in reverse order (the column passes run them forward; see Launch::col)
   const int by = gridDim.y - 1 - blockIdx.y;
   constexpr int L = Pass<N>::L, E = Pass<N>::E, LINES = Pass<N>::LINES;
@@ -242,8 +242,11 @@ __global__ __launch_bounds__(kThreads, N == 192 && !EMAX && !WHOLE ? 3 : 1) void
   const Item it = items[item_off + by];
   const ReqDev& r = reqs.r[it.req];
   const int i = step;
-  const int m_lo = split ? blockIdx.z : 0, m_hi = split ? m_lo + 1 : r.M;
-  if (!it.valid || i >= r.S || m_lo >= r.M) return;
+  // per: modes a workgroup. (S and M are asked for together and tested at once: M by
+  // itself is one more scalar load to wait for in a launch of few workgroups, 420 against
+  // 418 us for a forward of one mode, 22 slices, 9 positions at 256 x 256.)
+  const int n_slices = r.S, n_modes = r.M, m_lo = (int)blockIdx.z * per, m_hi = min(n_modes, m_lo + per);
+  if ((int)(it.valid == 0) | (int)(i >= n_slices) | (int)(m_lo >= n_modes)) return;
   load_twiddles<N>(tw, twg);
   __syncthreads();
   using CT = typename Ck<HALF>::T;
@@ -1071,16 +1074,17 @@ struct Launch {
     // workgroups of whole items), 625 -> 584 at 32 (192); forward: 299 -> 282 at 48
     // (288), against 470 -> 477 at 100 (600). At 256 x 256, 4 modes, 6 slices: 245 ->
     // 229 at 16 (256), against 761 -> 770 at 100 (1600).
-    const int split = !L.emax && L.max_modes > 1 && (int)Pass<N>::NBLK * L.n_items <= 320;
+    const bool split = !L.emax && L.max_modes > 1 && (int)Pass<N>::NBLK * L.n_items <= 320;
+    const int per = split ? 1 : L.max_modes;
     dim3 g(Pass<N>::NBLK, L.n_items, split ? L.max_modes : 1);
     if (from_real)
-      hipLaunchKernelGGL((k_row_fwd<N, true, HALF>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, st, L.item_off, split);
+      hipLaunchKernelGGL((k_row_fwd<N, true, HALF>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, st, L.item_off, per);
     else if (L.emax)
-      hipLaunchKernelGGL((k_row_fwd<N, false, HALF, true>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, st, L.item_off, split);
+      hipLaunchKernelGGL((k_row_fwd<N, false, HALF, true>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, st, L.item_off, per);
     else if (whole_exchange((long long)g.x * g.y * g.z))
-      hipLaunchKernelGGL((k_row_fwd<N, false, HALF, false, Xch<N>::COL_SPLIT>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, st, L.item_off, split);
+      hipLaunchKernelGGL((k_row_fwd<N, false, HALF, false, Xch<N>::COL_SPLIT>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, st, L.item_off, per);
     else
-      hipLaunchKernelGGL((k_row_fwd<N, false, HALF>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, st, L.item_off, split);
+      hipLaunchKernelGGL((k_row_fwd<N, false, HALF>), g, dim3(kThreads), 0, L.stream, L.items, L.reqs, L.ws, L.ck, L.tw, step, st, L.item_off, per);
   }
   static void rows_fwd(const LaunchCtx& L, int step, PsiStore st, bool from_real) {
     if (L.ck_half) rows_fwd_t<true>(L, step, st, from_real);
