@@ -179,8 +179,9 @@ pty_status pty_set_strategy(pty_ctx* ctx, int32_t strategy);
 
 /* How the object gradient (Sec. 3.2: the sum over the group of every
  * position's windowed contribution, slice by slice) is accumulated.
- * ATOMIC (default): no order is promised. Large groups of many modes at N = 256
- * add each contribution with float atomics in the adjoint row pass (the last
+ * ATOMIC (default): no order is promised. Large groups of many modes at N = 256,
+ * and few positions with half checkpoints, recomputed slices or LSQML, add
+ * each contribution with float atomics in the adjoint row pass (the last
  * bits of the gradient then vary from run to run); the others, faster so, take
  * the sum of the ORDERED mode. ORDERED: the adjoint stores each position's
  * contribution (in the slice's checkpoint, or in a scratch area allocated at

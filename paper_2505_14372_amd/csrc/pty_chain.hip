@@ -292,10 +292,12 @@ __global__ __launch_bounds__(Ch<N>::T) void k_chain_begin(const ReqTable reqs, i
 //               tile (real space).
 // A far field or detector gradient that the next launch takes over waits in
 // the work tile (transposed).
-// Bound by vector arithmetic where there are fewer tiles than the CUs hold
-// (about 100 operations per value and slice; 8 us a slice with two 64 x 64
-// tiles per CU), by the checkpoints' traffic beyond (128 x 128, 4 modes, 8 slices,
-// 1024 positions: forward 1.9, adjoint 2.7 ms; the two passes took 2.6 and 3.7).
+// With few tiles bound by too few waves to hide barriers and loads: 8 and 10 us a slice
+// with 450 tiles of 64 x 64 (6 of 16 waves a CU, vector issue 0.5 of the time), 26 and 34
+// us with 277 of 128 x 128 (6 waves, 0.36 and 0.30). With many, by vector issue and the
+// checkpoints' traffic together: 128 x 128, 4 modes, 8 slices, 1024 positions forward
+// 1.9 ms (14 waves, issue 0.73, 4.2 TB/s), adjoint 2.7 ms (0.55, 4.7 TB/s); the two passes
+// took 2.6 and 3.7.
 template <int N, int WHAT>
 __global__ __launch_bounds__(Ch<N>::T, 4) void k_chain(
     const Item* __restrict__ items, const ReqTable reqs, float2* __restrict__ ws, float2* __restrict__ ck,

@@ -22,7 +22,8 @@ constexpr int kProbeSplit = 16;   // interleaved sums of the probe-spectrum grad
 //     positions per workgroup behind barriers, 8 x 64 tiles and 4 waves, this
 //     launch took 36 us at 64 x 64, 1 slice, 256 positions (now 15), 53 us at 2
 //     modes, 8 slices (35; 118 MB of contributions) and 1.15 ms at 128 x 128, 4
-//     modes, 8 slices, 1024 positions (1.07; 4.3 GB, read at 4.0 TB/s);
+//     modes, 8 slices, 1024 positions (1.10; 4.3 GB of contributions, 5.6 GB of counted
+//     traffic at 5.1 TB/s);
 //   - probe-spectrum gradient: gphat_m(u) = scale sum_b h_hat_{b,m}(u) conj(R_b(u)),
 //     16 interleaved sums over the items, added in order (finish_pixels); for the
 //     requests whose final pass kept these sums (chain_final), the 16 tiles it
