@@ -54,7 +54,9 @@ struct Item {
 // The fields that every row and column pass reads come first: with the item pointer
 // in front of a kernel's table, those of the first request share one 64-byte line.
 // Spread over four lines, a pass waited for them one after the other: forward of one
-// mode, 22 slices, 9 positions 418 -> 405 us at 256 x 256 and 429 -> 413 at 192 x 192.
+// mode, 22 slices, 9 positions 418 -> 405 us at 256 x 256 and 429 -> 413 at 192 x 192. The
+// next line holds the rest of what the last sums read, the one after that what makes the
+// items and the noise model.
 struct ReqDev {
   const float2* obj;        // [S][H][W]
   int S, M, H, W;
@@ -68,30 +70,30 @@ struct ReqDev {
   const float2* prop;       // [S-1][N][N] propagators divided by N^2
   const float2* phat;       // [M][N][N] unitary probe spectrum
   float2* gobj;             // [S][H][W] or null
-  const float* patterns;    // [J][N][N] or null
-  float* I_out;             // [n_items][N][N] or null
-  int loss;
-  float eps, inv_sigma2;
-  int modulus;              // far-field weight: 0 loss gradient, 1 modulus update (ePIE, LSQML)
+  int item0, n_items;
   const double* scale_dev;  // device double multiplying the adjoint's outputs (gradient of the
                             // caller's objective with respect to the loss), or null (1)
-  float* emax;              // [n_items][S][2] window maxima of sum_m |psi_i|^2 and |O_i|^2 (ePIE) or null
-  float* wsum;              // [S][H][W] scatter of sum_m |psi_i|^2 (LSQML) or null
-  int item0, n_items;
-  long long ck_base;        // first checkpoint tile of this request
-  int tile_base;            // first workspace tile of this request
-  int J;
-  const float* positions;   // [J][2]
-  const int32_t* batch_idx; // [n_items]
-  double* loss_out;         // device double or null
-  float* gpos;              // [n_items][2] or null
-  float* gpos_dense;        // [J][2] or null
-  float2* gphat;            // [M][N][N] probe-spectrum gradient (scratch) or null
   int accumulate;           // add into gpos (chain kernels: gobj too) instead of overwriting
   int chain_final;          // the final column pass walks this request's items in kProbeSplit
                             // chains and keeps the probe-gradient sums in registers
                             // (k_col_final_chain) instead of storing h_hat (set per launch by
                             // set_chain_final); k_finish adds either
+  float2* gphat;            // [M][N][N] probe-spectrum gradient (scratch) or null
+  double* loss_out;         // device double or null
+  const float* patterns;    // [J][N][N] or null
+  float* I_out;             // [n_items][N][N] or null
+  int loss;
+  float eps, inv_sigma2;
+  int modulus;              // far-field weight: 0 loss gradient, 1 modulus update (ePIE, LSQML)
+  long long ck_base;        // first checkpoint tile of this request
+  int tile_base;            // first workspace tile of this request
+  int J;
+  const float* positions;   // [J][2]
+  const int32_t* batch_idx; // [n_items]
+  float* emax;              // [n_items][S][2] window maxima of sum_m |psi_i|^2 and |O_i|^2 (ePIE) or null
+  float* wsum;              // [S][H][W] scatter of sum_m |psi_i|^2 (LSQML) or null
+  float* gpos;              // [n_items][2] or null
+  float* gpos_dense;        // [J][2] or null
   const float2* probe;      // [M][N][N] (chain kernels: transformed by their first launch)
 };
 
@@ -396,8 +398,15 @@ struct FinishWork {
   int req;
   unsigned index;
 };
+// (One request, the usual case, needs two comparisons; the search through the tables takes
+// 0.3 us of a launch of 15.)
 __host__ __device__ inline FinishWork finish_work(const FinishRun& p, unsigned g) {
   FinishWork w{g < p.rest_at[0], -1, 0};
+  if (p.n_reqs == 1) {
+    w.req = g >= p.rest_at[1] ? 1 : 0;
+    w.index = w.tile ? g : g - (w.req ? p.rest_at[1] : p.rest_at[0]);
+    return w;
+  }
 #if defined(__HIP_DEVICE_COMPILE__)
 #pragma unroll
 #endif
